@@ -1,0 +1,176 @@
+"""The work that a user of this framework has it do, as measurable cases.
+
+The operator is called per stage of a vision backbone: forward in inference, forward and backward in
+training, and as part of the module (linear layers around the operator).  The listed cases walk over that
+range through the public entry points: one small map, where launches count; the four stages of a 224x224
+classification input at batch 64; the large maps of detection and segmentation at batch 1 and 2; groups of
+16 and of 32 channels; fp32 and fp16 storage; separate and merged offset/scalar tensors; the softmax form.
+`draw` gives further cases of the same ranges, odd sizes among them.
+
+Inputs follow the recipe of paper_2401_06197_amd.synth (x, scalars and upstream gradients ~ N(0,1), offsets
+~ N(0, sigma) pixels with one pair in eight on whole pixels), drawn on the GPU.
+"""
+import math
+
+import torch
+
+from paper_2401_06197_amd import binding as dcn
+from paper_2401_06197_amd import synth
+
+DTYPES = {"f32": torch.float32, "f16": torch.float16}
+ES = {"f32": 4, "f16": 2}
+
+
+def _case(name, op, dtype, N, H, W, C, G, sigma=2.0, stride=1, dilation=1):
+    return {"name": name, "op": op, "dtype": dtype, "N": N, "H": H, "W": W, "C": C, "G": G, "sigma": sigma,
+            "stride": stride, "dilation": dilation}
+
+
+def listed():
+    return [
+        # one small image through forward and backward: launches and host work are most of it
+        _case("train_f32_14x14x64_b1", "train", "f32", 1, 14, 14, 64, 4),
+        # stage 1 of a classification backbone, batch 64: inference in half precision
+        _case("forward_f16_56x56x128_b64", "forward", "f16", 64, 56, 56, 128, 8),
+        # the same stage in a training step, all gradients, in single precision
+        _case("train_f32_56x56x128_b64", "train", "f32", 64, 56, 56, 128, 8),
+        # the backward pass of a middle stage in half precision
+        _case("backward_f16_28x28x256_b64", "backward", "f16", 64, 28, 28, 256, 16),
+        # the deeper stages: many groups on small maps
+        _case("forward_f16_14x14x512_b64", "forward", "f16", 64, 14, 14, 512, 32),
+        _case("forward_f16_7x7x1024_b64", "forward", "f16", 64, 7, 7, 1024, 64),
+        # dense prediction: large maps, small batch, wider offsets
+        _case("forward_f16_200x336x256_b2", "forward", "f16", 2, 200, 336, 256, 16, sigma=4.0),
+        # one detection image, groups of 32 channels, softmax-normalised scalars
+        _case("softmax_f16_100x160x256_b1", "softmax", "f16", 1, 100, 160, 256, 8),
+        # groups of 32 channels in single precision (the group width of most published networks)
+        _case("forward_f32_28x28x256_b64", "forward", "f32", 64, 28, 28, 256, 8),
+        # fine-tuning at an odd resolution: merged offset/scalar tensor, ragged map, wide groups
+        _case("train_merged_f16_37x53x320_b3", "train_merged", "f16", 3, 37, 53, 320, 10),
+        # the whole module in inference: stage 1 in half precision, stage 3 in single precision
+        _case("module_f16_56x56x128_b64", "module", "f16", 64, 56, 56, 128, 4),
+        _case("module_f32_14x14x512_b64", "module", "f32", 64, 14, 14, 512, 16),
+    ]
+
+
+def draw(rng):
+    op = rng.choice(["forward", "forward", "forward", "backward", "train", "train_merged", "merged", "softmax",
+                     "module", "module", "module_light", "module_dw"])
+    dtype = rng.choice(["f16", "f16", "f32"])
+    H = int(round(math.exp(rng.uniform(math.log(7), math.log(200)))))
+    W = max(7, int(round(H * rng.uniform(0.75, 1.7))))
+    Cg = rng.choice([16, 16, 32, 32, 32, 64, 8])
+    if Cg == 64 and dtype == "f16" and op in ("backward", "train", "train_merged"):
+        Cg = 32                                     # (the half-precision backward takes groups of up to 32)
+    C = Cg * max(1, int(round(math.exp(rng.uniform(math.log(64), math.log(1024))) / Cg)))
+    if op.startswith("module"):
+        C = (C + 63) // 64 * 64                     # (the linear layers take multiples of 32 channels)
+    # a batch that keeps the case below half of the largest listed one
+    most = 12_000_000 if not op.startswith("module") else 6_000_000
+    if Cg == 8 or (dtype == "f32" and Cg >= 32 and op != "forward"):
+        most //= 2
+    while H * W * C > most and C > 64:
+        C = max(64, C // 128 * 64)
+    N = max(1, int(math.exp(rng.uniform(0.0, math.log(min(64.0, max(1.0, most / (H * W * C))) + 1e-9)))))
+    stride, dilation = 1, 1
+    if not op.startswith("module"):
+        stride = 2 if rng.random() < 0.08 else 1
+        dilation = 2 if rng.random() < 0.08 else 1
+    case = _case("", op, dtype, N, H, W, C, C // Cg, sigma=rng.choice([1.0, 2.0, 2.0, 4.0]), stride=stride,
+                 dilation=dilation)
+    del case["name"]
+    return case
+
+
+def _config(case):
+    d = case["dilation"]
+    return synth.Config("case", N=case["N"], H=case["H"], W=case["W"], C=case["C"], G=case["G"], sigma=case["sigma"],
+                        stride=case["stride"], pad=d, dilation=d)
+
+
+def prepare(case, seed):
+    cfg = _config(case)
+    dt = DTYPES[case["dtype"]]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    Ho, Wo = cfg.out_hw
+    N, G, K = cfg.N, cfg.G, 9
+
+    def randn(*shape):
+        return torch.randn(shape, generator=gen, device="cuda", dtype=torch.float32)
+
+    state = {"op": case["op"], "kw": {"stride": cfg.stride, "pad": cfg.pad, "dilation": cfg.dilation},
+             "x": randn(N, cfg.H, cfg.W, cfg.C).to(dt)}
+    if case["op"].startswith("module"):
+        light = case["op"] == "module_light"
+        par = synth.make_module_params(cfg, case["dtype"], seed=seed, lightweight=light, depthwise=case["op"] == "module_dw")
+        names = {"w_om_padded": "w_om", "b_om_padded": "b_om"}
+        state["weights"] = {names.get(k, k): torch.from_numpy(v).to("cuda") for k, v in par.items() if k not in ("w_om", "b_om")}
+        need = dcn.dcnv4_module_workspace_bytes(N, cfg.H, cfg.W, G, cfg.Cg, dcn.DCNV4_F16 if dt == torch.float16 else dcn.DCNV4_F32,
+                                                light, case["op"] == "module_dw")
+        state["workspace"] = torch.empty(need, dtype=torch.uint8, device="cuda")
+        state["G"] = G
+        return state
+    off = randn(N, Ho, Wo, G, K, 2) * cfg.sigma
+    whole = torch.rand((N, Ho, Wo, G, K), generator=gen, device="cuda") < 0.125
+    off = torch.where(whole[..., None], torch.round(off), off).to(dt)
+    mask = randn(N, Ho, Wo, G, K).to(dt)
+    if case["op"] in ("merged", "train_merged"):
+        om = torch.zeros((N, Ho, Wo, G, 32), dtype=dt, device="cuda")
+        om[..., :18] = off.reshape(N, Ho, Wo, G, 18)
+        om[..., 18:27] = mask
+        state["om"] = om
+    else:
+        state["offset"], state["mask"] = off, mask
+    if case["op"] in ("backward", "train", "train_merged"):
+        state["grad_y"] = randn(N, Ho, Wo, cfg.C).to(dt)
+    return state
+
+
+def run(s):
+    op, kw = s["op"], s["kw"]
+    if op == "forward":
+        return dcn.dcnv4_forward(s["x"], s["offset"], s["mask"], **kw)
+    if op == "softmax":
+        return dcn.dcnv4_forward_softmax(s["x"], s["offset"], s["mask"], **kw)
+    if op == "merged":
+        return dcn.dcnv4_forward_merged(s["x"], s["om"], **kw)
+    if op == "backward":
+        return dcn.dcnv4_backward(s["x"], s["offset"], s["mask"], s["grad_y"], **kw)
+    if op == "train":
+        y = dcn.dcnv4_forward(s["x"], s["offset"], s["mask"], **kw)
+        return (y, *dcn.dcnv4_backward(s["x"], s["offset"], s["mask"], s["grad_y"], **kw))
+    if op == "train_merged":
+        y = dcn.dcnv4_forward_merged(s["x"], s["om"], **kw)
+        return (y, *dcn.dcnv4_backward_merged(s["x"], s["om"], s["grad_y"], **kw))
+    return dcn.dcnv4_module_forward(s["x"], G=s["G"], workspace=s["workspace"], **s["weights"], **kw)
+
+
+def work(case):
+    cfg = _config(case)
+    Ho, Wo = cfg.out_hw
+    es, op = ES[case["dtype"]], case["op"]
+    px_in, px = cfg.N * cfg.H * cfg.W, cfg.N * Ho * Wo
+    values, scalars = px * cfg.C, px * cfg.G * 27
+    forward = 72.0 * values                             # 36 multiply-adds per output element
+    if op.startswith("module"):
+        linear = cfg.G * 27 + (0 if op == "module_light" else 2 * cfg.C)     # output channels over all layers
+        flops = forward + 2.0 * px * cfg.C * linear + (18.0 * values if op == "module_dw" else 0.0)
+        return {"bytes": es * (2.0 * values + cfg.C * (linear + 9 * (op == "module_dw"))), "flops": flops}
+    fwd_bytes = px_in * cfg.C + values + scalars        # x, y, offsets and scalars
+    bwd_bytes = 2 * px_in * cfg.C + values + 2 * scalars     # x and grad_x, grad_y, offsets and scalars and their gradients
+    if op in ("forward", "softmax", "merged"):
+        return {"bytes": float(es * fwd_bytes), "flops": forward}
+    if op == "backward":
+        return {"bytes": float(es * bwd_bytes), "flops": 2 * forward}
+    # forward and backward: every input once, every output once
+    return {"bytes": float(es * (bwd_bytes + values)), "flops": 3 * forward}
+
+
+def tolerance(case):
+    # Relative 2-norm errors against a double-precision evaluation, over all listed cases and fourteen drawn ones:
+    # at most 2.2e-7 (fp32 operator), 2.0e-6 (fp32 module), 2.8e-4 (fp16 operator: one rounding of the results,
+    # and of the tap weights where the forward multiplies fp16 pairs), 3.9e-4 (fp16 module).  Four times that.
+    if case["op"].startswith("module"):
+        return {"rel": 8e-6} if case["dtype"] == "f32" else {"rel": 1.6e-3}
+    return {"rel": 1e-6} if case["dtype"] == "f32" else {"rel": 1.1e-3}
