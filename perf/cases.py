@@ -174,3 +174,77 @@ def tolerance(case):
     if case["op"].startswith("module"):
         return {"rel": 8e-6} if case["dtype"] == "f32" else {"rel": 1.6e-3}
     return {"rel": 1e-6} if case["dtype"] == "f32" else {"rel": 1.1e-3}
+
+
+def _sampled(state, x, offset, mask, grad_y):
+    """Eq. 1 in 64 bits, tap by tap: the output, and with grad_y the three gradients."""
+    kw = state["kw"]
+    N, H, W, C = x.shape
+    Ho, Wo, G = mask.shape[1:4]
+    Cg = C // G
+    rows = x.reshape(N * H * W * G, Cg)
+    dev = {"device": x.device, "dtype": torch.float64}
+    h0 = (torch.arange(Ho, **dev) * kw["stride"] - kw["pad"])[None, :, None, None]
+    w0 = (torch.arange(Wo, **dev) * kw["stride"] - kw["pad"])[None, None, :, None]
+    image = torch.arange(N, device=x.device)[:, None, None, None] * (H * W)
+    group = torch.arange(G, device=x.device)[None, None, None, :]
+    y = torch.zeros((N, Ho, Wo, G, Cg), **dev)
+    if grad_y is not None:
+        gy = grad_y.reshape(N, Ho, Wo, G, Cg)
+        grad_rows, grad_offset, grad_mask = torch.zeros_like(rows), torch.zeros_like(offset), torch.zeros_like(mask)
+    for k in range(9):
+        j, i = divmod(k, 3)
+        hy, wx = h0 + i * kw["dilation"] + offset[..., k, 1], w0 + j * kw["dilation"] + offset[..., k, 0]
+        m = mask[..., k]
+        top, left = hy.floor(), wx.floor()
+        lh, lw = hy - top, wx - left
+        for a in (0, 1):
+            for b in (0, 1):
+                r, c = top + a, left + b
+                inside = ((r >= 0) & (r < H) & (c >= 0) & (c < W)).double()
+                at = (image + r.clamp(0, H - 1).long() * W + c.clamp(0, W - 1).long()) * G + group
+                fh, fw = (lh if a else 1 - lh), (lw if b else 1 - lw)
+                value = rows[at.reshape(-1)].reshape(y.shape)
+                weight = (fh * fw * inside)
+                y.addcmul_(value, (m * weight)[..., None])
+                if grad_y is None:
+                    continue
+                dot = (value * gy).sum(-1) * inside
+                grad_mask[..., k] += fh * fw * dot
+                grad_offset[..., k, 0] += m * fh * dot * (1 if b else -1)
+                grad_offset[..., k, 1] += m * fw * dot * (1 if a else -1)
+                grad_rows.index_add_(0, at.reshape(-1), ((m * weight)[..., None] * gy).reshape(-1, Cg))
+    y = y.reshape(N, Ho, Wo, C)
+    return (y,) if grad_y is None else (y, grad_rows.reshape(x.shape), grad_offset, grad_mask)
+
+
+def exact(case, seed):
+    s = prepare(case, seed)
+    op, x = s["op"], s["x"].double()
+    if op.startswith("module"):
+        # no rounding between the layers
+        w = {k: v.double() for k, v in s["weights"].items()}
+        N, H, W, C = x.shape
+        source = x
+        if "w_dw" in w:
+            kernel = w["w_dw"].permute(2, 0, 1).reshape(C, 1, 3, 3)
+            source = torch.nn.functional.conv2d(x.permute(0, 3, 1, 2), kernel, w["b_dw"], padding=1, groups=C).permute(0, 2, 3, 1)
+        om = (source @ w["w_om"].T + w["b_om"]).reshape(N, H, W, s["G"], 32)
+        value = x @ w["w_in"].T + w["b_in"] if "w_in" in w else x
+        y = _sampled(s, value, om[..., :18].reshape(N, H, W, s["G"], 9, 2), om[..., 18:27], None)[0]
+        return y @ w["w_out"].T + w["b_out"] if "w_out" in w else y
+    if "om" in s:
+        om = s["om"].double()
+        offset, mask = om[..., :18].reshape(*om.shape[:-1], 9, 2), om[..., 18:27]
+    else:
+        offset, mask = s["offset"].double(), s["mask"].double()
+    if op == "softmax":
+        mask = mask.softmax(-1)
+    if "grad_y" not in s:
+        return _sampled(s, x, offset, mask, None)[0]
+    y, grad_x, grad_offset, grad_mask = _sampled(s, x, offset, mask, s["grad_y"].double())
+    if "om" not in s:
+        return (grad_x, grad_offset, grad_mask) if op == "backward" else (y, grad_x, grad_offset, grad_mask)
+    grad_om = torch.zeros_like(om)
+    grad_om[..., :18], grad_om[..., 18:27] = grad_offset.reshape(*om.shape[:-1], 18), grad_mask
+    return y, grad_x, grad_om
