@@ -352,6 +352,7 @@ __global__ __launch_bounds__(kThreads) void dcnv4_fwd_kernel(const T *__restrict
 }
 
 #include "dcnv4_tiled.inc"
+#include "dcnv4_gradx.inc"
 #include "dcnv4_ring.inc"
 #include "dcnv4_linear.inc"
 
@@ -1270,6 +1271,173 @@ int dispatch_bwd_cpt(int cpt, const void *x, const void *off, const void *msk, c
     return DCNV4_ERR_UNSUPPORTED;
 }
 
+// ---- grad_x through dcnv4_gradx_kernel ----------------------------------------------------------
+constexpr int kMaxHaloGradX = 8;
+
+struct GxLaunch {
+    GxGeo p;
+    int lds;
+    unsigned grid;
+};
+
+// Tile choice: output rows per band x columns per tile whose cells fit the LDS, by an estimate of the time (in
+// clocks) of the busiest compute unit.  Returns false where no tile fits.
+bool choose_gx_tile(const Problem &q, int waves, int halo, int max_halo, int lds_bytes, int slices, int cus, GxGeo *p)
+{
+    const int max_cells = lds_bytes / (kGxCell + 4) - 2;
+    auto ceil_div = [](long long a, long long b) { return (a + b - 1) / b; };
+    // Rows (columns) the largest rectangle of a split into parts of `len` outputs can have; `border`: cells kept
+    // outside the image on each side.  Columns need one more cell unless every tile goes from border to border.
+    auto extent = [&](int out, int len, int size, int s, int pad, int dil, int h, int border, bool columns) {
+        const long long parts = ceil_div(out, len), span = (long long)(len - 1) * s + 2LL * dil + 2LL * h + 2;
+        if (parts > 8)                                     // (many parts: those inside are not clipped)
+            return (span < size + 2 * border ? span : size + 2 * border) + (columns ? 1 : 0);
+        long long most = 0;
+        for (long long k = 0; k < parts; ++k) {
+            const long long o0 = k * len, n = out - o0 < len ? out - o0 : len;
+            const long long want = o0 * s - pad - h, end = (o0 + n - 1) * s - pad + 2LL * dil + h + 2;
+            const long long lo = want > -border ? want : -border, hi = end < size + border ? end : size + border;
+            const long long e = (hi - lo > 0 ? hi - lo : 0) + (columns && !(want <= -border && end >= size + border) ? 1 : 0);
+            if (e > most) most = e;
+        }
+        return most;
+    };
+    double best = 1e30;
+    bool found = false;
+    int splits = 0;
+    for (int kq = 1; kq <= q.Wo && splits < 12; ++kq) {
+        const int Q = (int)ceil_div(q.Wo, kq);
+        if (kq > 1 && Q == (int)ceil_div(q.Wo, kq - 1))
+            continue;
+        const long long cols = extent(q.Wo, Q, q.W, q.sw, q.pw, q.dw, halo, 1, true);
+        if (cols < 1 || cols > max_cells)
+            continue;
+        const int tiles_q = (int)ceil_div(q.Wo, Q);
+        bool fits = false;
+        int last_r = 0;
+        for (int bands = 1; bands <= q.Ho && bands <= 256; bands += bands < 32 ? 1 : bands / 16) {
+            const int R = (int)ceil_div(q.Ho, bands);
+            if (R == last_r)
+                continue;
+            last_r = R;
+            const long long rows = extent(q.Ho, R, q.H, q.sh, q.ph, q.dh, halo, 2, false);
+            if (rows * cols > max_cells || (long long)R * Q >= (1 << 20))
+                continue;
+            fits = true;
+            const long long tiles = (long long)q.N * q.G * slices * ceil_div(q.Ho, R) * tiles_q;
+            const long long units = ceil_div(R * ceil_div(Q, 4), 4);
+            const long long full = units / waves, rest = units % waves;
+            // a round in which every wave has a unit is bound by the unit's issue slots, one with few waves by its
+            // latency; then the flush, and the drained pipeline at the tile's end
+            const double per_unit = 550.0, latency = 3500.0;
+            const double round = per_unit * waves > latency ? per_unit * waves : latency;
+            const double last = rest == 0 ? 0.0 : per_unit * rest > latency ? per_unit * rest : latency;
+            const double cost = (double)ceil_div(tiles, cus) * (full * round + last + 11.0 * (double)(rows * cols) + 5000.0);
+            if (cost < best) {
+                best = cost;
+                found = true;
+                p->R = R;
+                p->Q = Q;
+                p->pitch = (int)cols;
+                p->tiles_q = tiles_q;
+                p->tiles_per_img = (int)(ceil_div(q.Ho, R) * tiles_q);
+            }
+        }
+        if (fits)
+            ++splits;
+    }
+    if (!found)
+        return false;
+    // what is left of the LDS allows for larger displacements
+    p->halo = halo;
+    for (int h = halo; h <= max_halo; ++h) {
+        const long long rows = extent(q.Ho, p->R, q.H, q.sh, q.ph, q.dh, h, 2, false);
+        const long long cols = extent(q.Wo, p->Q, q.W, q.sw, q.pw, q.dw, h, 1, true);
+        if (rows * cols > max_cells)
+            break;
+        p->halo = h;
+        p->pitch = (int)cols;
+        p->cells = (int)(rows * cols) + 2;
+    }
+    return true;
+}
+
+template <typename T, int WAVES>
+int prepare_gx(const Problem &q, GxLaunch *out)
+{
+    if (q.Cg % kGxChan != 0 || q.softmax)
+        return DCNV4_ERR_UNSUPPORTED;
+    Geo base;
+    int rc = make_geo(q, 1, &base);
+    if (rc)
+        return rc;
+    const long long es = (long long)sizeof(T), pgi = (long long)q.Ho * q.Wo * q.G, lim24 = 1LL << 23;
+    GxGeo p;
+    memset(&p, 0, sizeof(p));
+    p.og_bytes = (int)((q.merged ? 32 : 18) * es);
+    p.mg_bytes = (int)((q.merged ? 32 : 9) * es);
+    // 24-bit multiplications of pixel numbers, strides and positions
+    if (pgi >= 0x1000000 || pgi * p.og_bytes >= (1LL << 31) || base.pix_bytes >= lim24 || q.Ho >= lim24 || q.Wo >= lim24 ||
+        q.sh >= lim24 || q.sw >= lim24)
+        return DCNV4_ERR_UNSUPPORTED;
+    const int cus = device_cus();
+    if (cus <= 0)
+        return DCNV4_ERR_LAUNCH;
+    p.slices = q.Cg / kGxChan;
+    const int lds = (g_opt.lds_kb ? g_opt.lds_kb : kMaxLdsBytes / 1024) * 1024;
+    const int halo = g_opt.halo ? g_opt.halo : kDefaultHaloGradX;
+    if (!choose_gx_tile(q, WAVES, halo, g_opt.halo ? halo : kMaxHaloGradX, lds, p.slices, cus, &p))
+        return DCNV4_ERR_UNSUPPORTED;
+    const long long nblocks = (long long)q.N * p.tiles_per_img * q.G * p.slices;
+    if (nblocks >= (1LL << 30))
+        return DCNV4_ERR_UNSUPPORTED;
+    p.Wo = q.Wo; p.Ho = q.Ho; p.G = q.G; p.H = q.H; p.W = q.W;
+    p.sh = q.sh; p.sw = q.sw; p.ph = q.ph; p.pw = q.pw; p.dh = q.dh; p.dw = q.dw;
+    p.scale = q.scale;
+    p.dmax = base.dmax;
+    p.quads_row = (p.Q + 3) / 4;
+    p.div_quads = make_div((unsigned)p.quads_row);
+    p.nblocks = (int)nblocks;
+    p.blocks_per_xcd = (int)((nblocks + kXcds - 1) / kXcds);
+    p.remap = g_opt.xcd_remap;
+    p.div_g = make_div((unsigned)q.G);
+    p.div_s = make_div((unsigned)p.slices);
+    p.div_tpi = make_div((unsigned)p.tiles_per_img);
+    p.div_tq = make_div((unsigned)p.tiles_q);
+    p.group_bytes = (int)(q.Cg * es);
+    p.pix_bytes = base.pix_bytes;
+    p.row_bytes = base.row_bytes;
+    p.x_img_bytes = base.x_img_bytes;
+    p.y_img_bytes = base.y_img_bytes;
+    p.off_img_bytes = (int)(pgi * p.og_bytes);
+    p.msk_img_bytes = (int)(pgi * p.mg_bytes);
+    p.off_ext_bytes = (int)((pgi - 1) * p.og_bytes + 18 * es);
+    p.msk_ext_bytes = (int)((pgi - 1) * p.mg_bytes + 9 * es);
+    out->p = p;
+    out->lds = p.cells * (kGxCell + 4);
+    static int granted[kMaxDevices];
+    if (!grant_lds(reinterpret_cast<const void *>(dcnv4_gradx_kernel<T, WAVES>), out->lds, granted))
+        return DCNV4_ERR_LAUNCH;
+    if (p.remap) {
+        const int per = cus / kXcds < p.blocks_per_xcd ? cus / kXcds : p.blocks_per_xcd;
+        out->grid = (unsigned)(per * kXcds);
+    } else {
+        out->grid = (unsigned)(cus < p.nblocks ? cus : p.nblocks);
+    }
+    return DCNV4_OK;
+}
+
+template <typename T, int WAVES>
+int run_gx(const GxLaunch &l, const void *off, const void *msk, const void *gy, void *gx, hipStream_t s)
+{
+    hipLaunchKernelGGL((dcnv4_gradx_kernel<T, WAVES>), dim3(l.grid), dim3(WAVES * 64), l.lds, s, (const T *)off, (const T *)msk,
+                       (const T *)gy, (T *)gx, l.p);
+    const size_t had = strlen(g_last_kernel[1]);             // (the grad_offset/grad_mask pass, launched just before)
+    snprintf(g_last_kernel[1] + had, sizeof(g_last_kernel[1]) - had, " + dcnv4_gradx_kernel<%s, %d>",
+             sizeof(T) == 2 ? "_Float16" : "float", WAVES);
+    return hipGetLastError() == hipSuccess ? DCNV4_OK : DCNV4_ERR_LAUNCH;
+}
+
 // Backward through the LDS-staged kernels: zero-fill of grad_x, then the grad_offset/grad_mask
 // pass (gathers, like the forward) and the grad_x pass (LDS-private accumulation, one flush per
 // tile).  Both passes are prepared -- everything that can refuse -- before anything is launched,
@@ -1302,6 +1470,15 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
     }
     if (rc)
         return rc;
+    GxLaunch l_gx16;
+    rc = gxt == 768   ? prepare_gx<T, 12>(q, &l_gx16)
+         : gxt == 512 ? prepare_gx<T, 8>(q, &l_gx16)
+                      : prepare_gx<T, 4>(q, &l_gx16);
+    if (rc != DCNV4_OK && rc != DCNV4_ERR_UNSUPPORTED)
+        return rc;
+    const bool use_gx16 = rc == DCNV4_OK;
+    if (use_gx16) {
+    } else
     rc = gxt == 768   ? prepare_tiled<T, CG, 768, kTiledGradX>(q, any_size, 0, 0, &l_gx)
          : gxt == 512 ? prepare_tiled<T, CG, 512, kTiledGradX>(q, any_size, 0, 0, &l_gx)
                       : prepare_tiled<T, CG, 256, kTiledGradX>(q, any_size, 0, 0, &l_gx);
@@ -1313,7 +1490,7 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
         if (zb < 1) zb = 1;
         hipLaunchKernelGGL(dcnv4_zero_kernel, dim3((unsigned)zb), dim3(kThreads), 0, s, (u32x4 *)ptr, bytes);
     };
-    zero(gx, (long long)q.N * l_gx.p.x_img_bytes);
+    zero(gx, (long long)q.N * l_gom.p.x_img_bytes);
     if (q.merged) {
         zero(go, (long long)q.N * l_gom.p.off_img_bytes);       // one buffer: gradients and padding
     } else if (sliced) {
@@ -1326,6 +1503,10 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
     } else {
         rc = run_tiled<T, CG, THREADS, kTiledGradOM>(l_gom, x, off, msk, gy, go, gm, s, 1);
     }
+    if (rc == DCNV4_OK && use_gx16)
+        return gxt == 768   ? run_gx<T, 12>(l_gx16, off, msk, gy, gx, s)
+               : gxt == 512 ? run_gx<T, 8>(l_gx16, off, msk, gy, gx, s)
+                            : run_gx<T, 4>(l_gx16, off, msk, gy, gx, s);
     if (rc == DCNV4_OK)
         rc = gxt == 768   ? run_tiled<T, CG, 768, kTiledGradX>(l_gx, x, off, msk, gy, gx, nullptr, s, 1)
              : gxt == 512 ? run_tiled<T, CG, 512, kTiledGradX>(l_gx, x, off, msk, gy, gx, nullptr, s, 1)
