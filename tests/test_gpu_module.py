@@ -193,3 +193,33 @@ def test_module_refusals_leave_y_untouched():
     assert e.value.status == 2
     torch.cuda.synchronize()
     assert bool((out == 7.0).all())
+
+
+@pytest.mark.parametrize("P,K,nout", [(1, 8, 32), (33, 40, 32), (129, 72, 160), (300, 264, 96), (64, 1000, 64)],
+                         ids=lambda v: str(v))
+def test_linear_fp32_from_split_operands(P, K, nout):
+    """Odd numbers of 8-channel groups, K past one chunk, magnitudes over many orders; bound: 32-bit sums of K
+    products, 2^-24 * K^0.5 of the 2-norms' product (observed: a third of it)."""
+    g = torch.Generator().manual_seed(P + K)
+    scale = torch.exp(torch.randn(K, generator=g) * 3)
+    x = torch.randn(P, K, generator=g) * scale
+    w = torch.randn(nout, K, generator=g)
+    y = dcn.dcnv4_linear(x.cuda(), w.cuda(), None).double().cpu()
+    ref = x.double() @ w.double().T
+    lim = 2.0 ** -24 * K ** 0.5 * x.double().norm(dim=1)[:, None] * w.double().norm(dim=1)[None, :]
+    assert ((y - ref).abs() <= lim + 1e-30).all(), ((y - ref).abs() / lim).max()
+
+
+def test_linear_fp32_infinities_and_large_numbers_are_those_of_fp32():
+    """One row with an infinity, one with a NaN, one with numbers that round to infinity in bf16: the outputs are
+    what 32-bit products give (their neighbours in the same wave included)."""
+    x = torch.ones(64, 16)
+    x[3, 5], x[7, 2], x[9] = float("inf"), float("nan"), 0.0
+    x[9, 0] = torch.finfo(torch.float32).max
+    w = torch.full((32, 16), 0.5)
+    w[1] = -0.25
+    y = dcn.dcnv4_linear(x.cuda(), w.cuda(), None).cpu()
+    ref = x.double() @ w.double().T
+    assert torch.equal(torch.isnan(y), torch.isnan(ref)) and torch.equal(torch.isinf(y), torch.isinf(ref))
+    fin = torch.isfinite(ref)
+    assert (y[fin].double() / ref[fin] - 1).abs().max() < 1e-6 and torch.equal(y[3] > 0, ref[3] > 0)
