@@ -12,6 +12,8 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "dcnv4.h"
 
 namespace {
@@ -1278,13 +1280,15 @@ struct GxLaunch {
     GxGeo p;
     int lds;
     unsigned grid;
+    int waves;
 };
 
 // Tile choice: output rows per band x columns per tile whose cells fit the LDS, by an estimate of the time (in
-// clocks) of the busiest compute unit.  Returns false where no tile fits.
-bool choose_gx_tile(const Problem &q, int waves, int halo, int max_halo, int lds_bytes, int slices, int cus, GxGeo *p)
+// clocks) of the busiest compute unit, `per_cu` workgroups of `waves` waves on each.  Returns false where no tile fits.
+bool choose_gx_tile(const Problem &q, int waves, int per_cu, int halo, int max_halo, int lds_bytes, int slices, int cus,
+                    GxGeo *p, double *cost_out)
 {
-    const int max_cells = lds_bytes / (kGxCell + 4) - 2;
+    const int max_cells = (lds_bytes - kGxCell) / (kGxCell + 4) - 2;
     auto ceil_div = [](long long a, long long b) { return (a + b - 1) / b; };
     // Rows (columns) the largest rectangle of a split into parts of `len` outputs can have; `border`: cells kept
     // outside the image on each side.  Columns need one more cell unless every tile goes from border to border.
@@ -1326,13 +1330,14 @@ bool choose_gx_tile(const Problem &q, int waves, int halo, int max_halo, int lds
             fits = true;
             const long long tiles = (long long)q.N * q.G * slices * ceil_div(q.Ho, R) * tiles_q;
             const long long units = ceil_div(R * ceil_div(Q, 4), 4);
-            const long long full = units / waves, rest = units % waves;
-            // a round in which every wave has a unit is bound by the unit's issue slots, one with few waves by its
-            // latency; then the flush, and the drained pipeline at the tile's end
-            const double per_unit = 550.0, latency = 3500.0;
-            const double round = per_unit * waves > latency ? per_unit * waves : latency;
-            const double last = rest == 0 ? 0.0 : per_unit * rest > latency ? per_unit * rest : latency;
-            const double cost = (double)ceil_div(tiles, cus) * (full * round + last + 11.0 * (double)(rows * cols) + 5000.0);
+            // the wave with the most units of 16 pixels: per batch of up to four of them the evaluation, per unit the
+            // adds, shared with the other waves of its SIMD; then the flush, which the workgroups of a unit share as
+            // well, and the drained pipeline at the tile's end
+            const long long most = ceil_div(units, waves), slots = (long long)cus * per_cu;
+            const double resident = (double)(tiles < slots ? ceil_div(tiles, cus) : per_cu);
+            const double simd = resident * (waves < units ? waves : (double)units) / 4.0;
+            const double batches = (simd > 1.0 ? simd : 1.0) * (2900.0 * ceil_div(most, 4) + 1200.0 * most);
+            const double cost = (double)ceil_div(tiles, slots) * (batches + 9.0 * resident * (double)(rows * cols) + 5000.0);
             if (cost < best) {
                 best = cost;
                 found = true;
@@ -1346,6 +1351,7 @@ bool choose_gx_tile(const Problem &q, int waves, int halo, int max_halo, int lds
         if (fits)
             ++splits;
     }
+    *cost_out = best;
     if (!found)
         return false;
     // what is left of the LDS allows for larger displacements
@@ -1362,7 +1368,7 @@ bool choose_gx_tile(const Problem &q, int waves, int halo, int max_halo, int lds
     return true;
 }
 
-template <typename T, int WAVES>
+template <typename T>
 int prepare_gx(const Problem &q, GxLaunch *out)
 {
     if (q.Cg % kGxChan != 0 || q.softmax)
@@ -1384,9 +1390,29 @@ int prepare_gx(const Problem &q, GxLaunch *out)
     if (cus <= 0)
         return DCNV4_ERR_LAUNCH;
     p.slices = q.Cg / kGxChan;
-    const int lds = (g_opt.lds_kb ? g_opt.lds_kb : kMaxLdsBytes / 1024) * 1024;
-    const int halo = g_opt.halo ? g_opt.halo : kDefaultHaloGradX;
-    if (!choose_gx_tile(q, WAVES, halo, g_opt.halo ? halo : kMaxHaloGradX, lds, p.slices, cus, &p))
+    const int halo = g_opt.halo ? g_opt.halo : kDefaultHaloGradX, max_halo = g_opt.halo ? halo : kMaxHaloGradX;
+    // Twelve waves per compute unit either way, in one workgroup or, where that makes small tiles, in three, whose
+    // flushes and tile switches overlap and whose waves get whole batches (14x14x512, 32 groups, batch 64, fp32: 106 us
+    // in one, 59 in three; two of six waves do not fit a unit's SIMDs together: 28x28x256 fp16 115 -> 150)
+    struct {
+        int waves, per_cu;
+    } shapes[2] = {{12, 1}, {4, 3}}, pick = {0, 0};
+    const int nshapes = g_opt.gx_threads ? 1 : 2;
+    if (g_opt.gx_threads)
+        shapes[0].waves = g_opt.gx_threads / 64;
+    double best = 1e30;
+    const GxGeo common = p;
+    for (int i = 0; i < nshapes; ++i) {
+        GxGeo t = common;
+        double cost = 0;
+        int lds = (g_opt.lds_kb ? g_opt.lds_kb * 1024 : kMaxLdsBytes) / shapes[i].per_cu & ~1023;
+        if (choose_gx_tile(q, shapes[i].waves, shapes[i].per_cu, halo, max_halo, lds, p.slices, cus, &t, &cost) && cost < best) {
+            best = cost;
+            pick = shapes[i];
+            p = t;
+        }
+    }
+    if (pick.waves == 0)
         return DCNV4_ERR_UNSUPPORTED;
     const long long nblocks = (long long)q.N * p.tiles_per_img * q.G * p.slices;
     if (nblocks >= (1LL << 30))
@@ -1395,6 +1421,7 @@ int prepare_gx(const Problem &q, GxLaunch *out)
     p.sh = q.sh; p.sw = q.sw; p.ph = q.ph; p.pw = q.pw; p.dh = q.dh; p.dw = q.dw;
     p.scale = q.scale;
     p.dmax = base.dmax;
+    p.bound_bytes = (p.cells * 4 + kGxCell - 1) / kGxCell * kGxCell;
     p.quads_row = (p.Q + 3) / 4;
     p.div_quads = make_div((unsigned)p.quads_row);
     p.nblocks = (int)nblocks;
@@ -1414,27 +1441,35 @@ int prepare_gx(const Problem &q, GxLaunch *out)
     p.off_ext_bytes = (int)((pgi - 1) * p.og_bytes + 18 * es);
     p.msk_ext_bytes = (int)((pgi - 1) * p.mg_bytes + 9 * es);
     out->p = p;
-    out->lds = p.cells * (kGxCell + 4);
-    static int granted[kMaxDevices];
-    if (!grant_lds(reinterpret_cast<const void *>(dcnv4_gradx_kernel<T, WAVES>), out->lds, granted))
+    out->lds = p.bound_bytes + p.cells * kGxCell;
+    out->waves = pick.waves;
+    static int granted[4][kMaxDevices];
+    const void *kern = pick.waves == 12  ? reinterpret_cast<const void *>(dcnv4_gradx_kernel<T, 12>)
+                       : pick.waves == 8 ? reinterpret_cast<const void *>(dcnv4_gradx_kernel<T, 8>)
+                                         : reinterpret_cast<const void *>(dcnv4_gradx_kernel<T, 4>);
+    if (!grant_lds(kern, out->lds, granted[pick.waves / 4]))
         return DCNV4_ERR_LAUNCH;
+    const int slots = cus * pick.per_cu;
     if (p.remap) {
-        const int per = cus / kXcds < p.blocks_per_xcd ? cus / kXcds : p.blocks_per_xcd;
+        const int per = slots / kXcds < p.blocks_per_xcd ? slots / kXcds : p.blocks_per_xcd;
         out->grid = (unsigned)(per * kXcds);
     } else {
-        out->grid = (unsigned)(cus < p.nblocks ? cus : p.nblocks);
+        out->grid = (unsigned)(slots < p.nblocks ? slots : p.nblocks);
     }
     return DCNV4_OK;
 }
 
-template <typename T, int WAVES>
+template <typename T>
 int run_gx(const GxLaunch &l, const void *off, const void *msk, const void *gy, void *gx, hipStream_t s)
 {
-    hipLaunchKernelGGL((dcnv4_gradx_kernel<T, WAVES>), dim3(l.grid), dim3(WAVES * 64), l.lds, s, (const T *)off, (const T *)msk,
-                       (const T *)gy, (T *)gx, l.p);
+    auto kern = l.waves == 12  ? dcnv4_gradx_kernel<T, 12>
+                : l.waves == 8 ? dcnv4_gradx_kernel<T, 8>
+                               : dcnv4_gradx_kernel<T, 4>;
+    hipLaunchKernelGGL(kern, dim3(l.grid), dim3((unsigned)l.waves * 64), l.lds, s, (const T *)off, (const T *)msk, (const T *)gy,
+                       (T *)gx, l.p);
     const size_t had = strlen(g_last_kernel[1]);             // (the grad_offset/grad_mask pass, launched just before)
     snprintf(g_last_kernel[1] + had, sizeof(g_last_kernel[1]) - had, " + dcnv4_gradx_kernel<%s, %d>",
-             sizeof(T) == 2 ? "_Float16" : "float", WAVES);
+             sizeof(T) == 2 ? "_Float16" : "float", l.waves);
     return hipGetLastError() == hipSuccess ? DCNV4_OK : DCNV4_ERR_LAUNCH;
 }
 
@@ -1471,17 +1506,15 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
     if (rc)
         return rc;
     GxLaunch l_gx16;
-    rc = gxt == 768   ? prepare_gx<T, 12>(q, &l_gx16)
-         : gxt == 512 ? prepare_gx<T, 8>(q, &l_gx16)
-                      : prepare_gx<T, 4>(q, &l_gx16);
+    rc = prepare_gx<T>(q, &l_gx16);
     if (rc != DCNV4_OK && rc != DCNV4_ERR_UNSUPPORTED)
         return rc;
+    // (groups of 8 channels and the softmax form stay with the accumulation by lanes = pixels)
     const bool use_gx16 = rc == DCNV4_OK;
-    if (use_gx16) {
-    } else
-    rc = gxt == 768   ? prepare_tiled<T, CG, 768, kTiledGradX>(q, any_size, 0, 0, &l_gx)
-         : gxt == 512 ? prepare_tiled<T, CG, 512, kTiledGradX>(q, any_size, 0, 0, &l_gx)
-                      : prepare_tiled<T, CG, 256, kTiledGradX>(q, any_size, 0, 0, &l_gx);
+    if (!use_gx16)
+        rc = gxt == 768   ? prepare_tiled<T, CG, 768, kTiledGradX>(q, any_size, 0, 0, &l_gx)
+             : gxt == 512 ? prepare_tiled<T, CG, 512, kTiledGradX>(q, any_size, 0, 0, &l_gx)
+                          : prepare_tiled<T, CG, 256, kTiledGradX>(q, any_size, 0, 0, &l_gx);
     if (rc)
         return rc;
     auto zero = [&](void *ptr, long long bytes) {
@@ -1504,9 +1537,7 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
         rc = run_tiled<T, CG, THREADS, kTiledGradOM>(l_gom, x, off, msk, gy, go, gm, s, 1);
     }
     if (rc == DCNV4_OK && use_gx16)
-        return gxt == 768   ? run_gx<T, 12>(l_gx16, off, msk, gy, gx, s)
-               : gxt == 512 ? run_gx<T, 8>(l_gx16, off, msk, gy, gx, s)
-                            : run_gx<T, 4>(l_gx16, off, msk, gy, gx, s);
+        return run_gx<T>(l_gx16, off, msk, gy, gx, s);
     if (rc == DCNV4_OK)
         rc = gxt == 768   ? run_tiled<T, CG, 768, kTiledGradX>(l_gx, x, off, msk, gy, gx, nullptr, s, 1)
              : gxt == 512 ? run_tiled<T, CG, 512, kTiledGradX>(l_gx, x, off, msk, gy, gx, nullptr, s, 1)
