@@ -1523,7 +1523,17 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
         if (zb < 1) zb = 1;
         hipLaunchKernelGGL(dcnv4_zero_kernel, dim3((unsigned)zb), dim3(kThreads), 0, s, (u32x4 *)ptr, bytes);
     };
-    zero(gx, (long long)q.N * l_gom.p.x_img_bytes);
+    // grad_x: by the grad_offset/grad_mask pass on the way, in whole 16-byte units (its pixels have 16 bytes or more);
+    // 32-bit unit numbers
+    const long long gx_units = (long long)q.N * l_gom.p.x_img_bytes / 16;
+    const long long per_tile = (gx_units + l_gom.p.nblocks - 1) / l_gom.p.nblocks;
+    if (gx_units + per_tile < (1LL << 31)) {
+        l_gom.p.zero = (u32x4 *)gx;
+        l_gom.p.zero_units = (unsigned)gx_units;
+        l_gom.p.zero_per_tile = (unsigned)per_tile;
+    } else {
+        zero(gx, (long long)q.N * l_gom.p.x_img_bytes);
+    }
     if (q.merged) {
         zero(go, (long long)q.N * l_gom.p.off_img_bytes);       // one buffer: gradients and padding
     } else if (sliced) {
