@@ -1308,6 +1308,17 @@ bool choose_gx_tile(const Problem &q, int waves, int per_cu, int halo, int max_h
     };
     double best = 1e30;
     bool found = false;
+    // the band heights, with their rectangles' rows
+    struct {
+        int R;
+        long long rows;
+    } heights[128];
+    int nheights = 0;
+    for (int bands = 1; bands <= q.Ho && bands <= 256 && nheights < 128; bands += bands < 32 ? 1 : bands / 16) {
+        const int R = (int)ceil_div(q.Ho, bands);
+        if (nheights == 0 || R != heights[nheights - 1].R)
+            heights[nheights++] = {R, extent(q.Ho, R, q.H, q.sh, q.ph, q.dh, halo, 2, false)};
+    }
     int splits = 0;
     for (int kq = 1; kq <= q.Wo && splits < 12; ++kq) {
         const int Q = (int)ceil_div(q.Wo, kq);
@@ -1318,25 +1329,23 @@ bool choose_gx_tile(const Problem &q, int waves, int per_cu, int halo, int max_h
             continue;
         const int tiles_q = (int)ceil_div(q.Wo, Q);
         bool fits = false;
-        int last_r = 0;
-        for (int bands = 1; bands <= q.Ho && bands <= 256; bands += bands < 32 ? 1 : bands / 16) {
-            const int R = (int)ceil_div(q.Ho, bands);
-            if (R == last_r)
-                continue;
-            last_r = R;
-            const long long rows = extent(q.Ho, R, q.H, q.sh, q.ph, q.dh, halo, 2, false);
+        for (int h = 0; h < nheights; ++h) {
+            const int R = heights[h].R;
+            const long long rows = heights[h].rows;
             if (rows * cols > max_cells || (long long)R * Q >= (1 << 20))
                 continue;
             fits = true;
-            const long long tiles = (long long)q.N * q.G * slices * ceil_div(q.Ho, R) * tiles_q;
-            const long long units = ceil_div(R * ceil_div(Q, 4), 4);
+            const int bands = (int)ceil_div(q.Ho, R);
+            const long long tiles = (long long)q.N * q.G * slices * bands * tiles_q;
+            const int units = (int)ceil_div(R * ceil_div(Q, 4), 4);
             // the wave with the most units of 16 pixels: per batch of up to four of them the evaluation, per unit the
             // adds, shared with the other waves of its SIMD; then the flush, which the workgroups of a unit share as
             // well, and the drained pipeline at the tile's end
-            const long long most = ceil_div(units, waves), slots = (long long)cus * per_cu;
-            const double resident = (double)(tiles < slots ? ceil_div(tiles, cus) : per_cu);
-            const double simd = resident * (waves < units ? waves : (double)units) / 4.0;
-            const double batches = (simd > 1.0 ? simd : 1.0) * (2900.0 * ceil_div(most, 4) + 1200.0 * most);
+            const int most = (units + waves - 1) / waves;
+            const long long slots = (long long)cus * per_cu;
+            const double resident = tiles < slots ? (double)ceil_div(tiles, cus) : (double)per_cu;
+            const double simd = resident * (waves < units ? waves : units) / 4.0;
+            const double batches = (simd > 1.0 ? simd : 1.0) * (2900.0 * ((most + 3) / 4) + 1200.0 * most);
             const double cost = (double)ceil_div(tiles, slots) * (batches + 9.0 * resident * (double)(rows * cols) + 5000.0);
             if (cost < best) {
                 best = cost;
@@ -1345,7 +1354,7 @@ bool choose_gx_tile(const Problem &q, int waves, int per_cu, int halo, int max_h
                 p->Q = Q;
                 p->pitch = (int)cols;
                 p->tiles_q = tiles_q;
-                p->tiles_per_img = (int)(ceil_div(q.Ho, R) * tiles_q);
+                p->tiles_per_img = bands * tiles_q;
             }
         }
         if (fits)
