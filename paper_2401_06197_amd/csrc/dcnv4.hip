@@ -1372,7 +1372,8 @@ bool choose_gx_tile(const Problem &q, int waves, int per_cu, int halo, int max_h
             break;
         p->halo = h;
         p->pitch = (int)cols;
-        p->cells = (int)(rows * cols) + 2;
+        // (at least a row: taps that stay out of the cells book on the corners of cell 0)
+        p->cells = (int)((rows > 1 ? rows : 1) * cols) + 2;
     }
     return true;
 }
