@@ -1483,8 +1483,8 @@ int run_gx(const GxLaunch &l, const void *off, const void *msk, const void *gy, 
     return hipGetLastError() == hipSuccess ? DCNV4_OK : DCNV4_ERR_LAUNCH;
 }
 
-// Backward through the LDS-staged kernels: zero-fill of grad_x, then the grad_offset/grad_mask
-// pass (gathers, like the forward) and the grad_x pass (LDS-private accumulation, one flush per
+// Backward through the LDS-staged kernels: the grad_offset/grad_mask pass (gathers, like the forward;
+// it clears grad_x on its way) and the grad_x pass (LDS-private accumulation, one flush per
 // tile).  Both passes are prepared -- everything that can refuse -- before anything is launched,
 // so a call that returns an error has written nothing.
 template <typename T, int CG>
