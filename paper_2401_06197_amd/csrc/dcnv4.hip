@@ -781,9 +781,14 @@ bool choose_tile(const Problem &q, int threads, int halo, int lds_bytes, int nbu
         if (Rmax > q.Ho) Rmax = q.Ho;
         if (Rmax < 1 || (Rmax < need && Rmax < q.Ho) || (Q < need && Q < q.Wo))
             continue;
+        const long long Rlow = Rmax < need ? Rmax : need;
+        if (accum && Rmax * Q > kFixMaxTilePixels) {        // (the bound words must not wrap)
+            Rmax = kFixMaxTilePixels / Q;
+            if (Rmax < Rlow)
+                continue;
+        }
         ++splits_tried;
         const int tiles_q = (q.Wo + Q - 1) / Q;
-        const long long Rlow = Rmax < need ? Rmax : need;
         for (long long R = Rmax; R >= Rlow; --R) {
             const long long bands = (q.Ho + R - 1) / R, Rlast = q.Ho - (bands - 1) * R;
             const long long b_full = (R * Q + 63) / 64, b_last = (Rlast * Q + 63) / 64;
@@ -1332,7 +1337,7 @@ bool choose_gx_tile(const Problem &q, int waves, int per_cu, int halo, int max_h
         for (int h = 0; h < nheights; ++h) {
             const int R = heights[h].R;
             const long long rows = heights[h].rows;
-            if (rows * cols > max_cells || (long long)R * Q >= (1 << 20))
+            if (rows * cols > max_cells || (long long)R * Q > kFixMaxTilePixels)     // (the bound words must not wrap)
                 continue;
             fits = true;
             const int bands = (int)ceil_div(q.Ho, R);

@@ -701,3 +701,27 @@ def test_grad_x_tiles(cfg, dtype, opts):
     assert "dcnv4_gradx_kernel<" in dcn.dcnv4_last_kernel_name(1)
     rgx = oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"], **geo_kw(cfg))[0]
     close(f"{cfg.name}/{dtype}/grad_x", gom[0].cpu().numpy(), rgx, TOL[dtype])
+
+
+@pytest.mark.parametrize("Cg", [8, 16])
+def test_grad_x_of_a_large_tile_that_piles_up_on_one_pixel(Cg):
+    """Wide padding around a small map puts tens of thousands of output pixels over a few cells.  Every tap of every
+    one of them is steered to pixel (3, 3) with a term of 60, so 186 * 186 * 9 bookings of 60 * 2^8 + 1 = 4.8e9 go to
+    that pixel's 32-bit bound word if they share a tile.  All sums are multiples of 4 below 2^26: fp32 holds them
+    exactly, in any order, and the result must be exact.  (N * G = 256: one tile per compute unit would be the whole
+    map.)"""
+    N, G, H, P = 64, 4, 8, 90
+    Ho = H + 2 * P - 2
+    lane = torch.arange(3, device="cuda", dtype=torch.float32)
+    at = 3.0 - (torch.arange(Ho, device="cuda", dtype=torch.float32) - P)
+    off = torch.empty((N, Ho, Ho, G, 3, 3, 2), device="cuda")               # taps k = 3 * column + row
+    off[..., 0] = at[None, None, :, None, None, None] - lane[:, None]
+    off[..., 1] = at[None, :, None, None, None, None] - lane[None, :]
+    mask = torch.ones((N, Ho, Ho, G, 9), device="cuda")
+    x = torch.zeros((N, H, H, G * Cg), device="cuda")
+    gy = torch.full((N, Ho, Ho, G * Cg), 60.0, device="cuda")
+    gx = dcn.dcnv4_backward(x, off.reshape(N, Ho, Ho, G, 9, 2), mask, gy, pad=P)[0]
+    torch.cuda.synchronize()
+    want = torch.zeros_like(gx)
+    want[:, 3, 3] = 60.0 * 9 * Ho * Ho
+    assert torch.equal(gx, want), (gx - want).abs().max()
