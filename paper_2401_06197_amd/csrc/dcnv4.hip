@@ -908,7 +908,7 @@ int make_tgeo(const Problem &q, int threads, int mode, TGeo *out, int cg_kernel 
 // that can refuse (tile choice, LDS size, LDS grant, device query) and launches nothing; run_tiled
 // launches what was prepared.  `which` = 0 forward, 1 backward (for the kernel-name record).
 struct TiledLaunch {
-    TGeo p;
+    TGeoClear p;
     int lds;
     unsigned grid;
 };
@@ -951,7 +951,8 @@ int prepare_tiled(const Problem &q, bool any_tile_size, int want_nbuf, int want_
     } else {
         grid = (unsigned)(slots < p.nblocks ? slots : p.nblocks);
     }
-    out->p = p;
+    memset(&out->p, 0, sizeof(out->p));
+    static_cast<TGeo &>(out->p) = p;
     out->lds = lds;
     out->grid = grid;
     return DCNV4_OK;
@@ -962,7 +963,8 @@ int run_tiled(const TiledLaunch &l, const void *x, const void *off, const void *
               hipStream_t s, int which)
 {
     hipLaunchKernelGGL((dcnv4_tiled_kernel<T, CG, THREADS, MODE>), dim3(l.grid), dim3(THREADS), l.lds, s, (const T *)x,
-                       (const T *)off, (const T *)msk, (const T *)gy, (T *)o1, (T *)o2, l.p);
+                       (const T *)off, (const T *)msk, (const T *)gy, (T *)o1, (T *)o2,
+                       static_cast<const TArgs<MODE> &>(l.p));
     snprintf(g_last_kernel[which], sizeof(g_last_kernel[which]), "dcnv4_tiled_kernel<%s, %d, %d, %d>",
              sizeof(T) == 2 ? "_Float16" : "float", CG, THREADS, MODE);
     return hipGetLastError() == hipSuccess ? DCNV4_OK : DCNV4_ERR_LAUNCH;
