@@ -223,3 +223,18 @@ def test_linear_fp32_infinities_and_large_numbers_are_those_of_fp32():
     assert torch.equal(torch.isnan(y), torch.isnan(ref)) and torch.equal(torch.isinf(y), torch.isinf(ref))
     fin = torch.isfinite(ref)
     assert (y[fin].double() / ref[fin] - 1).abs().max() < 1e-6 and torch.equal(y[3] > 0, ref[3] > 0)
+
+
+@pytest.mark.parametrize("ex,ew", [(-104, 0), (-112, 0), (-120, 20), (3, -116), (0, -125), (-60, -60)], ids=str)
+@pytest.mark.parametrize("K", [16, 320])
+def test_linear_fp32_small_numbers_keep_their_bits(K, ex, ew):
+    """Operands down to the denormals, beside rows and output channels of ordinary size: bound as for ordinary
+    numbers (2^-24 * K^0.5 of the 2-norms' product), and 2^-149 a rounding where fp32 has no more bits."""
+    g = torch.Generator().manual_seed(K - ex - ew)
+    x, w = torch.randn(300, K, generator=g), torch.randn(160, K, generator=g)
+    x[40:] *= 2.0 ** ex
+    w[:130] *= 2.0 ** ew
+    y = dcn.dcnv4_linear(x.cuda(), w.cuda(), None).double().cpu()
+    ref = x.double() @ w.double().T
+    lim = 2.0 ** -24 * K ** 0.5 * x.double().norm(dim=1)[:, None] * w.double().norm(dim=1)[None, :] + K * 2.0 ** -149
+    assert ((y - ref).abs() <= lim).all(), ((y - ref).abs() / lim).max()
