@@ -173,7 +173,8 @@ def _call(device, entry, args):
 def _conv_hw(H, W, kh, kw, sh, sw, ph, pw, dh, dw):
     """dcnv4_output_hw, worked out here (a call into the library costs more than the arithmetic)."""
     eh, ew = H + 2 * ph - dh * (kh - 1) - 1, W + 2 * pw - dw * (kw - 1) - 1
-    if min(H, W, kh, kw, sh, sw, dh, dw) < 1 or min(ph, pw, eh, ew) < 0 or max(eh, ew) >= 2 ** 31:
+    if (min(H, W, kh, kw, sh, sw, dh, dw) < 1 or min(ph, pw, eh, ew) < 0
+            or max(kh, kw, sh, sw, ph, pw, dh, dw, eh, ew) >= 2 ** 31 - 1):
         return dcnv4_output_hw(H, W, (kh, kw), (sh, sw), (ph, pw), (dh, dw))      # (refuses, or settles what is left)
     return eh // sh + 1, ew // sw + 1
 

@@ -149,6 +149,28 @@ def test_output_hw_matches_sliding_window_rule(H, W, k, s, p, d):
     assert (ho - 1) * s + d * (k - 1) + 1 <= H + 2 * p < ho * s + d * (k - 1) + 1
 
 
+def test_output_size_of_the_binding_is_the_librarys():
+    """The binding works the size out by itself; it must take, refuse and return what dcnv4_output_hw does, also for
+    numbers that the library's 32-bit arguments wrap."""
+    big = 2 ** 32
+    sizes = [(14, 14), (1, 1), (7, 200), (0, 5), (2 ** 31 - 1, 3)]
+    windows = [((3, 3), (1, 1), (1, 1), (1, 1)), ((3, 3), (2, 3), (0, 2), (1, 2)), ((1, 1), (1, 1), (0, 0), (1, 1)),
+               ((5, 5), (1, 1), (2, 2), (3, 1)), ((3, 3), (0, 1), (1, 1), (1, 1)), ((3, 3), (1, 1), (-1, 1), (1, 1)),
+               ((3, 3), (big + 1, big + 2), (1, 1), (1, 1)), ((3, 3), (1, 1), (big + 1, 1), (1, 1)),
+               ((3, 3), (1, 1), (1, 1), (big + 1, 1)), ((big + 3, 3), (1, 1), (1, 1), (1, 1)), ((1, 1), (1, 1), (1, 1), (big, big)),
+               ((1, 1), (1, 1), (2 ** 30, 0), (1, 1)), ((3, 3), (1, 1), (big, 0), (1, 1))]
+
+    def result(f, H, W, *window):
+        try:
+            return f(H, W, *window)
+        except dcn.Dcnv4Error as e:
+            return e.status
+
+    for H, W in sizes:
+        for k, s, p, d in windows:
+            assert result(dcn._conv_hw, H, W, *k, *s, *p, *d) == result(dcn.dcnv4_output_hw, H, W, k, s, p, d), (H, W, k, s, p, d)
+
+
 def test_algorithmic_bytes_follow_the_ideal_memory_access_model():
     # Sec. 3.2: 2*H*W*C + 27*H*W*G values, each touched once
     assert dcn.dcnv4_forward_algorithmic_bytes(64, 56, 56, 8, 16, 56, 56, dcn.DCNV4_F16) == 189_464_576
