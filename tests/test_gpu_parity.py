@@ -16,10 +16,10 @@ TOL = {"f32": 1e-5, "f16": 2e-2}
 TORCH_DT = {"f32": torch.float32, "f16": torch.float16}
 
 
-def close(name, got, ref, tol):
+def close(name, got, ref, tol, more=0.0):
     got = got.astype(np.float64)
     err = np.abs(got - ref)
-    lim = tol + tol * np.abs(ref)
+    lim = tol + tol * np.abs(ref) + more
     bad = err > lim
     if bad.any():
         idx = np.unravel_index(np.argmax(err - lim), err.shape)
@@ -47,7 +47,7 @@ def check_forward(cfg, dtype, seed=0, inputs=None):
     return close(f"{cfg.name}/{dtype}/y", y.cpu().numpy(), ref, TOL[dtype])
 
 
-def check_backward(cfg, seed=0, inputs=None, dtype="f32"):
+def check_backward(cfg, seed=0, inputs=None, dtype="f32", more_grad_x=0.0):
     t = inputs if inputs is not None else make_inputs(cfg, dtype, seed=seed)
     d = to_gpu(t, dtype)
     # poison the outputs: the call must overwrite all three
@@ -57,7 +57,7 @@ def check_backward(cfg, seed=0, inputs=None, dtype="f32"):
     rgx, rgo, rgm = oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"], **geo_kw(cfg))
     close(f"{cfg.name}/{dtype}/grad_mask", gm.cpu().numpy(), rgm, TOL[dtype])
     close(f"{cfg.name}/{dtype}/grad_offset", go.cpu().numpy(), rgo, TOL[dtype])
-    close(f"{cfg.name}/{dtype}/grad_x", gx.cpu().numpy(), rgx, TOL[dtype])
+    close(f"{cfg.name}/{dtype}/grad_x", gx.cpu().numpy(), rgx, TOL[dtype], more=more_grad_x)
 
 
 # ------------------------------------------------------------------ the five benchmark configs
@@ -655,7 +655,17 @@ def test_every_sample_on_the_same_pixels_contends_but_stays_exact(path):
     try:
         dcn.dcnv4_set_option("bwd_path", path)
         check_forward(cfg, "f32", inputs=t)
-        check_backward(cfg, inputs=t)
+        more = 0.0
+        if path == 1:
+            # The direct kernel adds its n = 1080 terms a pixel to memory one by one, in any order.  An addition is
+            # off by up to 2^-24 of the partial sum, 2^-24 / 3^0.5 in the mean square; a partial sum of terms in random
+            # order is about |ref| + (sum of the squared terms)^0.5.  Six times n^0.5 such errors (observed over
+            # 16000 random orders: up to 2.5).  The four weights are at most 0.5 * 0.75, so that the oracle on squared
+            # inputs bounds the sum of the squared terms.
+            ref = oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"], **geo_kw(cfg))[0]
+            squares = 0.375 * oracle.backward(t["x"], t["offset"], t["mask"] ** 2, t["grad_y"] ** 2, **geo_kw(cfg))[0]
+            more = 6 * 2.0 ** -24 * (1080 / 3) ** 0.5 * (np.abs(ref) + np.sqrt(squares))
+        check_backward(cfg, inputs=t, more_grad_x=more)
         if path == 2:
             h = {k: v.astype(np.float16) for k, v in t.items()}
             check_forward(cfg, "f16", inputs=h)
