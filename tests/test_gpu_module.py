@@ -225,6 +225,22 @@ def test_linear_fp32_infinities_and_large_numbers_are_those_of_fp32():
     assert (y[fin].double() / ref[fin] - 1).abs().max() < 1e-6 and torch.equal(y[3] > 0, ref[3] > 0)
 
 
+@pytest.mark.parametrize("K", [16, 64, 512])
+def test_linear_fp32_rows_with_one_weight(K):
+    """One nonzero weight in each row: the output is one product.  Bound: 2^-23 for the last addition inside the
+    matrix instruction, 2^-24 for the three partial products left out, 2^-30 for the rounding of the small ones."""
+    g = torch.Generator().manual_seed(K)
+    x = torch.randn(1024, K, generator=g)
+    w = torch.zeros(160, K)
+    w[torch.arange(160), torch.randint(0, K, (160,), generator=g)] = torch.randn(160, generator=g)
+    y = dcn.dcnv4_linear(x.cuda(), w.cuda(), None).double().cpu()
+    ref = x.double() @ w.double().T
+    lim = (2.0 ** -23 + 2.0 ** -24 + 2.0 ** -30) * ref.abs()
+    assert ((y - ref).abs() <= lim).all(), ((y - ref) / ref).abs().max()
+    ones = (w != 0).float()                                                  # weights of one: nothing to round
+    assert torch.equal(dcn.dcnv4_linear(x.cuda(), ones.cuda(), None).cpu().double(), x.double() @ ones.double().T)
+
+
 @pytest.mark.parametrize("ex,ew", [(-104, 0), (-112, 0), (-120, 20), (3, -116), (0, -125), (-60, -60)], ids=str)
 @pytest.mark.parametrize("K", [16, 320])
 def test_linear_fp32_small_numbers_keep_their_bits(K, ex, ew):

@@ -687,28 +687,33 @@ def test_every_sample_on_the_same_pixels_contends_but_stays_exact(path):
 GRADX = [Config("gx_rows5", N=2, H=9, W=5, C=32, G=2), Config("gx_rows1", N=1, H=17, W=1, C=16, G=1),
          Config("gx_row3", N=1, H=1, W=3, C=16, G=1, sigma=1.0), Config("gx_odd", N=3, H=23, W=31, C=48, G=3, sigma=4.0),
          Config("gx_s2", N=2, H=22, W=19, C=32, G=2, stride=2, pad=0), Config("gx_d2", N=1, H=16, W=21, C=32, G=2, pad=2, dilation=2),
-         Config("gx_wide32", N=2, H=10, W=90, C=64, G=2), Config("gx_wide64", N=1, H=12, W=13, C=128, G=2)]
+         Config("gx_wide32", N=2, H=10, W=90, C=64, G=2), Config("gx_wide64", N=1, H=12, W=13, C=128, G=2),
+         Config("gx_wide120", N=1, H=9, W=120, C=16, G=1), Config("gx_many", N=16, H=14, W=14, C=512, G=32)]
+# where the tile choice takes three workgroups of four waves per compute unit by itself, not one of twelve
+GRADX_FOUR_WAVES = {("default", "gx_wide32"), ("default", "gx_wide120"), ("default", "gx_many"), ("split", "gx_wide32"),
+                    ("split", "gx_wide120")}
+GRADX_OPTS = {"default": {}, "split": {"lds_kb": 40, "halo": 1}, "four_waves": {"gx_threads": 256, "lds_kb": 64}}
 
 
 @pytest.mark.parametrize("cfg", GRADX, ids=[c.name for c in GRADX])
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
-@pytest.mark.parametrize("opts", [{}, {"lds_kb": 40, "halo": 1}, {"gx_threads": 256, "lds_kb": 64}], ids=["default", "split", "four_waves"])
+@pytest.mark.parametrize("opts", list(GRADX_OPTS))
 def test_grad_x_tiles(cfg, dtype, opts):
     if dtype == "f16" and cfg.C // cfg.G == 64:
         pytest.skip("the half-precision backward takes groups of up to 32 channels")
+    if opts == "split" and cfg.name == "gx_wide120":
+        # a cell takes 64 + 4 bytes, a tile at least 2 * 1 + 2 * 1 + 2 rows: the whole width does not fit 40 KB
+        assert 6 * (cfg.W + 2) * 68 > 40 * 1024
     t = make_inputs(cfg, dtype, seed=11)
     d = to_gpu(t, dtype)
     dcn.dcnv4_set_option("bwd_path", 2)
-    gom = None
-    for k, v in opts.items():
+    for k, v in GRADX_OPTS[opts].items():
         dcn.dcnv4_set_option(k, v)
-    try:
-        gom = dcn.dcnv4_backward(d["x"], d["offset"], d["mask"], d["grad_y"], **geo_kw(cfg))
-    except dcn.Dcnv4Error as e:                    # the grad_offset/grad_mask pass finds no tile in so little LDS
-        assert e.status == 3 and "lds_kb" in opts
-        pytest.skip("no tile of the other pass fits")
+    gom = dcn.dcnv4_backward(d["x"], d["offset"], d["mask"], d["grad_y"], **geo_kw(cfg))      # (none of these is refused)
     torch.cuda.synchronize()
-    assert "dcnv4_gradx_kernel<" in dcn.dcnv4_last_kernel_name(1)
+    waves = 4 if opts == "four_waves" or (opts, cfg.name) in GRADX_FOUR_WAVES else 12
+    kernel = f"dcnv4_gradx_kernel<{'_Float16' if dtype == 'f16' else 'float'}, {waves}>"
+    assert dcn.dcnv4_last_kernel_name(1).endswith(kernel)
     rgx = oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"], **geo_kw(cfg))[0]
     close(f"{cfg.name}/{dtype}/grad_x", gom[0].cpu().numpy(), rgx, TOL[dtype])
 
