@@ -683,12 +683,14 @@ def test_every_sample_on_the_same_pixels_contends_but_stays_exact(path):
 
 # The grad_x kernel that adds four corners x 16 channels at a time: rows that end inside a run of four pixels,
 # rows shorter than one, tiles split in columns (padding cells instead of border cells), more waves than units,
-# strides and dilations, two and four channel slices per group.
+# strides and dilations, two and four channel slices per group, padding so wide that most samples lie outside and fill
+# the words of the border cells.
 GRADX = [Config("gx_rows5", N=2, H=9, W=5, C=32, G=2), Config("gx_rows1", N=1, H=17, W=1, C=16, G=1),
          Config("gx_row3", N=1, H=1, W=3, C=16, G=1, sigma=1.0), Config("gx_odd", N=3, H=23, W=31, C=48, G=3, sigma=4.0),
          Config("gx_s2", N=2, H=22, W=19, C=32, G=2, stride=2, pad=0), Config("gx_d2", N=1, H=16, W=21, C=32, G=2, pad=2, dilation=2),
          Config("gx_wide32", N=2, H=10, W=90, C=64, G=2), Config("gx_wide64", N=1, H=12, W=13, C=128, G=2),
-         Config("gx_wide120", N=1, H=9, W=120, C=16, G=1), Config("gx_many", N=16, H=14, W=14, C=512, G=32)]
+         Config("gx_wide120", N=1, H=9, W=120, C=16, G=1), Config("gx_many", N=16, H=14, W=14, C=512, G=32),
+         Config("gx_pad", N=1, H=8, W=8, C=32, G=2, pad=25, sigma=6.0)]
 # where the tile choice takes three workgroups of four waves per compute unit by itself, not one of twelve
 GRADX_FOUR_WAVES = {("default", "gx_wide32"), ("default", "gx_wide120"), ("default", "gx_many"), ("split", "gx_wide32"),
                     ("split", "gx_wide120")}
