@@ -170,13 +170,17 @@ def _call(device, entry, args):
         raise Dcnv4Error(rc, entry)
 
 
+_INT_MAX = 2 ** 31 - 1
+
+
 def _conv_hw(H, W, kh, kw, sh, sw, ph, pw, dh, dw):
     """dcnv4_output_hw, worked out here (a call into the library costs more than the arithmetic)."""
     eh, ew = H + 2 * ph - dh * (kh - 1) - 1, W + 2 * pw - dw * (kw - 1) - 1
-    if (min(H, W, kh, kw, sh, sw, dh, dw) < 1 or min(ph, pw, eh, ew) < 0
-            or max(kh, kw, sh, sw, ph, pw, dh, dw, eh, ew) >= 2 ** 31 - 1):
-        return dcnv4_output_hw(H, W, (kh, kw), (sh, sw), (ph, pw), (dh, dw))      # (refuses, or settles what is left)
-    return eh // sh + 1, ew // sw + 1
+    if (0 < H and 0 < W and 0 < kh < _INT_MAX and 0 < kw < _INT_MAX and 0 < sh < _INT_MAX and 0 < sw < _INT_MAX
+            and 0 <= ph < _INT_MAX and 0 <= pw < _INT_MAX and 0 < dh < _INT_MAX and 0 < dw < _INT_MAX
+            and 0 <= eh < _INT_MAX and 0 <= ew < _INT_MAX):
+        return eh // sh + 1, ew // sw + 1
+    return dcnv4_output_hw(H, W, (kh, kw), (sh, sw), (ph, pw), (dh, dw))          # (refuses, or settles what is left)
 
 
 def _shape_args(x, offset, mask, kernel, stride, pad, dilation):
