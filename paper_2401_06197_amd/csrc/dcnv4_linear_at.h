@@ -2,7 +2,7 @@
 //
 // A load has a vector and a scalar byte offset, and the range check that makes it read zero is documented for the vector
 // offset alone.  So what lies past an end -- of K, of a layer's rows, of the last pass -- has the vector offset
-// `outside` and no scalar one; everything else lies inside the tensor with both.
+// `outside`, or a descriptor of no bytes, and no scalar offset; everything else lies inside the tensor with both.
 #pragma once
 
 struct LinAt {
@@ -10,11 +10,18 @@ struct LinAt {
 };
 
 // Unit tid % 16 of row n0 + 16 * i + tid / 16 of a layer's weights, K bytes from kbase on.  nout is a multiple of 32:
-// a unit's 16 rows are all there or all past the last one, so the scalar offset is the same for all threads.
-constexpr LinAt lin_weight_at(int tid, int i, int n0, int kbase, int nout, int kbytes, int outside)
+// the 16 rows of a unit are all there or all past the last one, which is the same for all threads, as is the scalar offset
+// (so the choice takes scalar instructions only: in the vector offset it cost the fp16 layers 1 to 2 %).
+struct LinWeightAt {
+    LinAt at;
+    unsigned bytes;      // of the descriptor
+};
+constexpr LinWeightAt lin_weight_at(int tid, int i, int n0, int kbase, int nout, int kbytes, int outside)
 {
     const int row = n0 + 16 * i, u = (tid & 15) * 16;
-    return {row < nout && kbase + u < kbytes ? (tid >> 4) * kbytes + u : outside, row < nout ? row * kbytes + kbase : 0};
+    const bool in = n0 + 16 * (i & ~1) < nout;             // (32 rows at a time)
+    return {{kbase + u < kbytes ? (tid >> 4) * kbytes + u : outside, in ? row * kbytes + kbase : 0},
+            in ? (unsigned)nout * (unsigned)kbytes : 0u};
 }
 
 // The 32-byte group at byte column col (the same for all lanes) of the pixel row that starts at xo.  Plane-major x: column c

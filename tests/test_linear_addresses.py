@@ -12,7 +12,7 @@ WALK = r"""
 constexpr int kOutside = (int)0x80000000u;
 static void check(const LinAt &at, long long bytes, const char *what, int a, int b, int c, int d)
 {
-    // outside by the vector offset alone, with no scalar one; or all 16 bytes inside
+    // outside by the vector offset alone, or all 16 bytes inside
     const bool ok = at.v == kOutside ? at.s >= 0 && at.s < bytes : at.v >= 0 && at.s >= 0 && (long long)at.v + at.s + 16 <= bytes;
     if (!ok) {
         printf("%s %d %d %d %d: v %d s %d of %lld\n", what, a, b, c, d, at.v, at.s, bytes);
@@ -30,7 +30,13 @@ int main()
                     for (int i = 0; i < 8; ++i) {
                         int s = 0;
                         for (int tid = 0; tid < 256; ++tid) {
-                            const LinAt at = lin_weight_at(tid, i, pass * 128, ch * 256, nout, kbytes, kOutside);
+                            const LinWeightAt w = lin_weight_at(tid, i, pass * 128, ch * 256, nout, kbytes, kOutside);
+                            LinAt at = w.at;
+                            if (w.bytes != 0 && w.bytes != (unsigned)nout * kbytes) return printf("descriptor\n"), 1;
+                            if (w.bytes == 0) {                         // all outside, then, with no scalar offset
+                                if (at.s != 0) return printf("scalar offset with an empty descriptor\n"), 1;
+                                at.v = kOutside;
+                            }
                             check(at, (long long)nout * kbytes, "weights", kbytes, nout, pass, i);
                             if (tid == 0) s = at.s;
                             if (at.s != s) return printf("scalar offset differs between threads\n"), 1;
