@@ -240,6 +240,9 @@ long long dcnv4_backward_merged_algorithmic_bytes(int N, int H, int W, int G, in
  *   "fwd_path"    1 = direct global gather, 2 = input rectangle staged in LDS, 3 = ring of input rows
  *                 in LDS (fp16, Cg 16); 0 = ring on maps of 512 pixels or more, else rectangle where a
  *                 useful tile fits, else direct
+ *   "fwd_strip"   forward out of a rolling window of input rows, in strips of columns (every type and group
+ *                 width; taken with fwd_path 0 where there are batches enough to stream): 1 = wherever it
+ *                 applies, 2 = never
  *   "bwd_path"    1 = one kernel with global atomics for grad_x (fp32), 2 = two LDS-staged kernels
  *                 (gathers for grad_offset/grad_mask; fixed-point accumulation of grad_x in LDS),
  *                 0 = staged where a useful tile fits, else the first

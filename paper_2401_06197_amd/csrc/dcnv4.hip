@@ -356,6 +356,7 @@ __global__ __launch_bounds__(kThreads) void dcnv4_fwd_kernel(const T *__restrict
 #include "dcnv4_tiled.inc"
 #include "dcnv4_gradx.inc"
 #include "dcnv4_ring.inc"
+#include "dcnv4_strip.inc"
 #include "dcnv4_linear.inc"
 
 // ------------------------------------------------------------------------------------------
@@ -520,6 +521,7 @@ struct Options {
     int fwd_single = 0;    // rectangle buffers of the staged gather kernels: 1 always two, 2 always one
     int gx_threads = 0;    // workgroup size of the grad_x kernel (256, 512, 768)
     int gom_coop = 0;      // 1: the fp32 grad_offset/grad_mask pass goes through LDS slices even for whole groups
+    int fwd_strip = 0;     // forward out of a rolling window of rows: 1 wherever it applies, 2 never
     int module_rows = 0;   // 1: the module keeps its tensors channel-last between the layers (default: plane-major)
 } g_opt;
 
@@ -694,6 +696,7 @@ int dispatch_fwd_cpt(int cpt, const void *x, const void *off, const void *msk, v
 constexpr int kTiledZeroPixelsExtra = 2;
 constexpr int kDefaultHalo = 6;
 constexpr int kDefaultHaloGradX = 4;
+constexpr int kStripMinHalo = 4, kStripMaxHalo = 12;
 constexpr int kDefaultLdsKb = 158;
 constexpr int kMaxLdsBytes = 160 * 1024;
 
@@ -1204,6 +1207,218 @@ int dispatch_ring_fwd(const void *x, const void *off, const void *msk, void *y, 
     return launch_ring_fwd<8>(x, off, msk, y, q, s);
 }
 
+// ---- forward out of a rolling window of rows (any type and group width) ----
+constexpr int kStripRow = 1024;              // LDS bytes that one staging instruction fills
+
+struct StripLaunch {
+    SGeo p;
+    int lds;
+    unsigned grid;
+    long long busiest;                       // batches of the busiest workgroup
+};
+
+// Chooses strips of columns, bands of rows, the window's rows and the displacement it allows for, by the batches that
+// the busiest workgroup works through.
+int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out)
+{
+    const long long es = esize(q.dtype), pb = cg_kernel * es, pgi = (long long)q.Ho * q.Wo * q.G;
+    if (q.Cg % cg_kernel != 0)
+        return DCNV4_ERR_UNSUPPORTED;
+    Geo base;
+    int rc = make_geo(q, 1, &base);
+    if (rc)
+        return rc;
+    SGeo p;
+    memset(&p, 0, sizeof(p));
+    p.og_bytes = (int)((q.merged ? 32 : 18) * es);
+    p.mg_bytes = (int)((q.merged ? 32 : 9) * es);
+    // (whole tensors behind one descriptor each)
+    const long long xbytes = (long long)q.N * base.x_img_bytes, ybytes = (long long)q.N * base.y_img_bytes;
+    if (xbytes >= (1LL << 31) || ybytes >= (1LL << 31) || q.N * pgi * p.og_bytes >= (1LL << 31) || q.Ho >= (1 << 15) || q.Wo >= (1 << 15))
+        return DCNV4_ERR_UNSUPPORTED;
+    const int cus = device_cus();
+    if (cus <= 0)
+        return DCNV4_ERR_LAUNCH;
+    p.slices = q.Cg / cg_kernel;
+    // few batches: nothing to stream (2 images of 160x200, 4 groups of 32, fp16, 15.6 batches to a compute unit: 27.3 us by
+    // rectangles, 28.0 by strips)
+    const long long batches = (long long)q.N * q.G * p.slices * (((long long)q.Ho * q.Wo + 63) / 64);
+    if (g_opt.fwd_strip != 1 && batches < 16LL * cus)
+        return DCNV4_ERR_UNSUPPORTED;
+    int lds = (g_opt.lds_kb ? g_opt.lds_kb : kMaxLdsBytes / 1024) * 1024;
+    if (lds > kMaxLdsBytes) lds = kMaxLdsBytes;
+    const int halo_lo = g_opt.halo ? g_opt.halo : kStripMinHalo, halo_hi = g_opt.halo ? g_opt.halo : kStripMaxHalo;
+    auto cols_of = [&](int Q, int h) {
+        const int c = (Q - 1) * q.sw + 2 * q.dw + 2 * h + 2;
+        return c < q.W + 4 ? c : q.W + 4;
+    };
+    auto rows_of = [&](int R, int h) {
+        const int r = (R - 1) * q.sh + 2 * q.dh + 2 * h + 2;
+        return r < q.H + 4 ? r : q.H + 4;
+    };
+    double best = 1e30;
+    bool padded = false;
+    int splits = 0;
+    for (int kq = 1; kq <= q.Wo && splits < 6; ++kq) {
+        const int Q = (q.Wo + kq - 1) / kq;
+        if (kq > 1 && Q == (q.Wo + kq - 2) / (kq - 1))
+            continue;
+        const int tiles_q = (q.Wo + Q - 1) / Q;
+        int row = 0;
+        bool any = false;
+        for (int hc = halo_lo; hc <= (g_opt.halo ? halo_lo : 8); hc += 2) {
+            const int row_hc = (cols_of(Q, hc) * (int)pb + kStripRow - 1) / kStripRow * kStripRow;
+            const int ring = (lds - row_hc - 2 * (int)pb) / row_hc - 1;
+            if (row_hc == row || ring < 4)
+                continue;
+            row = row_hc;
+            any = true;
+            int hcm = hc;
+            while (hcm < halo_hi && cols_of(Q, hcm + 1) * (int)pb <= row)
+                ++hcm;
+            for (int bands = 1; bands <= q.Ho && bands <= 16; ++bands) {
+                const int R = (q.Ho + bands - 1) / bands;
+                if (bands > 1 && R == (q.Ho + bands - 2) / (bands - 1))
+                    continue;
+                const int nb = (q.Ho + R - 1) / R;
+                const long long tiles = (long long)q.N * q.G * p.slices * nb * tiles_q;
+                if (tiles >= (1LL << 24) || (long long)R * Q >= (1LL << 24))
+                    break;
+                const int S = ((int)tiles + cus - 1) / cus, B = (R * Q + 63) / 64;
+                if ((long long)S * B >= (1LL << 24))
+                    continue;
+                // virtual rows that two consecutive rounds can reach: a run of output rows, and what changes of tile add
+                // (a change of image in a run of several rounds is rare and adds little: left out)
+                const int px = 2 * waves * 64, run = ((px + Q - 2) / Q) * q.sh + 2 * q.dh + 2;
+                const int changes = S == 1 ? 0 : B < 2 * waves ? (2 * waves - 2) / B + (nb > 1 ? 1 : 0) : nb > 1 ? 1 : 0;
+                auto span = [&](int h) {
+                    const int change = nb > 1 ? 2 * q.dh + 2 * h + 2 - q.sh : 2 * q.dh + 5 - 2 * q.ph - q.sh;
+                    const long long most = run + 2 * h + (long long)changes * (change > 0 ? change : 0), all = (long long)S * rows_of(R, h);
+                    return most < all ? most : all;
+                };
+                if (span(halo_lo) > ring)
+                    continue;
+                int hr = halo_lo;
+                while (hr < halo_hi && span(hr + 1) <= ring)
+                    ++hr;
+                const double staged = (double)(row / pb) * rows_of(R, hr) / ((double)R * Q);
+                // taps that leave the window (on one side of a strip that has neighbours on both, on average)
+                auto leave = [&](int h) { return (h < 6 ? 0.04 * (6 - h) : 0.0) + (h < 8 ? 0.015 * (8 - h) : 0.0); };
+                const double far = g_opt.halo ? 0.0 : leave(hr) + (tiles_q > 1 ? leave(hcm) * 32.0 / Q : 0.0);
+                const double cost = ((double)S * B / waves + 0.5) * (1.0 + (pb < 64 ? 0.05 : 0.1) * staged + far) + 1.0;
+                if (cost < best - 1e-9) {
+                    best = cost;
+                    padded = row * 10 > cols_of(Q, halo_lo) * (int)pb * 17;
+                    p.R = R;
+                    p.Q = Q;
+                    p.halo_r = hr;
+                    p.halo_c = hcm;
+                    p.row_lds = row;
+                    p.VR = rows_of(R, hr);
+                    p.B = B;
+                    p.ring = (long long)ring < (long long)S * p.VR ? ring : S * p.VR;
+                    p.tiles_q = tiles_q;
+                    p.tiles_per_img = nb * tiles_q;
+                    p.ntiles = (int)tiles;
+                    out->busiest = (long long)S * B;
+                }
+            }
+        }
+        splits += any;
+    }
+    // Where rectangles stay: few batches in shares that are more than 15 % above the mean (12 images of 56x56, 8 groups of
+    // 32, fp16: 35.8 us by rectangles, 39.8 by strips; in equal shares 10 of 75x101, 4 groups: 43.0 and 33.0), and narrow
+    // pixels in rows that are mostly padding (64 of 14x14, 32 groups of 8, fp16: 18.7 and 21.5; 6 of 112x112, 16 groups: 68
+    // and 51).
+    if (best < 1e30 && g_opt.fwd_strip != 1 && ((batches < 24LL * cus && out->busiest * cus * 20 > batches * 23) || (pb < 64 && padded)))
+        return DCNV4_ERR_UNSUPPORTED;
+    if (best >= 1e30 || (long long)p.ntiles * p.VR >= (1LL << 30))
+        return DCNV4_ERR_UNSUPPORTED;
+    p.H = q.H; p.W = q.W; p.Ho = q.Ho; p.Wo = q.Wo; p.G = q.G;
+    p.sh = q.sh; p.sw = q.sw; p.ph = q.ph; p.pw = q.pw; p.dh = q.dh; p.dw = q.dw;
+    p.scale = q.scale;
+    p.dmax = base.dmax;
+    p.softmax = q.softmax;
+    p.cpr = p.row_lds / kStripRow;
+    p.tiles_per_xcd = (p.ntiles + kXcds - 1) / kXcds;
+    p.remap = g_opt.xcd_remap;
+    p.div_g = make_div((unsigned)q.G);
+    p.div_s = make_div((unsigned)p.slices);
+    p.div_tpi = make_div((unsigned)p.tiles_per_img);
+    p.div_tq = make_div((unsigned)p.tiles_q);
+    p.div_q = make_div((unsigned)p.Q);
+    p.div_vr = make_div((unsigned)p.VR);
+    p.div_b = make_div((unsigned)p.B);
+    p.div_ring = make_div((unsigned)p.ring);
+    p.div_cpr = make_div((unsigned)p.cpr);
+    p.group_bytes = (int)(q.Cg * es);
+    p.x_img_bytes = base.x_img_bytes;
+    p.row_bytes = base.row_bytes;
+    p.pix_bytes = base.pix_bytes;
+    p.x_bytes = (int)xbytes;
+    p.y_bytes = (int)ybytes;
+    p.off_bytes = (int)((q.N * pgi - 1) * p.og_bytes + 18 * es);
+    p.msk_bytes = (int)(((q.N * pgi - 1) * p.mg_bytes + 9 * es + 3) & ~3LL);
+    out->p = p;
+    out->lds = (p.ring + 2) * p.row_lds + (int)(2 * pb);
+    if (p.remap) {
+        const int per = cus / kXcds < p.tiles_per_xcd ? cus / kXcds : p.tiles_per_xcd;
+        out->grid = (unsigned)(per * kXcds);
+    } else {
+        out->grid = (unsigned)(cus < p.ntiles ? cus : p.ntiles);
+    }
+    return DCNV4_OK;
+}
+
+template <typename T, int CG, int WAVES>
+int launch_strip(const void *x, const void *off, const void *msk, void *y, const Problem &q, hipStream_t s)
+{
+    StripLaunch l;
+    const int rc = make_sgeo(q, CG, WAVES, &l);
+    if (rc)
+        return rc;
+    auto kern = dcnv4_strip_fwd_kernel<T, CG, WAVES>;
+    static int granted[kMaxDevices];
+    if (!grant_lds(reinterpret_cast<const void *>(kern), l.lds, granted))
+        return DCNV4_ERR_LAUNCH;
+    hipLaunchKernelGGL(kern, dim3(l.grid), dim3(WAVES * 64), l.lds, s, (const T *)x, (const T *)off, (const T *)msk, (T *)y, l.p);
+    snprintf(g_last_kernel[0], sizeof(g_last_kernel[0]), "dcnv4_strip_fwd_kernel<%s, %d, %d>", sizeof(T) == 2 ? "_Float16" : "float", CG, WAVES);
+    return hipGetLastError() == hipSuccess ? DCNV4_OK : DCNV4_ERR_LAUNCH;
+}
+
+// a lane keeps up to 64 bytes of a pixel (wider groups in slices); twelve waves fit the registers with up to 32
+template <typename T>
+int dispatch_strip(const void *x, const void *off, const void *msk, void *y, const Problem &q, hipStream_t s)
+{
+    constexpr int kWidest = 64 / (int)sizeof(T);
+    if (q.Cg >= kWidest)
+        return launch_strip<T, kWidest, 8>(x, off, msk, y, q, s);
+    if constexpr (sizeof(T) == 2) {
+        if (q.Cg == 16)
+            return launch_strip<T, 16, 12>(x, off, msk, y, q, s);
+    }
+    return launch_strip<T, 8, 12>(x, off, msk, y, q, s);
+}
+
+// fp16, 16 channels per group: the ring kernel (dot products of fp16 pairs) takes whole images, so with few of them
+// compute units stay idle, which strips and bands avoid: 10 images of 75x101, 8 groups: 106 us by the ring, 38 by
+// strips; 6 of 112x112: 201 and 41.  Where both fill the chip a batch costs 0.77 us by the ring and 0.88 by strips
+// (49 images of 28x28, 16 groups: 35.6 and 41.8).
+bool strip_beats_ring(const Problem &q)
+{
+    if (q.Cg != 16 || g_opt.fwd_strip == 2)
+        return false;
+    const int cus = device_cus();
+    if (cus <= 0)
+        return false;
+    const long long tiles = (long long)q.N * q.G, B = ((long long)q.Ho * q.Wo + 63) / 64;
+    const long long ring = (tiles + cus - 1) / cus * B;
+    if (ring * 77 * cus <= tiles * B * 88)                       // (the other's share at the least)
+        return false;
+    StripLaunch l;
+    return make_sgeo(q, 16, 12, &l) == DCNV4_OK && l.busiest * 88 < ring * 77;
+}
+
 template <typename T>
 int dispatch_fwd(const void *x, const void *off, const void *msk, void *y, const Problem &q, hipStream_t s)
 {
@@ -1214,13 +1429,18 @@ int dispatch_fwd(const void *x, const void *off, const void *msk, void *y, const
     }
     // (maps of a few batches per image leave most of a ring workgroup idle: the rectangle kernels,
     // with several small workgroups per compute unit, are faster there -- measured at 14x14 and 7x7)
-    if (sizeof(T) == 2 && (g_opt.fwd_path == 3 || (g_opt.fwd_path == 0 && q.Ho * q.Wo >= 512))) {
+    if (sizeof(T) == 2 && (g_opt.fwd_path == 3 || (g_opt.fwd_path == 0 && g_opt.fwd_strip != 1 && q.Ho * q.Wo >= 512 && !strip_beats_ring(q)))) {
         const int rc = dispatch_ring_fwd(x, off, msk, y, q, s);
         if (rc != DCNV4_ERR_UNSUPPORTED || g_opt.fwd_path == 3)
             return rc;
     }
     if (g_opt.fwd_path == 3)
         return DCNV4_ERR_UNSUPPORTED;
+    if (g_opt.fwd_path == 0 && g_opt.fwd_strip != 2) {
+        const int rc = dispatch_strip<T>(x, off, msk, y, q, s);
+        if (rc != DCNV4_ERR_UNSUPPORTED || g_opt.fwd_strip == 1)
+            return rc;
+    }
     if (g_opt.fwd_path != 1) {
         const int rc = dispatch_fwd_tiled_cg<T>(x, off, msk, y, q, s);
         if (rc != DCNV4_ERR_UNSUPPORTED || g_opt.fwd_path == 2)
@@ -2126,6 +2346,10 @@ int dcnv4_set_option(const char *key, int value)
     }
     if (!strcmp(key, "fwd_path") && value >= 0 && value <= 3) {
         g_opt.fwd_path = value;
+        return DCNV4_OK;
+    }
+    if (!strcmp(key, "fwd_strip") && value >= 0 && value <= 2) {
+        g_opt.fwd_strip = value;
         return DCNV4_OK;
     }
     if (!strcmp(key, "gx_threads") && (value == 0 || value == 256 || value == 512 || value == 768)) {

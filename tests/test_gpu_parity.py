@@ -591,6 +591,53 @@ def test_ring_forward_is_the_default_for_fp16_groups_of_16_on_maps_of_many_batch
     assert dcn.dcnv4_last_kernel_name(0).startswith("dcnv4_tiled_kernel<")
 
 
+STRIP_CASES = [
+    Config("st_rows", N=3, H=23, W=60, C=64, G=4),                    # 64 columns with the border: whole KiB rows in fp32
+    Config("st_rows1", N=2, H=30, W=61, C=64, G=4),                   # one column more
+    Config("st_many", N=40, H=9, W=10, C=256, G=16),                  # several images per workgroup, shorter than a round
+    Config("st_bands", N=1, H=90, W=33, C=32, G=2, sigma=3.0),        # bands of rows, most compute units without a tile
+    Config("st_wide", N=1, H=12, W=300, C=32, G=1, sigma=4.0),        # strips of columns, far taps
+    Config("st_s2", N=3, H=41, W=37, C=128, G=2, stride=2, pad=2, dilation=2, sigma=3.0),
+    Config("st_pad", N=2, H=7, W=8, C=24, G=3, pad=9, dilation=3),    # windows wholly outside the image
+    Config("st_one", N=2, H=1, W=1, C=64, G=1, pad=1),
+]
+
+
+@pytest.mark.parametrize("cfg", STRIP_CASES, ids=[c.name for c in STRIP_CASES])
+@pytest.mark.parametrize("opts", [{}, {"halo": 1}, {"lds_kb": 24}, {"xcd_remap": 0, "lds_kb": 64}],
+                         ids=["default", "halo1", "lds24", "lds64_plain_order"])
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_strip_forward(cfg, opts, dtype):
+    """The forward out of a rolling window of rows: rings from a few rows to whole images, one to several tiles per
+    workgroup, windows clipped on every side."""
+    try:
+        for k, v in {**opts, "fwd_strip": 1}.items():
+            dcn.dcnv4_set_option(k, v)
+        try:
+            check_forward(cfg, dtype, seed=71)
+        except dcn.Dcnv4Error as e:
+            assert e.status == 3 and "lds_kb" in opts                # (a window of the halo does not fit the LDS)
+            return
+        assert dcn.dcnv4_last_kernel_name(0).startswith("dcnv4_strip_fwd_kernel<")
+    finally:
+        dcn.dcnv4_set_option("reset", 0)
+
+
+def test_strip_forward_over_more_rounds_than_its_table_holds():
+    """66 rounds of twelve waves to a workgroup; the rectangle kernel does the same arithmetic on the same values."""
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x, off, mask = (torch.randn(*s, generator=gen, device="cuda", dtype=torch.float32).half()
+                    for s in ((64, 56, 56, 512), (64, 56, 56, 64, 9, 2), (64, 56, 56, 64, 9)))
+    got = {}
+    for path in (1, 2):
+        dcn.dcnv4_set_option("fwd_strip", path)
+        got[path] = dcn.dcnv4_forward(x, off, mask)
+        assert dcn.dcnv4_last_kernel_name(0).startswith({1: "dcnv4_strip", 2: "dcnv4_tiled"}[path])
+    dcn.dcnv4_set_option("reset", 0)
+    # (one rounding to fp16 of sums that agree to fp32 roundings: at most one step of fp16 apart)
+    torch.testing.assert_close(got[1], got[2], rtol=2.0 ** -10, atol=2.0 ** -14)
+
+
 def _random_cases(n, seed):
     rng = np.random.default_rng(seed)
     cases = []
