@@ -1219,10 +1219,20 @@ struct StripLaunch {
 
 // Chooses strips of columns, bands of rows, the window's rows and the displacement it allows for, by the batches that
 // the busiest workgroup works through.
-int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out)
+int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, bool gom = false, int slices_lds = 0)
 {
     const long long es = esize(q.dtype), pb = cg_kernel * es, pgi = (long long)q.Ho * q.Wo * q.G;
     if (q.Cg % cg_kernel != 0)
+        return DCNV4_ERR_UNSUPPORTED;
+    const int cus = device_cus(), slices = q.Cg / cg_kernel;
+    if (cus <= 0)
+        return DCNV4_ERR_LAUNCH;
+    // few batches: nothing to stream (2 images of 160x200, 4 groups of 32, fp16, 15.6 batches to a compute unit: 27.3 us by
+    // rectangles, 28.0 by strips)
+    const long long batches = (long long)q.N * q.G * slices * (((long long)q.Ho * q.Wo + 63) / 64);
+    // (the grad_offset/grad_mask pass is the better one from a quarter of a batch on: 1 image of 28x28, 8 groups, fp32: 21.2 us
+    // by rectangles, 18.6 by strips, with grad_x; 1 of 14x14, 4 groups: 16.3 and 16.5)
+    if (g_opt.fwd_strip != 1 && batches * 4 < (gom ? 1LL : 64LL) * cus)
         return DCNV4_ERR_UNSUPPORTED;
     Geo base;
     int rc = make_geo(q, 1, &base);
@@ -1236,17 +1246,10 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out)
     const long long xbytes = (long long)q.N * base.x_img_bytes, ybytes = (long long)q.N * base.y_img_bytes;
     if (xbytes >= (1LL << 31) || ybytes >= (1LL << 31) || q.N * pgi * p.og_bytes >= (1LL << 31) || q.Ho >= (1 << 15) || q.Wo >= (1 << 15))
         return DCNV4_ERR_UNSUPPORTED;
-    const int cus = device_cus();
-    if (cus <= 0)
-        return DCNV4_ERR_LAUNCH;
-    p.slices = q.Cg / cg_kernel;
-    // few batches: nothing to stream (2 images of 160x200, 4 groups of 32, fp16, 15.6 batches to a compute unit: 27.3 us by
-    // rectangles, 28.0 by strips)
-    const long long batches = (long long)q.N * q.G * p.slices * (((long long)q.Ho * q.Wo + 63) / 64);
-    if (g_opt.fwd_strip != 1 && batches < 16LL * cus)
-        return DCNV4_ERR_UNSUPPORTED;
+    p.slices = slices;
     int lds = (g_opt.lds_kb ? g_opt.lds_kb : kMaxLdsBytes / 1024) * 1024;
     if (lds > kMaxLdsBytes) lds = kMaxLdsBytes;
+    lds -= slices_lds;
     const int halo_lo = g_opt.halo ? g_opt.halo : kStripMinHalo, halo_hi = g_opt.halo ? g_opt.halo : kStripMaxHalo;
     auto cols_of = [&](int Q, int h) {
         const int c = (Q - 1) * q.sw + 2 * q.dw + 2 * h + 2;
@@ -1326,12 +1329,24 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out)
         }
         splits += any;
     }
-    // Where rectangles stay: few batches in shares that are more than 15 % above the mean (12 images of 56x56, 8 groups of
-    // 32, fp16: 35.8 us by rectangles, 39.8 by strips; in equal shares 10 of 75x101, 4 groups: 43.0 and 33.0), and narrow
-    // pixels in rows that are mostly padding (64 of 14x14, 32 groups of 8, fp16: 18.7 and 21.5; 6 of 112x112, 16 groups: 68
-    // and 51).
-    if (best < 1e30 && g_opt.fwd_strip != 1 && ((batches < 24LL * cus && out->busiest * cus * 20 > batches * 23) || (pb < 64 && padded)))
-        return DCNV4_ERR_UNSUPPORTED;
+    // Where rectangles stay in the forward.  Narrow pixels in rows that are mostly padding: 64 of 14x14, 32 groups of 8, fp16:
+    // 18.7 us by rectangles, 21.5 by strips (6 of 112x112, 16 groups: 68 and 51).  Few batches, unless in equal shares (12 of
+    // 56x56, 8 groups of 32, fp16, 36 % above the mean: 35.8 and 39.8) and where the rectangles' own estimate is high (2 of
+    // 71x96, 21 groups of 32, 4.0 a round: 27.7 and 31.4; 10 of 75x101, 4 groups, 6.0: 42.7 and 33.9).
+    if (best < 1e30 && g_opt.fwd_strip != 1 && !gom) {
+        if (pb < 64 && padded)
+            return DCNV4_ERR_UNSUPPORTED;
+        if (batches < 24LL * cus) {
+            if (out->busiest * cus * 20 > batches * 23)
+                return DCNV4_ERR_UNSUPPORTED;
+            TGeo t;
+            double two = 1e30, one = 1e30;
+            choose_tile(q, waves * 64, kDefaultHalo, kDefaultLdsKb * 1024, 2, (int)pb, false, false, p.slices, &t, &two);
+            choose_tile(q, waves * 64, kDefaultHalo, kDefaultLdsKb * 1024, 1, (int)pb, false, false, p.slices, &t, &one);
+            if ((one < two ? one : two) * waves < 4.5 * (double)out->busiest)
+                return DCNV4_ERR_UNSUPPORTED;
+        }
+    }
     if (best >= 1e30 || (long long)p.ntiles * p.VR >= (1LL << 30))
         return DCNV4_ERR_UNSUPPORTED;
     p.H = q.H; p.W = q.W; p.Ho = q.Ho; p.Wo = q.Wo; p.G = q.G;
@@ -1360,7 +1375,7 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out)
     p.off_bytes = (int)((q.N * pgi - 1) * p.og_bytes + 18 * es);
     p.msk_bytes = (int)(((q.N * pgi - 1) * p.mg_bytes + 9 * es + 3) & ~3LL);
     out->p = p;
-    out->lds = (p.ring + 2) * p.row_lds + (int)(2 * pb);
+    out->lds = (p.ring + 2) * p.row_lds + (int)(2 * pb) + slices_lds;
     if (p.remap) {
         const int per = cus / kXcds < p.tiles_per_xcd ? cus / kXcds : p.tiles_per_xcd;
         out->grid = (unsigned)(per * kXcds);
@@ -1370,20 +1385,33 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out)
     return DCNV4_OK;
 }
 
+// in two steps, as prepare_tiled and run_tiled
+template <typename T, int CG, int WAVES, bool GOM>
+int prepare_strip(const Problem &q, StripLaunch *l)
+{
+    const int rc = make_sgeo(q, CG, WAVES, l, GOM, GOM && sizeof(T) == 2 ? WAVES * 64 * 27 * 2 : 0);
+    if (rc)
+        return rc;
+    static int granted[kMaxDevices];
+    return grant_lds(reinterpret_cast<const void *>(dcnv4_strip_kernel<T, CG, WAVES, GOM>), l->lds, granted) ? DCNV4_OK : DCNV4_ERR_LAUNCH;
+}
+
+template <typename T, int CG, int WAVES, bool GOM>
+int run_strip(const StripLaunch &l, const void *x, const void *off, const void *msk, const void *gy, void *o1, void *o2, hipStream_t s)
+{
+    hipLaunchKernelGGL((dcnv4_strip_kernel<T, CG, WAVES, GOM>), dim3(l.grid), dim3(WAVES * 64), l.lds, s, (const T *)x, (const T *)off,
+                       (const T *)msk, (const T *)gy, (T *)o1, (T *)o2, l.p);
+    snprintf(g_last_kernel[GOM], sizeof(g_last_kernel[GOM]), "dcnv4_strip_kernel<%s, %d, %d, %d>",
+             sizeof(T) == 2 ? "_Float16" : "float", CG, WAVES, (int)GOM);
+    return hipGetLastError() == hipSuccess ? DCNV4_OK : DCNV4_ERR_LAUNCH;
+}
+
 template <typename T, int CG, int WAVES>
 int launch_strip(const void *x, const void *off, const void *msk, void *y, const Problem &q, hipStream_t s)
 {
     StripLaunch l;
-    const int rc = make_sgeo(q, CG, WAVES, &l);
-    if (rc)
-        return rc;
-    auto kern = dcnv4_strip_fwd_kernel<T, CG, WAVES>;
-    static int granted[kMaxDevices];
-    if (!grant_lds(reinterpret_cast<const void *>(kern), l.lds, granted))
-        return DCNV4_ERR_LAUNCH;
-    hipLaunchKernelGGL(kern, dim3(l.grid), dim3(WAVES * 64), l.lds, s, (const T *)x, (const T *)off, (const T *)msk, (T *)y, l.p);
-    snprintf(g_last_kernel[0], sizeof(g_last_kernel[0]), "dcnv4_strip_fwd_kernel<%s, %d, %d>", sizeof(T) == 2 ? "_Float16" : "float", CG, WAVES);
-    return hipGetLastError() == hipSuccess ? DCNV4_OK : DCNV4_ERR_LAUNCH;
+    const int rc = prepare_strip<T, CG, WAVES, false>(q, &l);
+    return rc ? rc : run_strip<T, CG, WAVES, false>(l, x, off, msk, nullptr, y, nullptr, s);
 }
 
 // a lane keeps up to 64 bytes of a pixel (wider groups in slices); twelve waves fit the registers with up to 32
@@ -1733,8 +1761,16 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
     // the grad_x pass: twelve waves keep the LDS busiest (measured)
     const int gxt = g_opt.gx_threads ? g_opt.gx_threads : 768;
     TiledLaunch l_gom, l_gx;
-    int rc;
-    if constexpr (sizeof(T) == 4) {
+    int rc = DCNV4_OK;
+    // the grad_offset/grad_mask pass out of a rolling window of rows where that applies (whole groups), else out of
+    // rectangles
+    constexpr int kGomWaves = CG * sizeof(T) >= 32 ? 8 : 12;
+    StripLaunch l_strip;
+    // (small fp32 maps stay with the direct kernel, whose sums of grad_x are fp32)
+    const bool strip = !sliced && !q.softmax && (any_size || q.Ho * q.Wo >= 128 || g_opt.fwd_strip == 1) && g_opt.bwd_path == 0 && g_opt.fwd_strip != 2 && g_opt.gom_coop == 0 &&
+                       prepare_strip<T, CG, kGomWaves, true>(q, &l_strip) == DCNV4_OK;
+    if (strip) {
+    } else if constexpr (sizeof(T) == 4) {
         rc = gom_direct ? prepare_tiled<T, CG, 512, kTiledGradOMDirect>(q, any_size, 0, 0, &l_gom)
                         : prepare_tiled<T, CG, THREADS, kTiledGradOM>(q, any_size, 0, 0, &l_gom);
     } else {
@@ -1762,22 +1798,30 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
     };
     // grad_x: by the grad_offset/grad_mask pass on the way, in whole 16-byte units (its pixels have 16 bytes or more);
     // 32-bit unit numbers
-    const long long gx_units = (long long)q.N * l_gom.p.x_img_bytes / 16;
-    const long long per_tile = (gx_units + l_gom.p.nblocks - 1) / l_gom.p.nblocks;
-    if (gx_units + per_tile < (1LL << 31)) {
-        l_gom.p.zero = (u32x4 *)gx;
-        l_gom.p.zero_units = (unsigned)gx_units;
-        l_gom.p.zero_per_tile = (unsigned)per_tile;
+    const long long gx_bytes = (long long)q.N * q.H * q.W * q.G * q.Cg * (long long)sizeof(T), gx_units = gx_bytes / 16;
+    const long long parts = strip ? (long long)l_strip.p.ntiles * l_strip.p.B : l_gom.p.nblocks, share = (gx_units + parts - 1) / parts;
+    u32x4 *cleared = gx_units + share < (1LL << 31) && (parts + 1) * share < (1LL << 32) ? (u32x4 *)gx : nullptr;
+    if (cleared == nullptr)
+        zero(gx, gx_bytes);
+    if (strip) {
+        l_strip.p.zero = cleared;
+        l_strip.p.zero_units = (unsigned)gx_units;
+        l_strip.p.zero_per_batch = (unsigned)share;
     } else {
-        zero(gx, (long long)q.N * l_gom.p.x_img_bytes);
+        l_gom.p.zero = cleared;
+        l_gom.p.zero_units = (unsigned)gx_units;
+        l_gom.p.zero_per_tile = (unsigned)share;
     }
+    const long long pairs = (long long)q.N * q.Ho * q.Wo * q.G * (long long)sizeof(T);
     if (q.merged) {
-        zero(go, (long long)q.N * l_gom.p.off_img_bytes);       // one buffer: gradients and padding
+        zero(go, 32 * pairs);                                   // one buffer: gradients and padding
     } else if (sliced) {
-        zero(go, (long long)q.N * l_gom.p.off_img_bytes);
-        zero(gm, (long long)q.N * l_gom.p.msk_img_bytes);
+        zero(go, 18 * pairs);
+        zero(gm, 9 * pairs);
     }
-    if constexpr (sizeof(T) == 4) {
+    if (strip) {
+        rc = run_strip<T, CG, kGomWaves, true>(l_strip, x, off, msk, gy, go, gm, s);
+    } else if constexpr (sizeof(T) == 4) {
         rc = gom_direct ? run_tiled<T, CG, 512, kTiledGradOMDirect>(l_gom, x, off, msk, gy, go, gm, s, 1)
                         : run_tiled<T, CG, THREADS, kTiledGradOM>(l_gom, x, off, msk, gy, go, gm, s, 1);
     } else {

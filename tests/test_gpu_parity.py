@@ -618,7 +618,25 @@ def test_strip_forward(cfg, opts, dtype):
         except dcn.Dcnv4Error as e:
             assert e.status == 3 and "lds_kb" in opts                # (a window of the halo does not fit the LDS)
             return
-        assert dcn.dcnv4_last_kernel_name(0).startswith("dcnv4_strip_fwd_kernel<")
+        assert dcn.dcnv4_last_kernel_name(0).startswith("dcnv4_strip_kernel<")
+    finally:
+        dcn.dcnv4_set_option("reset", 0)
+
+
+@pytest.mark.parametrize("cfg", STRIP_CASES, ids=[c.name for c in STRIP_CASES])
+@pytest.mark.parametrize("opts", [{}, {"halo": 1}, {"xcd_remap": 0, "lds_kb": 100}], ids=["default", "halo1", "lds100_plain_order"])
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_strip_backward(cfg, opts, dtype):
+    """grad_offset/grad_mask out of a rolling window of rows, and the clearing of grad_x on the way (fp32 groups of up
+    to 16 channels, fp16 of up to 32)."""
+    if cfg.Cg * (4 if dtype == "f32" else 2) > 64:
+        pytest.skip("the lanes of this pass hold whole groups of up to 64 bytes")
+    try:
+        for k, v in {**opts, "fwd_strip": 1}.items():
+            dcn.dcnv4_set_option(k, v)
+        check_backward(cfg, seed=72, dtype=dtype)
+        if cfg.Cg % 16 == 0 and cfg.name in ("st_rows", "st_rows1", "st_many", "st_wide"):
+            assert dcn.dcnv4_last_kernel_name(1).startswith("dcnv4_strip_kernel<")
     finally:
         dcn.dcnv4_set_option("reset", 0)
 
