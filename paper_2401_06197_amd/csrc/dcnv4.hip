@@ -1227,12 +1227,15 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, bool
     const int cus = device_cus(), slices = q.Cg / cg_kernel;
     if (cus <= 0)
         return DCNV4_ERR_LAUNCH;
-    // few batches: nothing to stream (2 images of 160x200, 4 groups of 32, fp16, 15.6 batches to a compute unit: 27.3 us by
-    // rectangles, 28.0 by strips)
     const long long batches = (long long)q.N * q.G * slices * (((long long)q.Ho * q.Wo + 63) / 64);
-    // (the grad_offset/grad_mask pass is the better one from a quarter of a batch on: 1 image of 28x28, 8 groups, fp32: 21.2 us
-    // by rectangles, 18.6 by strips, with grad_x; 1 of 14x14, 4 groups: 16.3 and 16.5)
-    if (g_opt.fwd_strip != 1 && batches * 4 < (gom ? 1LL : 64LL) * cus)
+    // The forward: where there are batches to stream, three rounds of eight waves, four of twelve (16 of 64x72, 8 groups of 16,
+    // fp16, 36 batches to a compute unit: 30.5 us by rectangles, 34.4 by strips; 2 of 56x56, 48 groups, 55: 49 and 43), or for
+    // a round or less of maps that are not tiny, since bands are cut finer than rectangles (1 of 40x47, 16 groups of 8, fp32:
+    // 12.3 and 8.2; 16 of 14x14, 16 groups of 16: 8.6 and 10.3).  In between rectangles are better.
+    const bool few = !gom && batches <= 2LL * cus && q.Ho * q.Wo >= (pb == 64 ? 400 : 700);
+    // The grad_offset/grad_mask pass from a quarter of a batch on (1 image of 28x28, 8 groups, fp32: 21.2 us by rectangles, 18.6
+    // by strips, with grad_x; 1 of 14x14, 4 groups: 16.3 and 16.5).
+    if (g_opt.fwd_strip != 1 && !few && (gom ? batches * 4 < cus : batches < (pb == 64 ? 16LL : 48LL) * cus))
         return DCNV4_ERR_UNSUPPORTED;
     Geo base;
     int rc = make_geo(q, 1, &base);
@@ -1330,20 +1333,21 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, bool
         splits += any;
     }
     // Where rectangles stay in the forward.  Narrow pixels in rows that are mostly padding: 64 of 14x14, 32 groups of 8, fp16:
-    // 18.7 us by rectangles, 21.5 by strips (6 of 112x112, 16 groups: 68 and 51).  Few batches, unless in equal shares (12 of
-    // 56x56, 8 groups of 32, fp16, 36 % above the mean: 35.8 and 39.8) and where the rectangles' own estimate is high (2 of
-    // 71x96, 21 groups of 32, 4.0 a round: 27.7 and 31.4; 10 of 75x101, 4 groups, 6.0: 42.7 and 33.9).
-    if (best < 1e30 && g_opt.fwd_strip != 1 && !gom) {
+    // 18.7 us by rectangles, 21.5 by strips.  Few batches where the rectangles' own estimate is low: 2 of 71x96, 21 groups of
+    // 32, fp16, 18 batches, 4.0 a round: 27.7 and 31.4 (10 of 75x101, 4 groups, 6.0: 42.7 and 33.9); 4 of 64x72, 12 groups of 64,
+    // 27 batches, 3.56: 46.8 and 48.6 (49 of 28x28, 16 groups of 16, fp32, 40 batches, 3.69: 67.8 and 59.1).  The fewest only
+    // in equal shares: 12 of 56x56, 8 groups of 32, fp16, 36 % above the mean: 35.8 and 39.8.
+    if (best < 1e30 && g_opt.fwd_strip != 1 && !gom && !few) {
         if (pb < 64 && padded)
             return DCNV4_ERR_UNSUPPORTED;
-        if (batches < 24LL * cus) {
-            if (out->busiest * cus * 20 > batches * 23)
+        if (batches < 40LL * cus) {
+            if (batches < 24LL * cus && out->busiest * cus * 20 > batches * 23)
                 return DCNV4_ERR_UNSUPPORTED;
             TGeo t;
             double two = 1e30, one = 1e30;
             choose_tile(q, waves * 64, kDefaultHalo, kDefaultLdsKb * 1024, 2, (int)pb, false, false, p.slices, &t, &two);
             choose_tile(q, waves * 64, kDefaultHalo, kDefaultLdsKb * 1024, 1, (int)pb, false, false, p.slices, &t, &one);
-            if ((one < two ? one : two) * waves < 4.5 * (double)out->busiest)
+            if ((one < two ? one : two) * waves < (batches < 24LL * cus ? 4.5 : 3.6) * (double)out->busiest)
                 return DCNV4_ERR_UNSUPPORTED;
         }
     }
@@ -1428,23 +1432,19 @@ int dispatch_strip(const void *x, const void *off, const void *msk, void *y, con
     return launch_strip<T, 8, 12>(x, off, msk, y, q, s);
 }
 
-// fp16, 16 channels per group: the ring kernel (dot products of fp16 pairs) takes whole images, so with few of them
-// compute units stay idle, which strips and bands avoid: 10 images of 75x101, 8 groups: 106 us by the ring, 38 by
-// strips; 6 of 112x112: 201 and 41.  Where both fill the chip a batch costs 0.77 us by the ring and 0.88 by strips
-// (49 images of 28x28, 16 groups: 35.6 and 41.8).
-bool strip_beats_ring(const Problem &q)
+// fp16, 16 channels per group: where the ring kernel (dot products of fp16 pairs) is the better one.  It takes whole images,
+// so with few (image, group) pairs compute units stay idle, and on wide maps its window is too low: 1 image of 128x128, 16
+// groups: 217 us by the ring, 21 by rectangles; 10 of 75x101, 8 groups: 106, by strips 37.  Where it fills the chip a batch
+// costs it 0.77 us, the others about 1 (16 of 28x28, 16 groups: 15.4 and 17.1; 5 of 40x40, 44 groups: 23.1 and 23.4; 16 of
+// 40x47, 8 groups: 23.9 and 20.9).
+bool ring_first(const Problem &q)
 {
-    if (q.Cg != 16 || g_opt.fwd_strip == 2)
-        return false;
-    const int cus = device_cus();
-    if (cus <= 0)
-        return false;
     const long long tiles = (long long)q.N * q.G, B = ((long long)q.Ho * q.Wo + 63) / 64;
-    const long long ring = (tiles + cus - 1) / cus * B;
-    if (ring * 77 * cus <= tiles * B * 88)                       // (the other's share at the least)
-        return false;
-    StripLaunch l;
-    return make_sgeo(q, 16, 12, &l) == DCNV4_OK && l.busiest * 88 < ring * 77;
+    const int cus = device_cus();
+    if (cus <= 0 || q.Cg != 16 || B <= 12)
+        return true;
+    const double share = (double)((tiles + cus - 1) / cus * B), mean = (double)(tiles * B) / cus;
+    return q.W <= 80 && 0.77 * share <= mean + 4.0;
 }
 
 template <typename T>
@@ -1457,7 +1457,7 @@ int dispatch_fwd(const void *x, const void *off, const void *msk, void *y, const
     }
     // (maps of a few batches per image leave most of a ring workgroup idle: the rectangle kernels,
     // with several small workgroups per compute unit, are faster there -- measured at 14x14 and 7x7)
-    if (sizeof(T) == 2 && (g_opt.fwd_path == 3 || (g_opt.fwd_path == 0 && g_opt.fwd_strip != 1 && q.Ho * q.Wo >= 512 && !strip_beats_ring(q)))) {
+    if (sizeof(T) == 2 && (g_opt.fwd_path == 3 || (g_opt.fwd_path == 0 && g_opt.fwd_strip != 1 && q.Ho * q.Wo >= 512 && (g_opt.fwd_strip == 2 || ring_first(q))))) {
         const int rc = dispatch_ring_fwd(x, off, msk, y, q, s);
         if (rc != DCNV4_ERR_UNSUPPORTED || g_opt.fwd_path == 3)
             return rc;
@@ -1473,6 +1473,12 @@ int dispatch_fwd(const void *x, const void *off, const void *msk, void *y, const
         const int rc = dispatch_fwd_tiled_cg<T>(x, off, msk, y, q, s);
         if (rc != DCNV4_ERR_UNSUPPORTED || g_opt.fwd_path == 2)
             return rc;
+        // (no useful rectangle: the ring after all, where it was passed over)
+        if (sizeof(T) == 2 && g_opt.fwd_path == 0 && q.Ho * q.Wo >= 512) {
+            const int rr = dispatch_ring_fwd(x, off, msk, y, q, s);
+            if (rr != DCNV4_ERR_UNSUPPORTED)
+                return rr;
+        }
     }
     if (q.merged || q.softmax)               // (the direct kernels read two separate tensors and take m as given)
         return DCNV4_ERR_UNSUPPORTED;

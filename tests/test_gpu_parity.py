@@ -591,6 +591,17 @@ def test_ring_forward_is_the_default_for_fp16_groups_of_16_on_maps_of_many_batch
     assert dcn.dcnv4_last_kernel_name(0).startswith("dcnv4_tiled_kernel<")
 
 
+@pytest.mark.parametrize("cfg,kernel", [
+    (Config("rf_full", N=16, H=28, W=28, C=256, G=16), "dcnv4_ring_fwd_kernel<"),       # images enough for the ring
+    (Config("rf_few", N=1, H=40, W=40, C=32, G=2), "dcnv4_strip_kernel<"),              # most compute units without an image
+    (Config("rf_some", N=1, H=48, W=52, C=512, G=32), "dcnv4_tiled_kernel<"),
+    (Config("rf_wide", N=1, H=30, W=97, C=64, G=4), "dcnv4_strip_kernel<"),
+], ids=lambda v: getattr(v, "name", ""))
+def test_fp16_groups_of_16_by_number_of_images(cfg, kernel):
+    check_forward(cfg, "f16", seed=73)
+    assert dcn.dcnv4_last_kernel_name(0).startswith(kernel)
+
+
 STRIP_CASES = [
     Config("st_rows", N=3, H=23, W=60, C=64, G=4),                    # 64 columns with the border: whole KiB rows in fp32
     Config("st_rows1", N=2, H=30, W=61, C=64, G=4),                   # one column more
