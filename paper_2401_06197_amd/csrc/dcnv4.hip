@@ -1390,23 +1390,23 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, bool
 }
 
 // in two steps, as prepare_tiled and run_tiled
-template <typename T, int CG, int WAVES, bool GOM>
+template <typename T, int CG, int WAVES, int GOM>
 int prepare_strip(const Problem &q, StripLaunch *l)
 {
-    const int rc = make_sgeo(q, CG, WAVES, l, GOM, GOM && sizeof(T) == 2 ? WAVES * 64 * 27 * 2 : 0);
+    const int rc = make_sgeo(q, CG, WAVES, l, GOM != 0, GOM == 1 && sizeof(T) == 2 ? WAVES * 64 * 27 * 2 : 0);
     if (rc)
         return rc;
     static int granted[kMaxDevices];
     return grant_lds(reinterpret_cast<const void *>(dcnv4_strip_kernel<T, CG, WAVES, GOM>), l->lds, granted) ? DCNV4_OK : DCNV4_ERR_LAUNCH;
 }
 
-template <typename T, int CG, int WAVES, bool GOM>
+template <typename T, int CG, int WAVES, int GOM>
 int run_strip(const StripLaunch &l, const void *x, const void *off, const void *msk, const void *gy, void *o1, void *o2, hipStream_t s)
 {
     hipLaunchKernelGGL((dcnv4_strip_kernel<T, CG, WAVES, GOM>), dim3(l.grid), dim3(WAVES * 64), l.lds, s, (const T *)x, (const T *)off,
                        (const T *)msk, (const T *)gy, (T *)o1, (T *)o2, l.p);
-    snprintf(g_last_kernel[GOM], sizeof(g_last_kernel[GOM]), "dcnv4_strip_kernel<%s, %d, %d, %d>",
-             sizeof(T) == 2 ? "_Float16" : "float", CG, WAVES, (int)GOM);
+    snprintf(g_last_kernel[GOM != 0], sizeof(g_last_kernel[GOM != 0]), "dcnv4_strip_kernel<%s, %d, %d, %d>",
+             sizeof(T) == 2 ? "_Float16" : "float", CG, WAVES, GOM);
     return hipGetLastError() == hipSuccess ? DCNV4_OK : DCNV4_ERR_LAUNCH;
 }
 
@@ -1414,8 +1414,8 @@ template <typename T, int CG, int WAVES>
 int launch_strip(const void *x, const void *off, const void *msk, void *y, const Problem &q, hipStream_t s)
 {
     StripLaunch l;
-    const int rc = prepare_strip<T, CG, WAVES, false>(q, &l);
-    return rc ? rc : run_strip<T, CG, WAVES, false>(l, x, off, msk, nullptr, y, nullptr, s);
+    const int rc = prepare_strip<T, CG, WAVES, 0>(q, &l);
+    return rc ? rc : run_strip<T, CG, WAVES, 0>(l, x, off, msk, nullptr, y, nullptr, s);
 }
 
 // a lane keeps up to 64 bytes of a pixel (wider groups in slices); twelve waves fit the registers with up to 32
@@ -1774,7 +1774,7 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
     StripLaunch l_strip;
     // (small fp32 maps stay with the direct kernel, whose sums of grad_x are fp32)
     const bool strip = !sliced && !q.softmax && (any_size || q.Ho * q.Wo >= 128 || g_opt.fwd_strip == 1) && g_opt.bwd_path == 0 && g_opt.fwd_strip != 2 && g_opt.gom_coop == 0 &&
-                       prepare_strip<T, CG, kGomWaves, true>(q, &l_strip) == DCNV4_OK;
+                       (q.merged ? prepare_strip<T, CG, kGomWaves, 2>(q, &l_strip) : prepare_strip<T, CG, kGomWaves, 1>(q, &l_strip)) == DCNV4_OK;
     if (strip) {
     } else if constexpr (sizeof(T) == 4) {
         rc = gom_direct ? prepare_tiled<T, CG, 512, kTiledGradOMDirect>(q, any_size, 0, 0, &l_gom)
@@ -1819,14 +1819,15 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
         l_gom.p.zero_per_tile = (unsigned)share;
     }
     const long long pairs = (long long)q.N * q.Ho * q.Wo * q.G * (long long)sizeof(T);
-    if (q.merged) {
+    if (q.merged && !strip) {                                   // (strips write whole records)
         zero(go, 32 * pairs);                                   // one buffer: gradients and padding
     } else if (sliced) {
         zero(go, 18 * pairs);
         zero(gm, 9 * pairs);
     }
     if (strip) {
-        rc = run_strip<T, CG, kGomWaves, true>(l_strip, x, off, msk, gy, go, gm, s);
+        rc = q.merged ? run_strip<T, CG, kGomWaves, 2>(l_strip, x, off, msk, gy, go, gm, s)
+                      : run_strip<T, CG, kGomWaves, 1>(l_strip, x, off, msk, gy, go, gm, s);
     } else if constexpr (sizeof(T) == 4) {
         rc = gom_direct ? run_tiled<T, CG, 512, kTiledGradOMDirect>(l_gom, x, off, msk, gy, go, gm, s, 1)
                         : run_tiled<T, CG, THREADS, kTiledGradOM>(l_gom, x, off, msk, gy, go, gm, s, 1);

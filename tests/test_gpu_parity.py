@@ -652,6 +652,32 @@ def test_strip_backward(cfg, opts, dtype):
         dcn.dcnv4_set_option("reset", 0)
 
 
+@pytest.mark.parametrize("cfg", [c for c in STRIP_CASES if c.name in ("st_rows", "st_many", "st_bands", "st_s2")], ids=lambda c: c.name)
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_strip_backward_merged(cfg, dtype):
+    """Whole records of 32 values are written, the last five zeros, over what was there."""
+    if cfg.Cg * (4 if dtype == "f32" else 2) > 64:
+        pytest.skip("as above")
+    t = make_inputs(cfg, dtype, seed=74)
+    d = to_gpu(t, dtype)
+    Ho, Wo = cfg.out_hw
+    om = torch.full((cfg.N, Ho, Wo, cfg.G, 32), 777.0, dtype=d["x"].dtype, device="cuda")
+    om[..., :18] = d["offset"].reshape(cfg.N, Ho, Wo, cfg.G, 18)
+    om[..., 18:27] = d["mask"]
+    try:
+        dcn.dcnv4_set_option("fwd_strip", 1)
+        gx, gom = dcn.dcnv4_backward_merged(d["x"], om, d["grad_y"], out=(torch.full_like(d["x"], 7.0), torch.full_like(om, 7.0)), **geo_kw(cfg))
+        assert dcn.dcnv4_last_kernel_name(1).startswith("dcnv4_strip_kernel<")
+    finally:
+        dcn.dcnv4_set_option("reset", 0)
+    rgx, rgo, rgm = oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"], **geo_kw(cfg))
+    got = gom.cpu().numpy()
+    close(f"{cfg.name}/{dtype}/grad_mask", got[..., 18:27], rgm, TOL[dtype])
+    close(f"{cfg.name}/{dtype}/grad_offset", got[..., :18].reshape(rgo.shape), rgo, TOL[dtype])
+    close(f"{cfg.name}/{dtype}/grad_x", gx.cpu().numpy(), rgx, TOL[dtype])
+    assert not got[..., 27:].any()
+
+
 def test_strip_forward_over_more_rounds_than_its_table_holds():
     """66 rounds of twelve waves to a workgroup; the rectangle kernel does the same arithmetic on the same values."""
     gen = torch.Generator(device="cuda").manual_seed(5)
