@@ -1224,6 +1224,11 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, bool
     const long long es = esize(q.dtype), pb = cg_kernel * es, pgi = (long long)q.Ho * q.Wo * q.G;
     if (q.Cg % cg_kernel != 0)
         return DCNV4_ERR_UNSUPPORTED;
+    // (what no kernel takes is refused before the device is asked for: the answer does not depend on there being one)
+    Geo base;
+    int rc = make_geo(q, 1, &base);
+    if (rc)
+        return rc;
     const int cus = device_cus(), slices = q.Cg / cg_kernel;
     if (cus <= 0)
         return DCNV4_ERR_LAUNCH;
@@ -1237,10 +1242,6 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, bool
     // by strips, with grad_x; 1 of 14x14, 4 groups: 16.3 and 16.5).
     if (g_opt.fwd_strip != 1 && !few && (gom ? batches * 4 < cus : batches < (pb == 64 ? 16LL : 48LL) * cus))
         return DCNV4_ERR_UNSUPPORTED;
-    Geo base;
-    int rc = make_geo(q, 1, &base);
-    if (rc)
-        return rc;
     SGeo p;
     memset(&p, 0, sizeof(p));
     p.og_bytes = (int)((q.merged ? 32 : 18) * es);
