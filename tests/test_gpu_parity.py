@@ -678,6 +678,33 @@ def test_strip_backward_merged(cfg, dtype):
     assert not got[..., 27:].any()
 
 
+@pytest.mark.parametrize("cfg", [c for c in STRIP_CASES if c.name in ("st_rows", "st_many", "st_bands", "st_wide")], ids=lambda c: c.name)
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_strip_infinite_offsets_give_what_they_give_in_the_oracle(cfg, dtype):
+    """A sample at infinity has no fractional part (NaN) whether its window is clipped on that side or not."""
+    t = make_inputs(cfg, dtype, seed=75)
+    rng = np.random.default_rng(75)
+    for v in (np.inf, -np.inf):
+        t["offset"][rng.random(t["offset"].shape) < 0.004] = v
+    d = to_gpu(t, dtype)
+    try:
+        dcn.dcnv4_set_option("fwd_strip", 1)
+        got = [dcn.dcnv4_forward(d["x"], d["offset"], d["mask"], **geo_kw(cfg))]
+        assert dcn.dcnv4_last_kernel_name(0).startswith("dcnv4_strip_kernel<")
+        if cfg.Cg * d["x"].element_size() <= 64:
+            got += dcn.dcnv4_backward(d["x"], d["offset"], d["mask"], d["grad_y"], **geo_kw(cfg))[1:]
+            assert dcn.dcnv4_last_kernel_name(1).startswith("dcnv4_strip_kernel<")
+    finally:
+        dcn.dcnv4_set_option("reset", 0)
+    refs = [oracle.forward(t["x"], t["offset"], t["mask"], **geo_kw(cfg))]
+    refs += oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"], **geo_kw(cfg))[1:]
+    for name, g, ref in zip(("y", "grad_offset", "grad_mask"), got, refs):
+        g, bad = g.cpu().numpy(), np.isnan(ref)
+        assert bad.any() and not bad.all()
+        assert np.array_equal(np.isnan(g), bad), f"{cfg.name}/{dtype}/{name}: NaN in other places than the oracle's"
+        close(f"{cfg.name}/{dtype}/{name}", g[~bad], ref[~bad], TOL[dtype])
+
+
 def test_strip_forward_over_more_rounds_than_its_table_holds():
     """66 rounds of twelve waves to a workgroup; the rectangle kernel does the same arithmetic on the same values."""
     gen = torch.Generator(device="cuda").manual_seed(5)
