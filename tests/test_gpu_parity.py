@@ -646,18 +646,13 @@ def test_strip_backward(cfg, opts, dtype):
         for k, v in {**opts, "fwd_strip": 1}.items():
             dcn.dcnv4_set_option(k, v)
         check_backward(cfg, seed=72, dtype=dtype)
-        if cfg.Cg % 16 == 0 and cfg.name in ("st_rows", "st_rows1", "st_many", "st_wide"):
+        if cfg.name != "st_pad":                     # (groups of 8: the name kept is the grad_x pass's)
             assert dcn.dcnv4_last_kernel_name(1).startswith("dcnv4_strip_kernel<")
     finally:
         dcn.dcnv4_set_option("reset", 0)
 
 
-@pytest.mark.parametrize("cfg", [c for c in STRIP_CASES if c.name in ("st_rows", "st_many", "st_bands", "st_s2")], ids=lambda c: c.name)
-@pytest.mark.parametrize("dtype", ["f32", "f16"])
-def test_strip_backward_merged(cfg, dtype):
-    """Whole records of 32 values are written, the last five zeros, over what was there."""
-    if cfg.Cg * (4 if dtype == "f32" else 2) > 64:
-        pytest.skip("as above")
+def check_strip_backward_merged(cfg, dtype):
     t = make_inputs(cfg, dtype, seed=74)
     d = to_gpu(t, dtype)
     Ho, Wo = cfg.out_hw
@@ -676,6 +671,45 @@ def test_strip_backward_merged(cfg, dtype):
     close(f"{cfg.name}/{dtype}/grad_offset", got[..., :18].reshape(rgo.shape), rgo, TOL[dtype])
     close(f"{cfg.name}/{dtype}/grad_x", gx.cpu().numpy(), rgx, TOL[dtype])
     assert not got[..., 27:].any()
+
+
+@pytest.mark.parametrize("cfg", [c for c in STRIP_CASES if c.name in ("st_rows", "st_many", "st_bands", "st_s2")], ids=lambda c: c.name)
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_strip_backward_merged(cfg, dtype):
+    """Whole records of 32 values are written, the last five zeros, over what was there."""
+    if cfg.Cg * (4 if dtype == "f32" else 2) > 64:
+        pytest.skip("as above")
+    check_strip_backward_merged(cfg, dtype)
+
+
+class PaddedConfig(Config):
+    """Padding by rows and columns."""
+
+    @property
+    def out_hw(self):
+        return oracle.output_hw(self.H, self.W, self.kernel, self.stride, self.pad, self.dilation)
+
+
+# Padding so far beyond the window that the first rounds' rows all lie above the image.
+ABOVE_CASES = [
+    PaddedConfig("above_8", N=3, H=20, W=59, C=32, G=4, pad=(45, 45), dilation=2),
+    PaddedConfig("above_s2", N=20, H=52, W=31, C=16, G=2, stride=2, pad=(50, 50), dilation=2),
+    PaddedConfig("above_16", N=20, H=17, W=46, C=32, G=2, pad=(45, 1)),
+    PaddedConfig("above_32", N=20, H=36, W=26, C=64, G=2, pad=(42, 3), dilation=2),
+    PaddedConfig("above_64", N=16, H=35, W=47, C=256, G=4, pad=(29, 1), dilation=2),
+]
+
+
+@pytest.mark.parametrize("cfg", ABOVE_CASES, ids=[c.name for c in ABOVE_CASES])
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_strip_windows_far_above_the_image(cfg, dtype):
+    dcn.dcnv4_set_option("fwd_strip", 1)
+    check_forward(cfg, dtype, seed=76)
+    assert dcn.dcnv4_last_kernel_name(0).startswith("dcnv4_strip_kernel<")
+    if cfg.Cg * (4 if dtype == "f32" else 2) <= 64:
+        check_backward(cfg, seed=76, dtype=dtype)
+        assert cfg.Cg % 16 or dcn.dcnv4_last_kernel_name(1).startswith("dcnv4_strip_kernel<")
+        check_strip_backward_merged(cfg, dtype)
 
 
 @pytest.mark.parametrize("cfg", [c for c in STRIP_CASES if c.name in ("st_rows", "st_many", "st_bands", "st_wide")], ids=lambda c: c.name)
