@@ -614,6 +614,11 @@ STRIP_CASES = [
 ]
 
 
+# windows whose rows, for two rounds, do not fit 24 KB of LDS
+TOO_HIGH_FOR_24_KB = ("st_many", "st_wide", "st_s2")
+TOO_WIDE_FOR_24_KB = ("st_rows", "st_rows1", "st_bands")              # (in fp32)
+
+
 @pytest.mark.parametrize("cfg", STRIP_CASES, ids=[c.name for c in STRIP_CASES])
 @pytest.mark.parametrize("opts", [{}, {"halo": 1}, {"lds_kb": 24}, {"xcd_remap": 0, "lds_kb": 64}],
                          ids=["default", "halo1", "lds24", "lds64_plain_order"])
@@ -624,11 +629,12 @@ def test_strip_forward(cfg, opts, dtype):
     try:
         for k, v in {**opts, "fwd_strip": 1}.items():
             dcn.dcnv4_set_option(k, v)
-        try:
-            check_forward(cfg, dtype, seed=71)
-        except dcn.Dcnv4Error as e:
-            assert e.status == 3 and "lds_kb" in opts                # (a window of the halo does not fit the LDS)
+        if opts.get("lds_kb") == 24 and (cfg.name in TOO_HIGH_FOR_24_KB or dtype == "f32" and cfg.name in TOO_WIDE_FOR_24_KB):
+            with pytest.raises(dcn.Dcnv4Error) as refused:
+                check_forward(cfg, dtype, seed=71)
+            assert refused.value.status == 3
             return
+        check_forward(cfg, dtype, seed=71)
         assert dcn.dcnv4_last_kernel_name(0).startswith("dcnv4_strip_kernel<")
     finally:
         dcn.dcnv4_set_option("reset", 0)
@@ -662,7 +668,7 @@ def check_strip_backward_merged(cfg, dtype):
     try:
         dcn.dcnv4_set_option("fwd_strip", 1)
         gx, gom = dcn.dcnv4_backward_merged(d["x"], om, d["grad_y"], out=(torch.full_like(d["x"], 7.0), torch.full_like(om, 7.0)), **geo_kw(cfg))
-        assert dcn.dcnv4_last_kernel_name(1).startswith("dcnv4_strip_kernel<")
+        assert cfg.Cg % 16 or dcn.dcnv4_last_kernel_name(1).startswith("dcnv4_strip_kernel<")
     finally:
         dcn.dcnv4_set_option("reset", 0)
     rgx, rgo, rgm = oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"], **geo_kw(cfg))
@@ -752,6 +758,24 @@ def test_strip_forward_over_more_rounds_than_its_table_holds():
     dcn.dcnv4_set_option("reset", 0)
     # (one rounding to fp16 of sums that agree to fp32 roundings: at most one step of fp16 apart)
     torch.testing.assert_close(got[1], got[2], rtol=2.0 ** -10, atol=2.0 ** -14)
+
+
+def test_strip_backward_over_more_rounds_than_its_table_holds():
+    """As above, in the grad_offset/grad_mask pass, which also clears grad_x."""
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    x, off, mask, gy = (torch.randn(*s, generator=gen, device="cuda", dtype=torch.float32).half()
+                        for s in ((64, 56, 56, 512), (64, 56, 56, 64, 9, 2), (64, 56, 56, 64, 9), (64, 56, 56, 512)))
+    got = {}
+    for path in (1, 2):
+        dcn.dcnv4_set_option("fwd_strip", path)
+        out = tuple(torch.full_like(t, 7.0) for t in (x, off, mask))
+        got[path] = dcn.dcnv4_backward(x, off, mask, gy, out=out)
+    for one, two in zip(got[1][1:], got[2][1:]):
+        torch.testing.assert_close(one, two, rtol=2.0 ** -10, atol=2.0 ** -14)
+    # grad_x: the same kernel over the same tiles; the sums of up to four tiles are added in another order, each time with one
+    # rounding to fp16 of at most twice the largest result
+    gx = [got[path][0].float() for path in (1, 2)]
+    assert float((gx[0] - gx[1]).abs().max()) <= 2 * 4 * 2.0 ** -11 * 2 * float(gx[1].abs().max())
 
 
 def _random_cases(n, seed):
