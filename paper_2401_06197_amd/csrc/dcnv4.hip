@@ -353,6 +353,7 @@ __global__ __launch_bounds__(kThreads) void dcnv4_fwd_kernel(const T *__restrict
     store_run<CPT>(ry, it.pix * p.pix_bytes + chan_bytes, acc, (T *)nullptr);
 }
 
+#include "dcnv4_tile_choice.h"
 #include "dcnv4_tiled.inc"
 #include "dcnv4_gradx.inc"
 #include "dcnv4_ring.inc"
@@ -700,10 +701,6 @@ constexpr int kStripMinHalo = 4, kStripMaxHalo = 12;
 constexpr int kDefaultLdsKb = 158;
 constexpr int kMaxLdsBytes = 160 * 1024;
 
-// Tile choice for the LDS-staged forward: full-width row bands when a band with a useful
-// number of rows fits the LDS budget, otherwise split the columns too.  Returns false when
-// no tile with at least as many output rows/cols as the halo fits (the rectangle would be
-// mostly halo); the caller then uses the direct kernel.
 // Per-device caches (compute-unit count, dynamic-LDS grants) are indexed by the HIP device number.
 constexpr int kMaxDevices = 64;
 int current_device()
@@ -749,75 +746,12 @@ bool grant_lds(const void *kern, int lds, int (&granted)[kMaxDevices])
 bool choose_tile(const Problem &q, int threads, int halo, int lds_bytes, int nbuf, int pb, bool accum, bool with_slices,
                  int chan_slices, TGeo *out, double *cost_out = nullptr)
 {
-    const int es = esize(q.dtype);
     // per-wave LDS slices for the 27 offset/mask values of 64 pixels (grad_offset/grad_mask pass only)
-    const int slices = with_slices ? (threads / 64) * 64 * 27 * es : 0;
-    const int need = halo > 4 ? halo : 4;
-    const int waves = threads / 64;
+    const int slices = with_slices ? (threads / 64) * 64 * 27 * esize(q.dtype) : 0;
     int cus = device_cus();
     if (cus <= 0) cus = 256;                 // no device in this process (host-only checks): assume a full MI355X
-    // Cost of a candidate (column splits kq, band height R), in units of one round (= every wave
-    // of a workgroup doing one batch of 64 output pixels): a tile of B batches takes ceil(B / waves)
-    // rounds plus about four for the switch (barrier, drained pipeline; measured; six with a single
-    // buffer, whose refill is not hidden), and a workgroup
-    // works through ceil(tiles / CUs) tiles -- so few, huge tiles that leave CUs idle lose against
-    // more, smaller ones.
-    double best_cost = 1e30;
-    bool found = false;
-    int splits_tried = 0;
-    for (int kq = 1; kq <= q.Wo && splits_tried < 12; ++kq) {
-        const int Q = (q.Wo + kq - 1) / kq;
-        if (kq > 1 && Q == (q.Wo + kq - 2) / (kq - 1))
-            continue;                        // same tile width as the previous split count
-        long long cols = (long long)(Q - 1) * q.sw + 2LL * q.dw + 2LL * halo + 2;
-        if (cols > q.W + 4) cols = q.W + 4;
-        // the rectangle buffers (each a multiple of 1 KiB) share what the slices leave, after
-        // a block of zeros (pitch + 2 pixels) or one more dword per rectangle pixel (the bound words of the grad_x accumulator)
-        const long long zero_bytes = accum ? 16 : ((cols + kTiledZeroPixelsExtra) * pb + 15) & ~15LL;
-        const long long budget_px =
-            ((((long long)lds_bytes - slices - zero_bytes) * pb / (pb + (accum ? 4 : 0)) / nbuf) & ~1023LL) / pb;
-        if (budget_px < 64)
-            continue;
-        const long long rows_max = budget_px / cols;
-        long long Rmax = (rows_max - 2LL * q.dh - 2LL * halo - 2) / q.sh + 1;
-        if (rows_max >= q.H + 4) Rmax = q.Ho;               // the whole (clipped) height fits
-        if (Rmax > q.Ho) Rmax = q.Ho;
-        if (Rmax < 1 || (Rmax < need && Rmax < q.Ho) || (Q < need && Q < q.Wo))
-            continue;
-        const long long Rlow = Rmax < need ? Rmax : need;
-        if (accum && Rmax * Q > kFixMaxTilePixels) {        // (the bound words must not wrap)
-            Rmax = kFixMaxTilePixels / Q;
-            if (Rmax < Rlow)
-                continue;
-        }
-        ++splits_tried;
-        const int tiles_q = (q.Wo + Q - 1) / Q;
-        for (long long R = Rmax; R >= Rlow; --R) {
-            const long long bands = (q.Ho + R - 1) / R, Rlast = q.Ho - (bands - 1) * R;
-            const long long b_full = (R * Q + 63) / 64, b_last = (Rlast * Q + 63) / 64;
-            const double rounds_img = tiles_q * ((bands - 1) * (double)((b_full + waves - 1) / waves) +
-                                                 (double)((b_last + waves - 1) / waves) + (nbuf == 1 && !accum ? 6.0 : 4.0) * bands);
-            const long long tiles = (long long)q.N * q.G * chan_slices * bands * tiles_q;
-            const double per_tile = rounds_img / (double)(bands * tiles_q);
-            const double cost = (double)((tiles + cus - 1) / cus) * per_tile;
-            if (cost < best_cost - 1e-9) {
-                best_cost = cost;
-                found = true;
-                long long rows = (R - 1) * q.sh + 2LL * q.dh + 2LL * halo + 2;
-                if (rows > q.H + 4) rows = q.H + 4;
-                out->R = (int)R;
-                out->Q = Q;
-                out->halo = halo;
-                out->pitch = (int)cols;
-                out->tiles_q = tiles_q;
-                out->tiles_per_img = (int)(bands * tiles_q);
-                out->xtile_bytes = (int)((rows * cols * pb + 1023) & ~1023LL);
-            }
-        }
-    }
-    if (cost_out)
-        *cost_out = best_cost;
-    return found;
+    return tile_choice(q, threads / 64, halo, lds_bytes - slices, nbuf, pb, accum, kFixMaxTilePixels, kTiledZeroPixelsExtra, chan_slices,
+                       cus, out, cost_out);
 }
 
 // `mode`: kTiledGradX has a single LDS rectangle of Cg + 1 dwords per pixel (fixed-point sums and a bound word);
