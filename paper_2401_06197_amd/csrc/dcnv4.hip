@@ -1702,22 +1702,24 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
     // the grad_x pass: twelve waves keep the LDS busiest (measured)
     const int gxt = g_opt.gx_threads ? g_opt.gx_threads : 768;
     TiledLaunch l_gom, l_gx;
-    int rc = DCNV4_OK;
-    // the grad_offset/grad_mask pass out of a rolling window of rows where that applies (whole groups), else out of
-    // rectangles
-    constexpr int kGomWaves = CG * sizeof(T) >= 32 ? 8 : 12;
-    StripLaunch l_strip;
-    // (small fp32 maps stay with the direct kernel, whose sums of grad_x are fp32)
-    const bool strip = !sliced && !q.softmax && (any_size || q.Ho * q.Wo >= 128 || g_opt.fwd_strip == 1) && g_opt.bwd_path == 0 && g_opt.fwd_strip != 2 && g_opt.gom_coop == 0 &&
-                       (q.merged ? prepare_strip<T, CG, kGomWaves, 2>(q, &l_strip) : prepare_strip<T, CG, kGomWaves, 1>(q, &l_strip)) == DCNV4_OK;
-    if (strip) {
-    } else if constexpr (sizeof(T) == 4) {
+    int rc;
+    if constexpr (sizeof(T) == 4) {
         rc = gom_direct ? prepare_tiled<T, CG, 512, kTiledGradOMDirect>(q, any_size, 0, 0, &l_gom)
                         : prepare_tiled<T, CG, THREADS, kTiledGradOM>(q, any_size, 0, 0, &l_gom);
     } else {
         rc = prepare_tiled<T, CG, THREADS, kTiledGradOM>(q, any_size, 0, 0, &l_gom);
     }
-    if (rc)
+    if (rc != DCNV4_OK && rc != DCNV4_ERR_UNSUPPORTED)
+        return rc;
+    // The grad_offset/grad_mask pass out of a rolling window of rows where that applies (whole groups), else out of
+    // rectangles.  fp32 calls without a useful rectangle stay with the direct kernel all the same: its sums of grad_x are fp32
+    // (4 images of 48x46, 4 groups, stride 2: error 7e-8 of grad_x, 2e-7 through the fixed-point sums).
+    constexpr int kGomWaves = CG * sizeof(T) >= 32 ? 8 : 12;
+    StripLaunch l_strip;
+    const bool strip = !sliced && !q.softmax && (any_size || rc == DCNV4_OK || g_opt.fwd_strip == 1) && g_opt.bwd_path == 0 &&
+                       g_opt.fwd_strip != 2 && g_opt.gom_coop == 0 &&
+                       (q.merged ? prepare_strip<T, CG, kGomWaves, 2>(q, &l_strip) : prepare_strip<T, CG, kGomWaves, 1>(q, &l_strip)) == DCNV4_OK;
+    if (rc != DCNV4_OK && !strip)
         return rc;
     GxLaunch l_gx16;
     rc = prepare_gx<T>(q, &l_gx16);

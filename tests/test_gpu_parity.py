@@ -688,6 +688,19 @@ def test_strip_backward_merged(cfg, dtype):
     check_strip_backward_merged(cfg, dtype)
 
 
+@pytest.mark.parametrize("cfg", [Config("dir_s2", N=4, H=48, W=46, C=64, G=4, stride=2), Config("dir_wide", N=1, H=48, W=74, C=352, G=22, stride=2)],
+                         ids=lambda c: c.name)
+def test_fp32_backward_without_a_useful_rectangle_sums_grad_x_in_fp32(cfg):
+    t = make_inputs(cfg, "f32", seed=77)
+    d = to_gpu(t, "f32")
+    gx = dcn.dcnv4_backward(d["x"], d["offset"], d["mask"], d["grad_y"], **geo_kw(cfg))[0].cpu().numpy()
+    ref = oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"], **geo_kw(cfg))[0]
+    # each value is a sum of some 9 terms (stride 2) with two fp32 roundings each, and as many of the sum: below one step of fp32
+    # in the mean (7e-8; the 22-bit fixed point gives 2e-7)
+    assert np.linalg.norm(gx - ref) <= 2.0 ** -23 * np.linalg.norm(ref)
+    assert dcn.dcnv4_last_kernel_name(1).startswith("dcnv4_bwd_kernel<")
+
+
 class PaddedConfig(Config):
     """Padding by rows and columns."""
 
