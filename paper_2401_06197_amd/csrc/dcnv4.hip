@@ -851,13 +851,9 @@ struct TiledLaunch {
 };
 
 template <typename T, int CG, int THREADS, int MODE>
-int prepare_tiled(const Problem &q, bool any_tile_size, int want_nbuf, int want_per_cu, TiledLaunch *out)
+int finish_tiled(const TGeo &p, bool any_tile_size, int want_per_cu, TiledLaunch *out)
 {
-    TGeo p;
     constexpr bool kGradX = MODE == kTiledGradX;
-    int rc = make_tgeo(q, THREADS, MODE, &p, CG, want_nbuf);
-    if (rc)
-        return rc;
     // a tile of one or two 64-pixel batches leaves most of the workgroup's waves idle and pays the
     // tile switch for almost no work: such images are left to the direct kernel unless forced
     if (!any_tile_size && p.R * p.Q < 128)
@@ -896,6 +892,14 @@ int prepare_tiled(const Problem &q, bool any_tile_size, int want_nbuf, int want_
 }
 
 template <typename T, int CG, int THREADS, int MODE>
+int prepare_tiled(const Problem &q, bool any_tile_size, int want_nbuf, int want_per_cu, TiledLaunch *out)
+{
+    TGeo p;
+    const int rc = make_tgeo(q, THREADS, MODE, &p, CG, want_nbuf);
+    return rc ? rc : finish_tiled<T, CG, THREADS, MODE>(p, any_tile_size, want_per_cu, out);
+}
+
+template <typename T, int CG, int THREADS, int MODE>
 int run_tiled(const TiledLaunch &l, const void *x, const void *off, const void *msk, const void *gy, void *o1, void *o2,
               hipStream_t s, int which)
 {
@@ -907,67 +911,74 @@ int run_tiled(const TiledLaunch &l, const void *x, const void *off, const void *
     return hipGetLastError() == hipSuccess ? DCNV4_OK : DCNV4_ERR_LAUNCH;
 }
 
-template <typename T, int CG, int THREADS, int MODE>
-int launch_tiled(const void *x, const void *off, const void *msk, const void *gy, void *o1, void *o2,
-                 const Problem &q, hipStream_t s, int which, bool any_tile_size, int want_nbuf = 0, int want_per_cu = 0)
-{
+// The forward through rectangles, ready to be launched: the choice between it and the strips looks at its tile.
+struct RectForward {
     TiledLaunch l;
-    const int rc = prepare_tiled<T, CG, THREADS, MODE>(q, any_tile_size, want_nbuf, want_per_cu, &l);
-    if (rc)
-        return rc;
-    return run_tiled<T, CG, THREADS, MODE>(l, x, off, msk, gy, o1, o2, s, which);
+    int (*run)(const TiledLaunch &, const void *, const void *, const void *, const void *, void *, void *, hipStream_t, int);
+    int waves;
+    bool many;               // several workgroups on a compute unit
+};
+
+template <typename T, int CG, int THREADS>
+int finish_fwd_tiled(const TGeo &p, bool any_tile_size, int want_per_cu, RectForward *out)
+{
+    out->run = run_tiled<T, CG, THREADS, kTiledFwd>;
+    out->waves = THREADS / 64;
+    out->many = THREADS == 64 || want_per_cu > 1;
+    return finish_tiled<T, CG, THREADS, kTiledFwd>(p, any_tile_size, want_per_cu, &out->l);
 }
 
 template <typename T, int CG, int THREADS>
-int launch_fwd_tiled(const void *x, const void *off, const void *msk, void *y, const Problem &q, hipStream_t s)
+int prepare_fwd_tiled(const Problem &q, RectForward *out)
 {
-    return launch_tiled<T, CG, THREADS, kTiledFwd>(x, off, msk, nullptr, y, nullptr, q, s, 0, g_opt.fwd_path == 2 || q.merged || q.softmax);
+    TGeo p;
+    const int rc = make_tgeo(q, THREADS, kTiledFwd, &p, CG);
+    return rc ? rc : finish_fwd_tiled<T, CG, THREADS>(p, g_opt.fwd_path == 2 || q.merged || q.softmax, 0, out);
 }
 
 // The tiled kernel keeps Cg fp32 accumulators and 4*Cg input values per lane, so it is built
 // for staged pixels of up to 64 bytes.
 template <typename T, int CG>
-int dispatch_fwd_tiled(const void *x, const void *off, const void *msk, void *y, const Problem &q, hipStream_t s)
+int choose_fwd_tiled(const Problem &q, RectForward *out)
 {
     if constexpr (CG * sizeof(T) <= 64 && CG * sizeof(T) >= 16) {
         if constexpr (CG * sizeof(T) == 64) {
             // 64-byte pixels: eight waves still fit the register file (no LDS slices, no exchange registers)
             if (g_opt.fwd_threads == 256)
-                return launch_fwd_tiled<T, CG, 256>(x, off, msk, y, q, s);
-            return launch_fwd_tiled<T, CG, 512>(x, off, msk, y, q, s);
+                return prepare_fwd_tiled<T, CG, 256>(q, out);
+            return prepare_fwd_tiled<T, CG, 512>(q, out);
         }
         if (g_opt.fwd_threads == 256)
-            return launch_fwd_tiled<T, CG, 256>(x, off, msk, y, q, s);
+            return prepare_fwd_tiled<T, CG, 256>(q, out);
         if constexpr (CG * sizeof(T) < 64) {
             // Small whole-image tiles: several four-wave workgroups per compute unit, whose tile
             // switches overlap with each other's work, beat one big workgroup.
             if (g_opt.fwd_threads == 64)
-                return launch_fwd_tiled<T, CG, 64>(x, off, msk, y, q, s);
+                return prepare_fwd_tiled<T, CG, 64>(q, out);
             if (g_opt.fwd_threads == 128)
-                return launch_fwd_tiled<T, CG, 128>(x, off, msk, y, q, s);
+                return prepare_fwd_tiled<T, CG, 128>(q, out);
             if (g_opt.fwd_threads == 768)
-                return launch_fwd_tiled<T, CG, 768>(x, off, msk, y, q, s);
-            if (g_opt.fwd_threads == 0 && g_opt.fwd_path != 1) {
+                return prepare_fwd_tiled<T, CG, 768>(q, out);
+            const long long px = (long long)q.Ho * q.Wo;
+            if (g_opt.fwd_threads == 0 && g_opt.fwd_path != 1 && px <= 128) {
                 // An image of one or two batches: one-wave workgroups, eight to a compute unit, so that
                 // no wave idles while another works (beats the direct kernel on 7x7 maps).
                 TGeo tiny;
-                if (make_tgeo(q, 64, kTiledFwd, &tiny, CG) == DCNV4_OK && tiny.tiles_per_img == 1 && tiny.R * tiny.Q <= 128)
-                    return launch_tiled<T, CG, 64, kTiledFwd>(x, off, msk, nullptr, y, nullptr, q, s, 0, true);
+                if (make_tgeo(q, 64, kTiledFwd, &tiny, CG) == DCNV4_OK && tiny.tiles_per_img == 1)
+                    return finish_fwd_tiled<T, CG, 64>(tiny, true, 0, out);
             }
-            if (g_opt.fwd_threads == 0) {
-                TGeo probe;
+            if (g_opt.fwd_threads == 0 && px <= 16 * 64) {
+                TGeo whole;
                 // (one rectangle buffer each: with several workgroups on the unit, one computes while
                 // another refills, and the halved LDS lets three of them in)
-                if (make_tgeo(q, 256, kTiledFwd, &probe, CG, 1) == DCNV4_OK && probe.tiles_per_img == 1 &&
-                    probe.R * probe.Q <= 16 * 64)
-                    return launch_tiled<T, CG, 256, kTiledFwd>(x, off, msk, nullptr, y, nullptr, q, s, 0,
-                                                               g_opt.fwd_path == 2 || q.merged || q.softmax, 1, 3);
+                if (make_tgeo(q, 256, kTiledFwd, &whole, CG, 1) == DCNV4_OK && whole.tiles_per_img == 1)
+                    return finish_fwd_tiled<T, CG, 256>(whole, g_opt.fwd_path == 2 || q.merged || q.softmax, 3, out);
             }
             if (g_opt.fwd_threads == 512)
-                return launch_fwd_tiled<T, CG, 512>(x, off, msk, y, q, s);
+                return prepare_fwd_tiled<T, CG, 512>(q, out);
             // pixels of up to 32 bytes leave room for twelve waves in the register file (measured: 2-5 %
             // over eight)
-            return launch_fwd_tiled<T, CG, 768>(x, off, msk, y, q, s);
+            return prepare_fwd_tiled<T, CG, 768>(q, out);
         } else {
             return DCNV4_ERR_UNSUPPORTED;
         }
@@ -976,18 +987,18 @@ int dispatch_fwd_tiled(const void *x, const void *off, const void *msk, void *y,
 }
 
 template <typename T>
-int dispatch_fwd_tiled_cg(const void *x, const void *off, const void *msk, void *y, const Problem &q, hipStream_t s)
+int choose_fwd_tiled_cg(const Problem &q, RectForward *out)
 {
     constexpr int kWidest = 64 / (int)sizeof(T);     // channels of a 64-byte pixel: the widest run a lane keeps
     switch (q.Cg) {
-    case 8: return dispatch_fwd_tiled<T, 8>(x, off, msk, y, q, s);
-    case 16: return dispatch_fwd_tiled<T, 16>(x, off, msk, y, q, s);
+    case 8: return choose_fwd_tiled<T, 8>(q, out);
+    case 16: return choose_fwd_tiled<T, 16>(q, out);
     case 32:
     case 64:
         // wider groups go through in slices of 64 bytes (same offsets and mask, own channels)
         if (q.Cg <= kWidest)
-            return dispatch_fwd_tiled<T, 32>(x, off, msk, y, q, s);
-        return dispatch_fwd_tiled<T, kWidest>(x, off, msk, y, q, s);
+            return choose_fwd_tiled<T, 32>(q, out);
+        return choose_fwd_tiled<T, kWidest>(q, out);
     }
     return DCNV4_ERR_UNSUPPORTED;
 }
@@ -1151,31 +1162,74 @@ struct StripLaunch {
     long long busiest;                       // batches of the busiest workgroup
 };
 
+// The forward's time through rectangles and through strips (us), for calls of more than two batches of 64 pixels to a compute
+// unit: by the busiest unit's rounds (a batch to each wave), whole and in fractions, its staged LDS bytes, its tiles, and the
+// mean rounds of all units.  Fitted to graph replays of 5800 random calls of both kernels (stride 1; maps of 7x7 to 200x360, up
+// to 64 groups, offsets of 1, 2 and 4 pixels): either within 7 to 13 % (one standard deviation), their ratio within 6 to 8 %,
+// most of it by the offsets' size, which the host does not know.
+struct ForwardTimes {
+    float rect_rounds, rect_staged, rect_tiles, rect_mean, rect_once;
+    float strip_whole, strip_rounds, strip_staged, strip_near, strip_mean, strip_once;
+};
+ForwardTimes forward_times(int dtype, int pb)
+{
+    if (pb == 64)
+        return dtype == DCNV4_F32 ? ForwardTimes{3.82f, 1.51f, 1.58f, 3.00f, 5.92f, 2.73f, 3.07f, 1.37f, 0.08f, 1.24f, 8.72f}
+                                  : ForwardTimes{5.27f, 1.17f, 2.13f, 2.77f, 6.47f, 3.38f, 3.50f, 0.93f, 0.08f, 1.17f, 10.72f};
+    if (pb == 32)
+        return dtype == DCNV4_F32 ? ForwardTimes{5.12f, 0.07f, 1.44f, 6.23f, -14.23f, 1.69f, 1.56f, 1.49f, 0.15f, 6.69f, -7.56f}
+                                  : ForwardTimes{4.21f, 1.82f, 1.05f, 3.17f, 2.80f, 2.31f, 3.51f, 0.84f, 0.16f, 2.10f, 6.93f};
+    return ForwardTimes{3.80f, 0.00f, 0.88f, 1.98f, 2.89f, 2.78f, 0.00f, 1.36f, 0.00f, 2.67f, 6.29f};
+}
+bool strips_win(const Problem &q, const TGeo &r, int rect_waves, const SGeo &p, int waves, long long busiest, int pb, long long batches, int cus)
+{
+    const ForwardTimes t = forward_times(q.dtype, pb);
+    const float mean = (float)batches / (float)(cus * waves);
+    const float tiles = (float)((r.nblocks + cus - 1) / cus), rounds = (float)((r.R * r.Q + 63) / 64) / rect_waves;
+    const float rect = tiles * (t.rect_rounds * rounds + t.rect_staged * (float)r.xtile_bytes * (1.f / 65536) + t.rect_tiles) +
+                       t.rect_mean * mean + t.rect_once;
+    const int near_r = p.halo_r < 7 ? 7 - p.halo_r : 0, near_c = p.tiles_q > 1 && p.halo_c < 7 ? 7 - p.halo_c : 0;
+    const float staged = (float)((p.ntiles + cus - 1) / cus) * (float)p.VR * (float)p.row_lds * (1.f / 65536);
+    const float strip = t.strip_whole * (float)((busiest + waves - 1) / waves) +
+                        (t.strip_rounds + t.strip_near * near_r) * (float)busiest / waves + t.strip_staged * staged +
+                        t.strip_mean * mean + t.strip_once;
+    // A margin for windows that allow for small displacements: offsets of 4 pixels cost the strips most there (64-byte pixels in
+    // fp32, allowing for 4: 6 % faster than rectangles at offsets of 1 and 2 pixels, 7 % slower at 4).  Over a thousand other
+    // calls for which this picks strips: 9 % faster on average, 6 % of the calls slower by 5 % or more.
+    return strip * (1.f + 0.02f * (float)(near_r > near_c ? near_r : near_c)) < rect;
+}
+
 // Chooses strips of columns, bands of rows, the window's rows and the displacement it allows for, by the batches that
-// the busiest workgroup works through.
-int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, bool gom = false, int slices_lds = 0)
+// the busiest workgroup works through.  `rect`: what the forward's rectangles would launch, if there are any.
+int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, const RectForward *rect, bool gom = false, int slices_lds = 0)
 {
     const long long es = esize(q.dtype), pb = cg_kernel * es, pgi = (long long)q.Ho * q.Wo * q.G;
     if (q.Cg % cg_kernel != 0)
         return DCNV4_ERR_UNSUPPORTED;
+    const int cus = device_cus(), slices = q.Cg / cg_kernel;
+    const long long batches = (long long)q.N * q.G * slices * (((long long)q.Ho * q.Wo + 63) / 64);
+    // The forward: for two batches to a compute unit or less of maps that are not tiny, since bands are cut finer than rectangles
+    // (1 of 40x47, 16 groups of 8, fp32: 12.3 us by rectangles, 8.2 by strips; 16 of 14x14, 16 groups of 16: 8.6 and 10.3), at
+    // stride 1 (at 2 a window holds four times the pixels: 2 of 64x98, 7 groups of 32, fp16: 12.6 and 16.0); and by both kernels'
+    // estimates where there are batches to stream, two rounds of eight waves or four of twelve.  In between, where several small
+    // workgroups share a unit (10 to 15 % faster in each of 29 calls) and where narrow pixels lie side by side in memory (one
+    // group: 5 % faster over 86 calls), rectangles.
+    const bool few = !gom && batches <= 2LL * cus && (long long)q.Ho * q.Wo >= (pb == 64 ? 400 : 700);
+    // The grad_offset/grad_mask pass from a quarter of a batch on (1 image of 28x28, 8 groups, fp32: 21.2 us by rectangles, 18.6
+    // by strips, with grad_x; 1 of 14x14, 4 groups: 16.3 and 16.5).
+    if (cus > 0 && g_opt.fwd_strip != 1) {
+        if (gom ? batches * 4 < cus : !few && batches < (pb == 64 ? 16LL : 48LL) * cus)
+            return DCNV4_ERR_UNSUPPORTED;
+        if (!gom && ((few && (q.sh > 1 || q.sw > 1) && pb > 16) || (!few && q.G == 1 && pb < 64) || (rect != nullptr && rect->many)))
+            return DCNV4_ERR_UNSUPPORTED;
+    }
     // (what no kernel takes is refused before the device is asked for: the answer does not depend on there being one)
     Geo base;
     int rc = make_geo(q, 1, &base);
     if (rc)
         return rc;
-    const int cus = device_cus(), slices = q.Cg / cg_kernel;
     if (cus <= 0)
         return DCNV4_ERR_LAUNCH;
-    const long long batches = (long long)q.N * q.G * slices * (((long long)q.Ho * q.Wo + 63) / 64);
-    // The forward: where there are batches to stream, three rounds of eight waves, four of twelve (16 of 64x72, 8 groups of 16,
-    // fp16, 36 batches to a compute unit: 30.5 us by rectangles, 34.4 by strips; 2 of 56x56, 48 groups, 55: 49 and 43), or for
-    // a round or less of maps that are not tiny, since bands are cut finer than rectangles (1 of 40x47, 16 groups of 8, fp32:
-    // 12.3 and 8.2; 16 of 14x14, 16 groups of 16: 8.6 and 10.3).  In between rectangles are better.
-    const bool few = !gom && batches <= 2LL * cus && q.Ho * q.Wo >= (pb == 64 ? 400 : 700);
-    // The grad_offset/grad_mask pass from a quarter of a batch on (1 image of 28x28, 8 groups, fp32: 21.2 us by rectangles, 18.6
-    // by strips, with grad_x; 1 of 14x14, 4 groups: 16.3 and 16.5).
-    if (g_opt.fwd_strip != 1 && !few && (gom ? batches * 4 < cus : batches < (pb == 64 ? 16LL : 48LL) * cus))
-        return DCNV4_ERR_UNSUPPORTED;
     SGeo p;
     memset(&p, 0, sizeof(p));
     p.og_bytes = (int)((q.merged ? 32 : 18) * es);
@@ -1198,7 +1252,6 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, bool
         return r < q.H + 4 ? r : q.H + 4;
     };
     double best = 1e30;
-    bool padded = false;
     int splits = 0;
     for (int kq = 1; kq <= q.Wo && splits < 6; ++kq) {
         const int Q = (q.Wo + kq - 1) / kq;
@@ -1249,7 +1302,6 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, bool
                 const double cost = ((double)S * B / waves + 0.5) * (1.0 + (pb < 64 ? 0.05 : 0.1) * staged + far) + 1.0;
                 if (cost < best - 1e-9) {
                     best = cost;
-                    padded = row * 10 > cols_of(Q, halo_lo) * (int)pb * 17;
                     p.R = R;
                     p.Q = Q;
                     p.halo_r = hr;
@@ -1267,26 +1319,10 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, bool
         }
         splits += any;
     }
-    // Where rectangles stay in the forward.  Narrow pixels in rows that are mostly padding: 64 of 14x14, 32 groups of 8, fp16:
-    // 18.7 us by rectangles, 21.5 by strips.  Few batches where the rectangles' own estimate is low: 2 of 71x96, 21 groups of
-    // 32, fp16, 18 batches, 4.0 a round: 27.7 and 31.4 (10 of 75x101, 4 groups, 6.0: 42.7 and 33.9); 4 of 64x72, 12 groups of 64,
-    // 27 batches, 3.56: 46.8 and 48.6 (49 of 28x28, 16 groups of 16, fp32, 40 batches, 3.69: 67.8 and 59.1).  The fewest only
-    // in equal shares: 12 of 56x56, 8 groups of 32, fp16, 36 % above the mean: 35.8 and 39.8.
-    if (best < 1e30 && g_opt.fwd_strip != 1 && !gom && !few) {
-        if (pb < 64 && padded)
-            return DCNV4_ERR_UNSUPPORTED;
-        if (batches < 40LL * cus) {
-            if (batches < 24LL * cus && out->busiest * cus * 20 > batches * 23)
-                return DCNV4_ERR_UNSUPPORTED;
-            TGeo t;
-            double two = 1e30, one = 1e30;
-            choose_tile(q, waves * 64, kDefaultHalo, kDefaultLdsKb * 1024, 2, (int)pb, false, false, p.slices, &t, &two);
-            choose_tile(q, waves * 64, kDefaultHalo, kDefaultLdsKb * 1024, 1, (int)pb, false, false, p.slices, &t, &one);
-            if ((one < two ? one : two) * waves < (batches < 24LL * cus ? 4.5 : 3.6) * (double)out->busiest)
-                return DCNV4_ERR_UNSUPPORTED;
-        }
-    }
     if (best >= 1e30 || (long long)p.ntiles * p.VR >= (1LL << 30))
+        return DCNV4_ERR_UNSUPPORTED;
+    if (g_opt.fwd_strip != 1 && !gom && !few && rect != nullptr &&
+        !strips_win(q, rect->l.p, rect->waves, p, waves, out->busiest, (int)pb, batches, cus))
         return DCNV4_ERR_UNSUPPORTED;
     p.H = q.H; p.W = q.W; p.Ho = q.Ho; p.Wo = q.Wo; p.G = q.G;
     p.sh = q.sh; p.sw = q.sw; p.ph = q.ph; p.pw = q.pw; p.dh = q.dh; p.dw = q.dw;
@@ -1326,9 +1362,9 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, bool
 
 // in two steps, as prepare_tiled and run_tiled
 template <typename T, int CG, int WAVES, int GOM>
-int prepare_strip(const Problem &q, StripLaunch *l)
+int prepare_strip(const Problem &q, StripLaunch *l, const RectForward *rect = nullptr)
 {
-    const int rc = make_sgeo(q, CG, WAVES, l, GOM != 0, GOM == 1 && sizeof(T) == 2 ? WAVES * 64 * 27 * 2 : 0);
+    const int rc = make_sgeo(q, CG, WAVES, l, rect, GOM != 0, GOM == 1 && sizeof(T) == 2 ? WAVES * 64 * 27 * 2 : 0);
     if (rc)
         return rc;
     static int granted[kMaxDevices];
@@ -1346,25 +1382,25 @@ int run_strip(const StripLaunch &l, const void *x, const void *off, const void *
 }
 
 template <typename T, int CG, int WAVES>
-int launch_strip(const void *x, const void *off, const void *msk, void *y, const Problem &q, hipStream_t s)
+int launch_strip(const void *x, const void *off, const void *msk, void *y, const Problem &q, const RectForward *rect, hipStream_t s)
 {
     StripLaunch l;
-    const int rc = prepare_strip<T, CG, WAVES, 0>(q, &l);
+    const int rc = prepare_strip<T, CG, WAVES, 0>(q, &l, rect);
     return rc ? rc : run_strip<T, CG, WAVES, 0>(l, x, off, msk, nullptr, y, nullptr, s);
 }
 
 // a lane keeps up to 64 bytes of a pixel (wider groups in slices); twelve waves fit the registers with up to 32
 template <typename T>
-int dispatch_strip(const void *x, const void *off, const void *msk, void *y, const Problem &q, hipStream_t s)
+int dispatch_strip(const void *x, const void *off, const void *msk, void *y, const Problem &q, const RectForward *rect, hipStream_t s)
 {
     constexpr int kWidest = 64 / (int)sizeof(T);
     if (q.Cg >= kWidest)
-        return launch_strip<T, kWidest, 8>(x, off, msk, y, q, s);
+        return launch_strip<T, kWidest, 8>(x, off, msk, y, q, rect, s);
     if constexpr (sizeof(T) == 2) {
         if (q.Cg == 16)
-            return launch_strip<T, 16, 12>(x, off, msk, y, q, s);
+            return launch_strip<T, 16, 12>(x, off, msk, y, q, rect, s);
     }
-    return launch_strip<T, 8, 12>(x, off, msk, y, q, s);
+    return launch_strip<T, 8, 12>(x, off, msk, y, q, rect, s);
 }
 
 // fp16, 16 channels per group: where the ring kernel (dot products of fp16 pairs) is the better one.  It takes whole images,
@@ -1399,14 +1435,21 @@ int dispatch_fwd(const void *x, const void *off, const void *msk, void *y, const
     }
     if (g_opt.fwd_path == 3)
         return DCNV4_ERR_UNSUPPORTED;
-    if (g_opt.fwd_path == 0 && g_opt.fwd_strip != 2) {
-        const int rc = dispatch_strip<T>(x, off, msk, y, q, s);
-        if (rc != DCNV4_ERR_UNSUPPORTED || g_opt.fwd_strip == 1)
-            return rc;
-    }
     if (g_opt.fwd_path != 1) {
-        const int rc = dispatch_fwd_tiled_cg<T>(x, off, msk, y, q, s);
-        if (rc != DCNV4_ERR_UNSUPPORTED || g_opt.fwd_path == 2)
+        RectForward rect;
+        const int rc = choose_fwd_tiled_cg<T>(q, &rect);
+        if (rc != DCNV4_OK && rc != DCNV4_ERR_UNSUPPORTED)
+            return rc;
+        // (two separate tensors without a useful rectangle go to the direct kernel, strips or not: 1 of 36x48, 1 group of 64,
+        // stride 2, fp16: 5.7 us, by strips 11.2)
+        if (g_opt.fwd_path == 0 && g_opt.fwd_strip != 2 && (rc == DCNV4_OK || q.merged || q.softmax || g_opt.fwd_strip == 1)) {
+            const int rs = dispatch_strip<T>(x, off, msk, y, q, rc == DCNV4_OK ? &rect : nullptr, s);
+            if (rs != DCNV4_ERR_UNSUPPORTED || g_opt.fwd_strip == 1)
+                return rs;
+        }
+        if (rc == DCNV4_OK)
+            return rect.run(rect.l, x, off, msk, nullptr, y, nullptr, s, 0);
+        if (g_opt.fwd_path == 2)
             return rc;
         // (no useful rectangle: the ring after all, where it was passed over)
         if (sizeof(T) == 2 && g_opt.fwd_path == 0 && q.Ho * q.Wo >= 512) {
@@ -1702,24 +1745,29 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
     // the grad_x pass: twelve waves keep the LDS busiest (measured)
     const int gxt = g_opt.gx_threads ? g_opt.gx_threads : 768;
     TiledLaunch l_gom, l_gx;
-    int rc;
-    if constexpr (sizeof(T) == 4) {
-        rc = gom_direct ? prepare_tiled<T, CG, 512, kTiledGradOMDirect>(q, any_size, 0, 0, &l_gom)
-                        : prepare_tiled<T, CG, THREADS, kTiledGradOM>(q, any_size, 0, 0, &l_gom);
-    } else {
-        rc = prepare_tiled<T, CG, THREADS, kTiledGradOM>(q, any_size, 0, 0, &l_gom);
-    }
-    if (rc != DCNV4_OK && rc != DCNV4_ERR_UNSUPPORTED)
-        return rc;
     // The grad_offset/grad_mask pass out of a rolling window of rows where that applies (whole groups), else out of
-    // rectangles.  fp32 calls without a useful rectangle stay with the direct kernel all the same: its sums of grad_x are fp32
+    // rectangles.  fp32 calls on two separate tensors: at stride 1 (58 calls at stride 2: 1.4 % slower on average, 18 of them by
+    // 3 % or more), and those without a useful rectangle stay with the direct kernel all the same: its sums of grad_x are fp32
     // (4 images of 48x46, 4 groups, stride 2: error 7e-8 of grad_x, 2e-7 through the fixed-point sums).
     constexpr int kGomWaves = CG * sizeof(T) >= 32 ? 8 : 12;
     StripLaunch l_strip;
-    const bool strip = !sliced && !q.softmax && (any_size || rc == DCNV4_OK || g_opt.fwd_strip == 1) && g_opt.bwd_path == 0 &&
-                       g_opt.fwd_strip != 2 && g_opt.gom_coop == 0 &&
+    auto rectangles = [&]() {
+        if constexpr (sizeof(T) == 4) {
+            if (gom_direct)
+                return prepare_tiled<T, CG, 512, kTiledGradOMDirect>(q, any_size, 0, 0, &l_gom);
+        }
+        return prepare_tiled<T, CG, THREADS, kTiledGradOM>(q, any_size, 0, 0, &l_gom);
+    };
+    const bool free_choice = any_size || g_opt.fwd_strip == 1;
+    int rc = free_choice ? DCNV4_ERR_UNSUPPORTED : rectangles();
+    if (rc != DCNV4_OK && !free_choice)
+        return rc;
+    const bool strip = !sliced && !q.softmax && (free_choice || (q.sh == 1 && q.sw == 1)) && g_opt.bwd_path == 0 && g_opt.fwd_strip != 2 &&
+                       g_opt.gom_coop == 0 &&
                        (q.merged ? prepare_strip<T, CG, kGomWaves, 2>(q, &l_strip) : prepare_strip<T, CG, kGomWaves, 1>(q, &l_strip)) == DCNV4_OK;
-    if (rc != DCNV4_OK && !strip)
+    if (!strip && free_choice)
+        rc = rectangles();
+    if (!strip && rc != DCNV4_OK)
         return rc;
     GxLaunch l_gx16;
     rc = prepare_gx<T>(q, &l_gx16);

@@ -54,7 +54,7 @@ bool tile_choice(const Problem &q, int waves, int halo, int lds_bytes, int nbuf,
         // Band heights from the highest down, those that cut the image into the same number of bands together: none of them
         // takes fewer rounds than all rows in one piece, so most numbers of bands are dropped by one comparison, and all
         // further ones once an even share of the rounds and switches is no better (the choice is that of trying every height:
-        // 1 image of 200x200, 4 groups of 8: 75 us of host time for the whole forward call that way, 13 like this)
+        // 1 image of 200x200, 4 groups of 8: 75 us of host time for the whole forward call that way, 6.5 like this)
         const int least = (q.Ho * Q + px_round - 1) / px_round;
         const double even = (double)q.N * q.G * chan_slices * tiles_q / cus * (1.0 - 1e-12);
         for (int R = top; R >= low;) {

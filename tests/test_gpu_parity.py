@@ -602,6 +602,19 @@ def test_fp16_groups_of_16_by_number_of_images(cfg, kernel):
     assert dcn.dcnv4_last_kernel_name(0).startswith(kernel)
 
 
+@pytest.mark.parametrize("cfg,dtype,kernel", [
+    (Config("fs_few", N=1, H=40, W=47, C=128, G=16), "f32", "dcnv4_strip_kernel<"),
+    (Config("fs_few_s2", N=11, H=32, W=53, C=128, G=2, stride=2), "f16", "dcnv4_tiled_kernel<"),
+    (Config("fs_tiny_s2", N=2, H=64, W=98, C=224, G=7, stride=2), "f16", "dcnv4_fwd_kernel<"),    # no useful rectangle
+    (Config("fs_uneven", N=2, H=181, W=285, C=64, G=4), "f32", "dcnv4_tiled_kernel<"),            # strips on few of the units
+    (Config("fs_even", N=8, H=42, W=53, C=320, G=10), "f32", "dcnv4_strip_kernel<"),
+    (Config("fs_whole", N=52, H=28, W=28, C=128, G=16), "f16", "dcnv4_tiled_kernel<"),            # several workgroups on a unit
+], ids=lambda v: getattr(v, "name", ""))
+def test_forward_by_the_estimates_of_both_kernels(cfg, dtype, kernel):
+    check_forward(cfg, dtype, seed=78)
+    assert dcn.dcnv4_last_kernel_name(0).startswith(kernel)
+
+
 STRIP_CASES = [
     Config("st_rows", N=3, H=23, W=60, C=64, G=4),                    # 64 columns with the border: whole KiB rows in fp32
     Config("st_rows1", N=2, H=30, W=61, C=64, G=4),                   # one column more
