@@ -1234,6 +1234,11 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, cons
     memset(&p, 0, sizeof(p));
     p.og_bytes = (int)((q.merged ? 32 : 18) * es);
     p.mg_bytes = (int)((q.merged ? 32 : 9) * es);
+    // offsets whose product with the scale is past fp32 (fp16 ones with a scale of 5e33 or more: rectangles)
+    const float scale = q.scale < 0.f ? -q.scale : q.scale;
+    if (es == 2 && scale > 5e33f)
+        return DCNV4_ERR_UNSUPPORTED;
+    p.off_max = es == 4 && scale > 1.f ? 3.4e38f / scale : 0.f;
     // (whole tensors behind one descriptor each)
     const long long xbytes = (long long)q.N * base.x_img_bytes, ybytes = (long long)q.N * base.y_img_bytes;
     if (xbytes >= (1LL << 31) || ybytes >= (1LL << 31) || q.N * pgi * p.og_bytes >= (1LL << 31) || q.Ho >= (1 << 15) || q.Wo >= (1 << 15))

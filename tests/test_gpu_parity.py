@@ -771,6 +771,29 @@ def test_strip_infinite_offsets_give_what_they_give_in_the_oracle(cfg, dtype):
         close(f"{cfg.name}/{dtype}/{name}", g[~bad], ref[~bad], TOL[dtype])
 
 
+@pytest.mark.parametrize("cfg", [c for c in STRIP_CASES if c.name in ("st_rows", "st_many", "st_bands", "st_wide")], ids=lambda c: c.name)
+@pytest.mark.parametrize("scale", [4.0, -2.0])                        # (products of ordinary offsets are exact)
+def test_strip_offsets_whose_scaled_value_is_past_fp32_lie_outside(cfg, scale):
+    """A finite sample far outside the image gives nothing, also where its position is more than fp32 holds."""
+    cfg = cfg.with_(offset_scale=scale)
+    t = make_inputs(cfg, "f32", seed=79)
+    rng = np.random.default_rng(79)
+    for v in (3.0e38, -3.4e38):
+        t["offset"][rng.random(t["offset"].shape) < 0.004] = v
+    dcn.dcnv4_set_option("fwd_strip", 1)
+    check_forward(cfg, "f32", inputs=t)
+    assert dcn.dcnv4_last_kernel_name(0).startswith("dcnv4_strip_kernel<")
+    if cfg.Cg > 16:
+        return                                       # (no strips in the backward)
+    d = to_gpu(t, "f32")
+    got = dcn.dcnv4_backward(d["x"], d["offset"], d["mask"], d["grad_y"], **geo_kw(cfg))[1:]
+    assert dcn.dcnv4_last_kernel_name(1).startswith("dcnv4_strip_kernel<")
+    refs = oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"], **geo_kw(cfg))[1:]
+    # (grad_offset is scale times the gradient of the position, which is held to the tolerance)
+    for name, g, ref, tol in zip(("grad_offset", "grad_mask"), got, refs, (abs(scale) * TOL["f32"], TOL["f32"])):
+        close(f"{cfg.name}/{name}", g.cpu().numpy(), ref, tol)
+
+
 def test_strip_forward_over_more_rounds_than_its_table_holds():
     """66 rounds of twelve waves to a workgroup; the rectangle kernel does the same arithmetic on the same values."""
     gen = torch.Generator(device="cuda").manual_seed(5)
