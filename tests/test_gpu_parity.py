@@ -809,6 +809,28 @@ def test_strip_forward_over_more_rounds_than_its_table_holds():
     torch.testing.assert_close(got[1], got[2], rtol=2.0 ** -10, atol=2.0 ** -14)
 
 
+@pytest.mark.parametrize("small", ["x", "grad_y"])
+def test_fp16_backward_keeps_subnormal_operands(small):
+    """grad_offset and grad_mask of operands below 2^-14, multiples of 2^-24, in the dot products of fp16 pairs."""
+    cfg = Config("sub", N=2, H=30, W=31, C=64, G=4)
+    t = make_inputs(cfg, "f16", seed=80)
+    big = "grad_y" if small == "x" else "x"
+    rng = np.random.default_rng(80)
+    t[small] = (rng.integers(-1000, 1001, t[small].shape) * 2.0 ** -24).astype(t[small].dtype)
+    t[big] = (t[big] * 2.0 ** 12).astype(np.float16).astype(t[big].dtype)
+    d = to_gpu(t, "f16")
+    for path in (1, 2):
+        dcn.dcnv4_set_option("fwd_strip", path)
+        got = dcn.dcnv4_backward(d["x"], d["offset"], d["mask"], d["grad_y"])[1:]
+        assert dcn.dcnv4_last_kernel_name(1).startswith({1: "dcnv4_strip_kernel<", 2: "dcnv4_tiled_kernel<"}[path])
+        refs = oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"])[1:]
+        for name, g, ref in zip(("grad_offset", "grad_mask"), got, refs):
+            # (sums of 64 products of up to 2^-14 and 2^14 at most: one rounding to fp16, and fp32 ones of 2^-24 of each)
+            assert np.abs(ref).max() > 0.25
+            err = np.abs(g.cpu().numpy().astype(np.float64) - ref)
+            assert (err <= 2.0 ** -11 * np.abs(ref) + 2.0 ** -16).all(), (name, path, float(err.max()))
+
+
 def test_strip_backward_over_more_rounds_than_its_table_holds():
     """As above, in the grad_offset/grad_mask pass, which also clears grad_x."""
     gen = torch.Generator(device="cuda").manual_seed(6)
