@@ -113,8 +113,8 @@ int dcnv4_backward(const void *x, const void *offset, const void *mask, const vo
                    float offset_scale, int dtype, void *stream);
 
 /* dcnv4_backward for the merged buffer: grad_offset_mask has the layout of
- * offset_mask (gradients of the 18 offsets, of the 9 mask values, 5 zeros); it is zero-filled on
- * `stream` first, like grad_x.  Same restrictions as dcnv4_forward_merged. */
+ * offset_mask (gradients of the 18 offsets, of the 9 mask values, 5 zeros), all of it written whatever
+ * was there.  Same restrictions as dcnv4_forward_merged. */
 int dcnv4_backward_merged(const void *x, const void *offset_mask, const void *grad_y,
                           void *grad_x, void *grad_offset_mask,
                           int N, int H, int W, int G, int Cg,
@@ -238,14 +238,18 @@ long long dcnv4_backward_merged_algorithmic_bytes(int N, int H, int W, int G, in
  * never calls this; the library's own choice is the value 0 of every switch.
  *   "reset"       (any value) puts every switch back to 0
  *   "fwd_path"    1 = direct global gather, 2 = input rectangle staged in LDS, 3 = ring of input rows
- *                 in LDS (fp16, Cg 16); 0 = ring on maps of 512 pixels or more, else rectangle where a
- *                 useful tile fits, else direct
- *   "fwd_strip"   forward out of a rolling window of input rows, in strips of columns (every type and group
- *                 width; taken with fwd_path 0 where there are batches enough to stream): 1 = wherever it
- *                 applies, 2 = never
+ *                 in LDS (fp16, Cg 16); 0 = the first of these that takes the call: ring (fp16, Cg 16, maps of
+ *                 512 pixels or more up to 80 wide, where the (image, group) pairs fill the chip), strips
+ *                 (below), rectangle where a useful tile fits, ring on any map that it fits, direct
+ *   "fwd_strip"   out of a rolling window of input rows, in strips of columns: the forward (with fwd_path 0) of
+ *                 every type and group width, and the backward's grad_offset/grad_mask pass (with bwd_path 0) of
+ *                 whole groups of up to 64 bytes.  0 = where the library's own estimate is that they are the
+ *                 faster, 1 = wherever they apply (in the backward also where the direct kernel would be taken,
+ *                 so that grad_x goes through its fixed-point sums), 2 = never.  Where strips take a call,
+ *                 "fwd_threads", "fwd_single" and "wg_per_cu" have no effect on it
  *   "bwd_path"    1 = one kernel with global atomics for grad_x (fp32), 2 = two LDS-staged kernels
- *                 (gathers for grad_offset/grad_mask; fixed-point accumulation of grad_x in LDS),
- *                 0 = staged where a useful tile fits, else the first
+ *                 (gathers out of rectangles for grad_offset/grad_mask; fixed-point accumulation of grad_x in
+ *                 LDS), 0 = staged, by strips or rectangles, where a useful rectangle fits, else the first
  *   "fwd_single"  LDS rectangle buffers of the staged gather kernels: 1 = always two (the next tile
  *                 streams in during the current one), 2 = always one (bigger rectangle, refilled
  *                 between tiles), 0 = whichever the tile chooser estimates to be cheaper

@@ -522,7 +522,7 @@ struct Options {
     int fwd_single = 0;    // rectangle buffers of the staged gather kernels: 1 always two, 2 always one
     int gx_threads = 0;    // workgroup size of the grad_x kernel (256, 512, 768)
     int gom_coop = 0;      // 1: the fp32 grad_offset/grad_mask pass goes through LDS slices even for whole groups
-    int fwd_strip = 0;     // forward out of a rolling window of rows: 1 wherever it applies, 2 never
+    int fwd_strip = 0;     // forward and grad_offset/grad_mask out of a rolling window of rows: 1 wherever it applies, 2 never
     int module_rows = 0;   // 1: the module keeps its tensors channel-last between the layers (default: plane-major)
 } g_opt;
 
@@ -1412,7 +1412,9 @@ int dispatch_strip(const void *x, const void *off, const void *msk, void *y, con
 // so with few (image, group) pairs compute units stay idle, and on wide maps its window is too low: 1 image of 128x128, 16
 // groups: 217 us by the ring, 21 by rectangles; 10 of 75x101, 8 groups: 106, by strips 37.  Where it fills the chip a batch
 // costs it 0.77 us, the others about 1 (16 of 28x28, 16 groups: 15.4 and 17.1; 5 of 40x40, 44 groups: 23.1 and 23.4; 16 of
-// 40x47, 8 groups: 23.9 and 20.9).
+// 40x47, 8 groups: 23.9 and 20.9).  Past 80 wide it was the faster in none of 36 calls that fill the chip (32 of 56x84, 8 groups:
+// 60 us and 58; of 56x104: 111 and 67).  Of 300 random calls that this keeps from the ring, 10 would be 5 % or more faster by it,
+// and it is 1.7 times slower on average.
 bool ring_first(const Problem &q)
 {
     const long long tiles = (long long)q.N * q.G, B = ((long long)q.Ho * q.Wo + 63) / 64;
