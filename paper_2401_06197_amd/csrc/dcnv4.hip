@@ -8,6 +8,7 @@
 // rows outside the image, offset/mask tiles staged through LDS with 128-bit coalesced
 // loads, tiles handed to XCDs in contiguous bands so that neighbouring outputs share an L2.
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 #include <stdio.h>
 #include <string.h>
@@ -359,6 +360,7 @@ __global__ __launch_bounds__(kThreads) void dcnv4_fwd_kernel(const T *__restrict
 #include "dcnv4_ring.inc"
 #include "dcnv4_strip.inc"
 #include "dcnv4_linear.inc"
+#include "dcnv4_linear_tile.inc"
 
 // ------------------------------------------------------------------------------------------
 // Backward (chain rule on Eq. 1), fp32, in one pass with grad_x added straight to memory; used
@@ -523,6 +525,7 @@ struct Options {
     int gx_threads = 0;    // workgroup size of the grad_x kernel (256, 512, 768)
     int gom_coop = 0;      // 1: the fp32 grad_offset/grad_mask pass goes through LDS slices even for whole groups
     int fwd_strip = 0;     // forward and grad_offset/grad_mask out of a rolling window of rows: 1 wherever it applies, 2 never
+    int linear_tile = 0;   // tile of the linear layers: 1 128x128, 2 64x64, 3 256x256, 4 128x256 (fp32), 5 K in one chunk (fp16, up to 256 bytes)
     int module_rows = 0;   // 1: the module keeps its tensors channel-last between the layers (default: plane-major)
 } g_opt;
 
@@ -1852,6 +1855,92 @@ int fill_problem(Problem *q, int N, int H, int W, int G, int Cg, int kh, int kw,
 
 }  // namespace
 
+namespace {
+
+template <typename T, int WR, int WC, int WM, int WN, int STAGES> int launch_linear_tile(const void *x, const LinGeo &g, hipStream_t s)
+{
+    GemmGeo q;
+    constexpr int RUN = 32 * WM, BN = WC * 32 * WN, STEP = sizeof(T) == 2 ? 128 : 64;
+    q.lin = g;
+    q.steps = (g.kbytes + STEP - 1) / STEP;
+    q.runs0 = (g.seg[0].nout + RUN - 1) / RUN;
+    q.runs = q.runs0 + (g.nseg > 1 ? (g.seg[1].nout + RUN - 1) / RUN : 0);
+    q.out_tiles = (q.runs + WR - 1) / WR;
+    q.tiles = q.out_tiles * ((g.P + BN - 1) / BN);
+    q.tiles_per_xcd = (q.tiles + kXcds - 1) / kXcds;
+    q.div_out = make_div((unsigned)q.out_tiles);
+    hipLaunchKernelGGL((dcnv4_linear_tile_kernel<T, WR, WC, WM, WN, STAGES>), dim3((unsigned)(q.tiles_per_xcd * kXcds)), dim3(WR * WC * 64), 0, s,
+                       (const T *)x, q);
+    return hipGetLastError() == hipSuccess ? DCNV4_OK : DCNV4_ERR_LAUNCH;
+}
+
+// Tiles of the linear layers: channels x pixels, waves.
+enum { kLinear128x128 = 1, kLinear64x64 = 2, kLinear256x256 = 3, kLinear128x256 = 4, kLinearInOneChunk = 5 };
+
+template <typename T> int launch_linear_shape(int shape, const void *x, const LinGeo &g, hipStream_t s)
+{
+    constexpr bool f16 = sizeof(T) == 2;
+    if (shape == kLinear64x64)
+        return launch_linear_tile<T, 2, 2, 1, 1, 4>(x, g, s);
+    if (shape == kLinear256x256)
+        return launch_linear_tile<T, 4, 2, 2, 4, 2>(x, g, s);
+    if constexpr (!f16)
+        if (shape == kLinear128x256)
+            return launch_linear_tile<T, 2, 4, 2, 2, 2>(x, g, s);
+    return launch_linear_tile<T, 2, 2, 2, 2, 2>(x, g, s);
+}
+
+// The tile with the lowest estimated time.  A tile takes `step` us for 128 (fp16) or 64 (fp32) bytes of K and `fixed` for
+// its first loads and its results; a compute unit works through its share one after the other or, of the 128x128 and 64x64
+// tiles, several side by side, where half the difference between the fullest unit and the mean is felt; a lone tile's step
+// takes `alone` at least.  Constants from ten to twenty layers each (49 to 200704 pixels, K 64 to 1024, 64 to 2048 channels),
+// over which the estimates are within 15 % and the choice costs 4 % at most.  us, fp32: 12544 pixels, 512 -> 1024: 92 (128x128), 101, 75 (256x256), 86
+// (128x256); 512 -> 512: 48, 56, 64, 44.5; 4000 pixels, 512 -> 512: 30, 21.8 (64x64), 59, 39.  fp16, 12544 pixels, 512 -> 1024: 24,
+// 34, 21.8; 512 -> 512: 13.5, 19.2, 18.5; 1000 pixels, 1024 -> 1024: 13.9, 7.9, 27.
+int pick_linear_tile(const LinGeo &g, int dtype)
+{
+    struct Tile {
+        int shape, run, waves_out, pixels;
+        bool side_by_side;
+        float step, fixed, alone;
+    };
+    static const Tile f16_tiles[] = {{kLinear128x128, 64, 2, 128, true, .55f, 1.9f, .55f},
+                                     {kLinear64x64, 32, 2, 64, true, .17f, 1.2f, .25f},
+                                     {kLinear256x256, 64, 4, 256, false, 1.15f, 8.6f, 1.15f}};
+    static const Tile f32_tiles[] = {{kLinear128x128, 64, 2, 128, true, .72f, 3.f, .72f},
+                                     {kLinear64x64, 32, 2, 64, true, .23f, .88f, .36f},
+                                     {kLinear256x256, 64, 4, 256, false, 1.76f, 15.6f, 1.76f},
+                                     {kLinear128x256, 64, 2, 256, false, 1.2f, 5.f, 1.2f}};
+    const bool f16 = dtype == DCNV4_F16;
+    const Tile *tiles = f16 ? f16_tiles : f32_tiles;
+    const int count = f16 ? 3 : 4, cus = device_cus();
+    const float steps = (float)((g.kbytes + (f16 ? 127 : 63)) / (f16 ? 128 : 64));
+    int best = 0;
+    float best_us = 0.f, small = 0.f;
+    for (int i = 0; i < count; ++i) {
+        const Tile &t = tiles[i];
+        int runs = 0;
+        for (int k = 0; k < g.nseg; ++k)
+            runs += (g.seg[k].nout + t.run - 1) / t.run;
+        const float n = (float)((runs + t.waves_out - 1) / t.waves_out) * (float)((g.P + t.pixels - 1) / t.pixels) / (float)cus;
+        const float full = ceilf(n), share = t.side_by_side && n > 1.f ? .5f * (n + full) : full;
+        const float us = steps * (t.step * share > t.alone ? t.step * share : t.alone) + t.fixed * share;
+        if (t.shape == kLinear64x64)
+            small = n;
+        if (best == 0 || us < best_us) {
+            best = t.shape;
+            best_us = us;
+        }
+    }
+    // K in one chunk, fp16: 64x64 tiles up to two a compute unit (3136 pixels, 128 -> 256: 3.8 us, 5.1 in one chunk; 12544 pixels:
+    // 7.6 and 6.8)
+    if (f16 && g.kbytes <= kLinChunk)
+        return small <= 2.f ? kLinear64x64 : kLinearInOneChunk;
+    return best;
+}
+
+}  // namespace
+
 extern "C" {
 
 int dcnv4_output_hw(int H, int W, int kernel_h, int kernel_w, int stride_h, int stride_w, int pad_h, int pad_w,
@@ -2015,12 +2104,14 @@ int begin_linear(LinGeo *g, const void *x, long long P, int K, int dtype)
         return DCNV4_ERR_ALIGN;
     g->P = (int)P;
     g->kbytes = (int)kbytes;
-    g->nchunks = (int)((kbytes + kLinChunk - 1) / kLinChunk);
     return DCNV4_OK;
 }
 
 int launch_linear(const void *x, const LinGeo &g, int dtype, hipStream_t s)
 {
+    const int shape = g_opt.linear_tile != 0 ? g_opt.linear_tile : pick_linear_tile(g, dtype);
+    if (shape != kLinearInOneChunk || dtype != DCNV4_F16 || g.kbytes > kLinChunk)
+        return dtype == DCNV4_F16 ? launch_linear_shape<_Float16>(shape, x, g, s) : launch_linear_shape<float>(shape, x, g, s);
     const int tiles = (g.P + kLinPixels - 1) / kLinPixels;
     // maps of few pixels and many channels: the passes over blocks of output channels are spread over
     // workgroups as well, until there are about two workgroups per compute unit
@@ -2031,22 +2122,7 @@ int launch_linear(const void *x, const LinGeo &g, int dtype, hipStream_t s)
     int split = (want + tiles - 1) / tiles;
     if (split > npass) split = npass;
     if (split < 1) split = 1;
-    const bool single = g.nchunks == 1;
-    // (K in several chunks: x is read again for every pass anyway, so every pass is a workgroup of its own -- 50176
-    // pixels, K 256 -> 512: fp32 107 -> 97 us, fp16 33.3 -> 30.4; 12544 pixels, K 512 -> 1024: fp32 120 -> 115)
-    if (!single) split = npass;
-    const dim3 grid((unsigned)tiles, (unsigned)split);
-    if (dtype == DCNV4_F16) {
-        if (single)
-            hipLaunchKernelGGL((dcnv4_linear_kernel<_Float16, true>), grid, dim3(256), 0, s, (const _Float16 *)x, g);
-        else
-            hipLaunchKernelGGL((dcnv4_linear_kernel<_Float16, false>), grid, dim3(256), 0, s, (const _Float16 *)x, g);
-    } else {
-        if (single)
-            hipLaunchKernelGGL((dcnv4_linear_kernel<float, true>), grid, dim3(256), 0, s, (const float *)x, g);
-        else
-            hipLaunchKernelGGL((dcnv4_linear_kernel<float, false>), grid, dim3(256), 0, s, (const float *)x, g);
-    }
+    hipLaunchKernelGGL(dcnv4_linear_kernel, dim3((unsigned)tiles, (unsigned)split), dim3(256), 0, s, (const _Float16 *)x, g);
     return hipGetLastError() == hipSuccess ? DCNV4_OK : DCNV4_ERR_LAUNCH;
 }
 
@@ -2401,6 +2477,10 @@ int dcnv4_set_option(const char *key, int value)
     }
     if (!strcmp(key, "fwd_single") && value >= 0 && value <= 2) {
         g_opt.fwd_single = value;
+        return DCNV4_OK;
+    }
+    if (!strcmp(key, "linear_tile") && value >= 0 && value <= 5) {
+        g_opt.linear_tile = value;
         return DCNV4_OK;
     }
     if (!strcmp(key, "module_rows") && (value == 0 || value == 1)) {

@@ -32,3 +32,10 @@ constexpr LinAt lin_x_at(int xo, int col, int kbytes, int plane_shift, int plane
         return {outside, 0};
     return {xo, plane_shift == 0 ? col : (col >> plane_shift) * plane_stride + (col & ((1 << plane_shift) - 1))};
 }
+
+// Byte column `col` of a pixel row, counted from the row's first byte: rows (shift 0), or planes of 2^shift bytes that lie
+// plane_stride apart.
+constexpr int lin_plane_at(int col, int plane_shift, int plane_stride)
+{
+    return plane_shift == 0 ? col : (col >> plane_shift) * plane_stride + (col & ((1 << plane_shift) - 1));
+}

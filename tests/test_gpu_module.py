@@ -254,3 +254,15 @@ def test_linear_fp32_small_numbers_keep_their_bits(K, ex, ew):
     ref = x.double() @ w.double().T
     lim = 2.0 ** -24 * K ** 0.5 * x.double().norm(dim=1)[:, None] * w.double().norm(dim=1)[None, :] + K * 2.0 ** -149
     assert ((y - ref).abs() <= lim).all(), ((y - ref).abs() / lim).max()
+
+
+@pytest.mark.parametrize("tile", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_linear_tiles(tile, dtype):
+    """Every tile at its edges: one pixel, a pixel less and more than a tile, runs of channels cut short, K of one unit,
+    of less than a step, of steps and a part; and the module, whose first launch has two layers and plane-major results."""
+    for P, K, Nout in [(1, 16, 32), (63, 48, 96), (65, 64, 160), (255, 144, 64), (257, 208, 288), (130, 528, 128), (513, 96, 544)]:
+        dcn.dcnv4_set_option("linear_tile", tile)
+        test_linear_layer_matches_oracle(P, K, Nout, dtype)
+    for cfg in (MODULE_CASES[3], MODULE_CASES[6], Config("m_two", N=2, H=9, W=11, C=192, G=6)):
+        run_module(cfg, dtype, lightweight=False)
