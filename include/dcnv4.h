@@ -260,6 +260,8 @@ long long dcnv4_backward_merged_algorithmic_bytes(int N, int H, int W, int G, in
  *   "gom_coop"    1 = the fp32 grad_offset/grad_mask pass moves its values through per-wave LDS slices
  *                 even for whole groups (default: each lane reads and writes its own pixel's values)
  *   "gx_threads"  workgroup size of the staged grad_x kernel (256, 512 or 768)
+ *   "gx_own"      grad_x kernel: 1 = all tiles of an (image, channel run) go to one workgroup, which stores
+ *                 its sums, 2 = tiles one by one, whose sums are added atomically (default: the faster by estimate)
  *   "halo"        displacement in pixels (rows, for the ring) that the staged window allows for;
  *                 samples beyond it are still exact, they take the path through global memory
  *   "lds_kb"      LDS budget per workgroup of the staged kernels (8..160)

@@ -32,6 +32,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
@@ -523,6 +524,7 @@ struct Options {
     int wg_per_cu = 0;     // persistent workgroups per compute unit of the rectangle kernels (1..32)
     int fwd_single = 0;    // rectangle buffers of the staged gather kernels: 1 always two, 2 always one
     int gx_threads = 0;    // workgroup size of the grad_x kernel (256, 512, 768)
+    int gx_own = 0;        // grad_x kernel, an (image, channel run) to one workgroup: 1 always, 2 never
     int gom_coop = 0;      // 1: the fp32 grad_offset/grad_mask pass goes through LDS slices even for whole groups
     int fwd_strip = 0;     // forward and grad_offset/grad_mask out of a rolling window of rows: 1 wherever it applies, 2 never
     int linear_tile = 0;   // tile of the linear layers: 1 128x128, 2 64x64, 3 256x256, 4 128x256 (fp32), 5 K in one chunk (fp16, up to 256 bytes)
@@ -1532,12 +1534,29 @@ struct GxLaunch {
     int waves;
 };
 
+// Clocks of the kernel in tiles of R x Q outputs with so many cells, `tiles_img` an image: handed out one by one, their sums
+// added atomically, or (owned) all tiles of an (image, channel run) to one workgroup, which stores them.  The wave with the
+// most units of 16 pixels takes a time per batch of up to four for the evaluation and per unit for the adds; it waits for most
+// of that, so other waves of its SIMD add less than as much again.  Then the flush, which the workgroups of a compute unit
+// share.  (Fitted to 230 kernels of 20 calls, 7 to 1200 us: 13 % rms; the tile it takes for each call is within 7 % of its
+// best measured one.)
+double gx_time(const Problem &q, int waves, int per_cu, int slices, int cus, int R, int Q, long long tiles_img, long long cells, bool owned)
+{
+    auto ceil_div = [](long long a, long long b) { return (a + b - 1) / b; };
+    const int units = (int)ceil_div(R * ceil_div(Q, 4), 4), most = (units + waves - 1) / waves;
+    const long long slots = (long long)cus * per_cu, planes = (long long)q.N * q.G * slices, blocks = owned ? planes : planes * tiles_img;
+    const double resident = blocks < slots ? (double)ceil_div(blocks, cus) : (double)per_cu;
+    const double simd = resident * (waves < units ? waves : units) / 4.0;
+    const double flush = (owned ? 4.3 : q.dtype == DCNV4_F32 ? 10.8 : 8.3) * resident * (double)cells;
+    return (double)(ceil_div(blocks, slots) * (owned ? tiles_img : 1)) * ((1800.0 * ((most + 3) / 4) + 960.0 * most) * (simd + 4.5) + flush);
+}
+
 // Tile choice: output rows per band x columns per tile whose cells fit the LDS, by an estimate of the time (in
 // clocks) of the busiest compute unit, `per_cu` workgroups of `waves` waves on each.  Returns false where no tile fits.
-bool choose_gx_tile(const Problem &q, int waves, int per_cu, int halo, int max_halo, int lds_bytes, int slices, int cus,
+bool choose_gx_tile(const Problem &q, int waves, int per_cu, int halo, int max_halo, int lds_bytes, int slices, int cus, bool owned,
                     GxGeo *p, double *cost_out)
 {
-    const int max_cells = (lds_bytes - kGxCell) / (kGxCell + 4) - 2;
+    const int max_cells = (lds_bytes - kGxCell - 16) / (kGxCell + 4) - 2;
     auto ceil_div = [](long long a, long long b) { return (a + b - 1) / b; };
     // Rows (columns) the largest rectangle of a split into parts of `len` outputs can have; `border`: cells kept
     // outside the image on each side.  Columns need one more cell unless every tile goes from border to border.
@@ -1587,15 +1606,20 @@ bool choose_gx_tile(const Problem &q, int waves, int per_cu, int halo, int max_h
             const int bands = (int)ceil_div(q.Ho, R);
             const long long tiles = (long long)q.N * q.G * slices * bands * tiles_q;
             const int units = (int)ceil_div(R * ceil_div(Q, 4), 4);
-            // the wave with the most units of 16 pixels: per batch of up to four of them the evaluation, per unit the
-            // adds, shared with the other waves of its SIMD; then the flush, which the workgroups of a unit share as
-            // well, and the drained pipeline at the tile's end
-            const int most = (units + waves - 1) / waves;
-            const long long slots = (long long)cus * per_cu;
-            const double resident = tiles < slots ? (double)ceil_div(tiles, cus) : (double)per_cu;
-            const double simd = resident * (waves < units ? waves : units) / 4.0;
-            const double batches = (simd > 1.0 ? simd : 1.0) * (2900.0 * ((most + 3) / 4) + 1200.0 * most);
-            const double cost = (double)ceil_div(tiles, slots) * (batches + 9.0 * resident * (double)(rows * cols) + 5000.0);
+            double cost;
+            if (owned) {
+                cost = gx_time(q, waves, per_cu, slices, cus, R, Q, (long long)bands * tiles_q, rows * cols, true);
+            } else {
+                // the wave with the most units of 16 pixels: per batch of up to four of them the evaluation, per unit the
+                // adds, shared with the other waves of its SIMD; then the flush, which the workgroups of a unit share as
+                // well, and the drained pipeline at the tile's end
+                const int most = (units + waves - 1) / waves;
+                const long long slots = (long long)cus * per_cu;
+                const double resident = tiles < slots ? (double)ceil_div(tiles, cus) : (double)per_cu;
+                const double simd = resident * (waves < units ? waves : units) / 4.0;
+                const double batches = (simd > 1.0 ? simd : 1.0) * (2900.0 * ((most + 3) / 4) + 1200.0 * most);
+                cost = (double)ceil_div(tiles, slots) * (batches + 9.0 * resident * (double)(rows * cols) + 5000.0);
+            }
             if (cost < best) {
                 best = cost;
                 found = true;
@@ -1655,27 +1679,54 @@ int prepare_gx(const Problem &q, GxLaunch *out)
     // in one, 59 in three; two of six waves do not fit a unit's SIMDs together: 28x28x256 fp16 115 -> 150)
     struct {
         int waves, per_cu;
-    } shapes[2] = {{12, 1}, {4, 3}}, pick = {0, 0};
-    const int nshapes = g_opt.gx_threads ? 1 : 2;
+    } shapes[3] = {{12, 1}, {4, 3}, {1, 12}}, pick = {0, 0};
+    const int nshapes = g_opt.gx_threads ? 1 : 3;
     if (g_opt.gx_threads)
         shapes[0].waves = g_opt.gx_threads / 64;
-    double best = 1e30;
     const GxGeo common = p;
-    for (int i = 0; i < nshapes; ++i) {
-        GxGeo t = common;
-        double cost = 0;
-        int lds = (g_opt.lds_kb ? g_opt.lds_kb * 1024 : kMaxLdsBytes) / shapes[i].per_cu & ~1023;
-        if (choose_gx_tile(q, shapes[i].waves, shapes[i].per_cu, halo, max_halo, lds, p.slices, cus, &t, &cost) && cost < best) {
-            best = cost;
-            pick = shapes[i];
-            p = t;
+    auto choose = [&](bool owned) {                     // (the estimate of what it took)
+        double best = 1e30;
+        for (int i = 0; i < nshapes; ++i) {
+            // (one wave: maps of one or two batches, many of them)
+            if (shapes[i].waves == 1 && (!owned || (long long)q.Ho * q.Wo > 128))
+                continue;
+            GxGeo t = common;
+            double cost = 0;
+            int lds = (g_opt.lds_kb ? g_opt.lds_kb * 1024 : kMaxLdsBytes) / shapes[i].per_cu & ~1023;
+            if (choose_gx_tile(q, shapes[i].waves, shapes[i].per_cu, halo, max_halo, lds, p.slices, cus, owned, &t, &cost) && cost < best) {
+                best = cost;
+                pick = shapes[i];
+                p = t;
+            }
         }
-    }
+        return best;
+    };
+    choose(false);
     if (pick.waves == 0)
         return DCNV4_ERR_UNSUPPORTED;
-    const long long nblocks = (long long)q.N * p.tiles_per_img * q.G * p.slices;
-    if (nblocks >= (1LL << 30))
+    // An (image, channel run) to one workgroup, which then stores its sums instead of adding them atomically, where that is
+    // faster in these tiles, or clearly so in others.
+    const long long planes = (long long)q.N * q.G * p.slices;
+    if (g_opt.gx_own == 1) {
+        p.owned = p.tiles_per_img;
+    } else if (g_opt.gx_own == 0 && planes >= cus) {
+        auto now = [&](bool owned) { return gx_time(q, pick.waves, pick.per_cu, p.slices, cus, p.R, p.Q, p.tiles_per_img, p.cells, owned); };
+        const double any = now(false), own = now(true);
+        const GxGeo first = p;
+        const auto first_shape = pick;
+        if (choose(true) < 0.85 * (own < any ? own : any)) {
+            p.owned = p.tiles_per_img;
+        } else {
+            p = first;
+            pick = first_shape;
+            p.owned = own < any ? p.tiles_per_img : 0;
+        }
+    }
+    const long long tiles = planes * p.tiles_per_img;
+    if (tiles >= (1LL << 30))
         return DCNV4_ERR_UNSUPPORTED;
+    const int slots = cus * pick.per_cu;
+    const long long nblocks = p.owned ? planes : tiles;
     p.Wo = q.Wo; p.Ho = q.Ho; p.G = q.G; p.H = q.H; p.W = q.W;
     p.sh = q.sh; p.sw = q.sw; p.ph = q.ph; p.pw = q.pw; p.dh = q.dh; p.dw = q.dw;
     p.scale = q.scale;
@@ -1690,6 +1741,7 @@ int prepare_gx(const Problem &q, GxLaunch *out)
     p.div_s = make_div((unsigned)p.slices);
     p.div_tpi = make_div((unsigned)p.tiles_per_img);
     p.div_tq = make_div((unsigned)p.tiles_q);
+    p.div_pitch = make_div((unsigned)p.pitch);
     p.group_bytes = (int)(q.Cg * es);
     p.pix_bytes = base.pix_bytes;
     p.row_bytes = base.row_bytes;
@@ -1700,15 +1752,15 @@ int prepare_gx(const Problem &q, GxLaunch *out)
     p.off_ext_bytes = (int)((pgi - 1) * p.og_bytes + 18 * es);
     p.msk_ext_bytes = (int)((pgi - 1) * p.mg_bytes + 9 * es);
     out->p = p;
-    out->lds = p.bound_bytes + p.cells * kGxCell;
+    out->lds = p.bound_bytes + p.cells * kGxCell + 16;
     out->waves = pick.waves;
     static int granted[4][kMaxDevices];
     const void *kern = pick.waves == 12  ? reinterpret_cast<const void *>(dcnv4_gradx_kernel<T, 12>)
                        : pick.waves == 8 ? reinterpret_cast<const void *>(dcnv4_gradx_kernel<T, 8>)
-                                         : reinterpret_cast<const void *>(dcnv4_gradx_kernel<T, 4>);
+                       : pick.waves == 4 ? reinterpret_cast<const void *>(dcnv4_gradx_kernel<T, 4>)
+                                         : reinterpret_cast<const void *>(dcnv4_gradx_kernel<T, 1>);
     if (!grant_lds(kern, out->lds, granted[pick.waves / 4]))
         return DCNV4_ERR_LAUNCH;
-    const int slots = cus * pick.per_cu;
     if (p.remap) {
         const int per = slots / kXcds < p.blocks_per_xcd ? slots / kXcds : p.blocks_per_xcd;
         out->grid = (unsigned)(per * kXcds);
@@ -1723,7 +1775,8 @@ int run_gx(const GxLaunch &l, const void *off, const void *msk, const void *gy, 
 {
     auto kern = l.waves == 12  ? dcnv4_gradx_kernel<T, 12>
                 : l.waves == 8 ? dcnv4_gradx_kernel<T, 8>
-                               : dcnv4_gradx_kernel<T, 4>;
+                : l.waves == 4 ? dcnv4_gradx_kernel<T, 4>
+                               : dcnv4_gradx_kernel<T, 1>;
     hipLaunchKernelGGL(kern, dim3(l.grid), dim3((unsigned)l.waves * 64), l.lds, s, (const T *)off, (const T *)msk, (const T *)gy,
                        (T *)gx, l.p);
     const size_t had = strlen(g_last_kernel[1]);             // (the grad_offset/grad_mask pass, launched just before)
@@ -2473,6 +2526,10 @@ int dcnv4_set_option(const char *key, int value)
     }
     if (!strcmp(key, "gx_threads") && (value == 0 || value == 256 || value == 512 || value == 768)) {
         g_opt.gx_threads = value;
+        return DCNV4_OK;
+    }
+    if (!strcmp(key, "gx_own") && value >= 0 && value <= 2) {
+        g_opt.gx_own = value;
         return DCNV4_OK;
     }
     if (!strcmp(key, "fwd_single") && value >= 0 && value <= 2) {

@@ -978,6 +978,42 @@ def test_grad_x_tiles(cfg, dtype, opts):
     close(f"{cfg.name}/{dtype}/grad_x", gom[0].cpu().numpy(), rgx, TOL[dtype])
 
 
+# All tiles of an (image, channel run) by one workgroup, which stores its sums: bands that overlap, taps past the halo and terms
+# too big for the fixed-point sums (both go straight to memory, before and after the stores), tiles split in columns (gx_wide120),
+# one-wave workgroups on many small maps.
+GRADX_OWNED = {"bands": ({"gx_own": 1, "halo": 1, "lds_kb": 40}, [c for c in GRADX if c.name != "gx_pad"]),
+               "own_choice": ({}, [Config("gx_planes", N=20, H=28, W=27, C=256, G=16), Config("gx_seven", N=40, H=7, W=9, C=1024, G=64),
+                                   Config("gx_two_bands", N=16, H=50, W=60, C=256, G=16)])}
+
+
+@pytest.mark.parametrize("opts,cfg", [(o, c) for o, (_, cs) in GRADX_OWNED.items() for c in cs], ids=lambda v: v if isinstance(v, str) else v.name)
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_grad_x_planes_of_one_workgroup(opts, cfg, dtype):
+    if dtype == "f16" and cfg.C // cfg.G == 64:
+        pytest.skip("the half-precision backward takes groups of up to 32 channels")
+    t = make_inputs(cfg, dtype, seed=12)
+    t["grad_y"][0, t["grad_y"].shape[1] // 2, t["grad_y"].shape[2] // 2] = 400.0         # (a term of 64 or more never enters the sums)
+    d = to_gpu(t, dtype)
+    dcn.dcnv4_set_option("bwd_path", 2)
+    for k, v in GRADX_OWNED[opts][0].items():
+        dcn.dcnv4_set_option(k, v)
+    gx = dcn.dcnv4_backward(d["x"], d["offset"], d["mask"], d["grad_y"], **geo_kw(cfg))[0]
+    torch.cuda.synchronize()
+    assert "dcnv4_gradx_kernel" in dcn.dcnv4_last_kernel_name(1)
+    if cfg.name == "gx_seven":
+        assert dcn.dcnv4_last_kernel_name(1).endswith(", 1>")
+    rgx = oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"], **geo_kw(cfg))[0]
+    more = 0.0
+    if dtype == "f16":
+        # the large pixel's terms go to memory in fp16: up to nine per cell, and the stored sum, each rounded to half a unit of a
+        # partial sum that the sum of all magnitudes bounds
+        mags = {k: np.abs(t[k]) for k in ("mask", "grad_y")}
+        alone = np.where(mags["grad_y"] == 400.0, mags["grad_y"], 0).astype(mags["grad_y"].dtype)
+        magnitudes, large = (oracle.backward(t["x"], t["offset"], mags["mask"], gy, **geo_kw(cfg))[0] for gy in (mags["grad_y"], alone))
+        more = 10 * 2.0 ** -11 * np.where(large > 0, magnitudes, 0.0)
+    close(f"{cfg.name}/{dtype}/grad_x", gx.cpu().numpy(), rgx, TOL[dtype], more)
+
+
 @pytest.mark.parametrize("Cg", [8, 16])
 def test_grad_x_of_a_large_tile_that_piles_up_on_one_pixel(Cg):
     """Wide padding around a small map puts tens of thousands of output pixels over a few cells.  Every tap of every
