@@ -949,8 +949,33 @@ int choose_fwd_tiled(const Problem &q, RectForward *out)
     if constexpr (CG * sizeof(T) <= 64 && CG * sizeof(T) >= 16) {
         if constexpr (CG * sizeof(T) == 64) {
             // 64-byte pixels: eight waves still fit the register file (no LDS slices, no exchange registers)
+            if (g_opt.fwd_threads == 64)
+                return prepare_fwd_tiled<T, CG, 64>(q, out);
             if (g_opt.fwd_threads == 256)
                 return prepare_fwd_tiled<T, CG, 256>(q, out);
+            // Whole images of a few batches leave waves of eight idle, and nothing runs beside a refill.  More of them than
+            // compute units go to smaller workgroups with one rectangle each: two of four waves a unit, eight of one wave
+            // where an image is one or two batches.  us, 64 images: fp32 14x14x512, 16 groups 44 -> 34; 20x20x256 35 -> 30;
+            // 28x28x256 57 (strips) -> 52; fp16 28x28x256, 8 groups 38.5 (strips) -> 34.5; merged fp32 7x7x1024 61 -> 19, fp16 41
+            // -> 13.  (With fewer images: 8 of 28x28x256, 13.3 in eight waves and 15.7 like this.)
+            const long long px = (long long)q.Ho * q.Wo, tiles = (long long)q.N * q.G * (q.Cg / CG);
+            const int cus = device_cus();
+            if (g_opt.fwd_threads == 0 && g_opt.fwd_path != 1 && cus > 0 && tiles > cus && px <= 16 * 64) {
+                TGeo whole;
+                if (px <= 128) {
+                    // (fp16 on two separate tensors: the direct kernel, 64 x 8x11x512 13.3 and 14.8)
+                    if ((sizeof(T) == 4 || q.merged || q.softmax) && make_tgeo(q, 64, kTiledFwd, &whole, CG, 1) == DCNV4_OK &&
+                        whole.tiles_per_img == 1)
+                        return finish_fwd_tiled<T, CG, 64>(whole, true, 8, out);
+                } else if (make_tgeo(q, 256, kTiledFwd, &whole, CG, 1) == DCNV4_OK && whole.tiles_per_img == 1 &&
+                           finish_fwd_tiled<T, CG, 256>(whole, true, 2, out) == DCNV4_OK && 2 * out->l.lds <= kMaxLdsBytes) {
+                    // (a last round of four with one wave in it, many times over, is dearer than strips: 30 x 24x24x1024 fp32,
+                    // 32 groups, 9 batches an image: 82.5 and 78.5; 64 x 17x19x256, 6 batches: 27.3 and 29.6)
+                    const long long batches = (px + 63) / 64, rounds = (tiles + 2 * cus - 1) / (2 * cus) * ((batches + 3) / 4);
+                    if (tiles < 6LL * cus || (double)(tiles * batches) >= 0.72 * 8 * (double)(rounds * cus))
+                        return DCNV4_OK;
+                }
+            }
             return prepare_fwd_tiled<T, CG, 512>(q, out);
         }
         if (g_opt.fwd_threads == 256)
@@ -1001,6 +1026,11 @@ int choose_fwd_tiled_cg(const Problem &q, RectForward *out)
     case 32:
     case 64:
         // wider groups go through in slices of 64 bytes (same offsets and mask, own channels)
+        // (in fp16, small maps by the direct kernel where that takes them: 64 images, us: 14x14x512 20 and 23.6 in slices,
+        // 20x20x256 19.4 and 21.5, 28x28x256 34 both)
+        if (sizeof(T) == 2 && q.Cg == 64 && q.Ho * q.Wo <= 512 && q.sh == 1 && q.sw == 1 && 2LL * q.N * q.G > device_cus() && !q.merged && !q.softmax && g_opt.fwd_path == 0 && g_opt.fwd_strip == 0 &&
+            g_opt.fwd_threads == 0)
+            return DCNV4_ERR_UNSUPPORTED;
         if (q.Cg <= kWidest)
             return choose_fwd_tiled<T, 32>(q, out);
         return choose_fwd_tiled<T, kWidest>(q, out);

@@ -2,6 +2,8 @@
 same seeded inputs.  Tolerances: |gpu - ref| <= atol + rtol*|ref| with atol = rtol = 1e-5
 for fp32 and 2e-2 for fp16 storage with fp32 accumulation; `ref` is the double-precision
 oracle evaluated on the already-rounded inputs."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -613,6 +615,38 @@ def test_fp16_groups_of_16_by_number_of_images(cfg, kernel):
 def test_forward_by_the_estimates_of_both_kernels(cfg, dtype, kernel):
     check_forward(cfg, dtype, seed=78)
     assert dcn.dcnv4_last_kernel_name(0).startswith(kernel)
+
+
+# Whole images of 64-byte pixels, more of them than compute units, in small workgroups: one wave for one or two batches, four
+# waves to as large as two rectangles fit the LDS (31x31), with strides and samples far outside.
+SMALL_GROUPS = [(Config("sg_49", N=9, H=7, W=7, C=1024, G=32), 64), (Config("sg_128", N=5, H=8, W=16, C=1024, G=32, sigma=4.0), 64),
+                (Config("sg_129", N=5, H=3, W=43, C=1024, G=32), 256), (Config("sg_s2", N=6, H=25, W=28, C=1024, G=32, stride=2, sigma=4.0), 256),
+                (Config("sg_961", N=5, H=31, W=31, C=1024, G=32, sigma=4.0), 256), (Config("sg_1024", N=5, H=32, W=32, C=1024, G=32), None)]
+
+
+@pytest.mark.parametrize("cfg,threads", SMALL_GROUPS, ids=lambda v: getattr(v, "name", ""))
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("form", ["separate", "merged", "softmax"])
+def test_forward_of_small_images_in_small_workgroups(cfg, threads, dtype, form):
+    if dtype == "f16":                                     # (one run of channels a group, two in fp32)
+        cfg = dataclasses.replace(cfg, N=max(cfg.N, 256 // cfg.G + 1))
+    t = make_inputs(cfg, dtype, seed=79)
+    d = to_gpu(t, dtype)
+    if form == "merged":
+        om = torch.from_numpy(merge_offset_mask(t["offset"], t["mask"], pad_value=5.0)).to("cuda")
+        y = dcn.dcnv4_forward_merged(d["x"], om, **geo_kw(cfg))
+    elif form == "softmax":
+        y = dcn.dcnv4_forward_softmax(d["x"], d["offset"], d["mask"], **geo_kw(cfg))
+    else:
+        y = dcn.dcnv4_forward(d["x"], d["offset"], d["mask"], **geo_kw(cfg))
+    torch.cuda.synchronize()
+    name = dcn.dcnv4_last_kernel_name(0)
+    if threads and not (dtype == "f16" and form == "separate" and threads == 64):
+        assert name == f"dcnv4_tiled_kernel<{'_Float16, 32' if dtype == 'f16' else 'float, 16'}, {threads}, 0>", name
+    else:
+        assert not name.endswith((" 64, 0>", " 256, 0>")), name
+    ref = (oracle.forward_softmax if form == "softmax" else oracle.forward)(t["x"], t["offset"], t["mask"], **geo_kw(cfg))
+    close(f"{cfg.name}/{dtype}/{form}", y.cpu().numpy(), ref, TOL[dtype])
 
 
 STRIP_CASES = [
