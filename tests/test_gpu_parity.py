@@ -1031,7 +1031,8 @@ def test_grad_x_planes_of_one_workgroup(opts, cfg, dtype):
     dcn.dcnv4_set_option("bwd_path", 2)
     for k, v in GRADX_OWNED[opts][0].items():
         dcn.dcnv4_set_option(k, v)
-    gx = dcn.dcnv4_backward(d["x"], d["offset"], d["mask"], d["grad_y"], **geo_kw(cfg))[0]
+    out = tuple(torch.full_like(d[k], 7.0) for k in ("x", "offset", "mask"))      # (grad_x is not cleared by another pass here)
+    gx = dcn.dcnv4_backward(d["x"], d["offset"], d["mask"], d["grad_y"], out=out, **geo_kw(cfg))[0]
     torch.cuda.synchronize()
     assert "dcnv4_gradx_kernel" in dcn.dcnv4_last_kernel_name(1)
     if cfg.name == "gx_seven":
