@@ -1849,7 +1849,17 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
     // (4 images of 48x46, 4 groups, stride 2: error 7e-8 of grad_x, 2e-7 through the fixed-point sums).
     constexpr int kGomWaves = CG * sizeof(T) >= 32 ? 8 : 12;
     StripLaunch l_strip;
+    // More images of one or two batches than compute units (those that no strip takes): one-wave workgroups, where one of eight
+    // waves had work (64 x 7x7x1024 fp16, 64 groups: kernel 82 -> 25 us).
+    bool one_wave = false;
     auto rectangles = [&]() {
+        if constexpr (sizeof(T) == 2) {
+            one_wave = g_opt.bwd_path == 0 && (long long)q.Ho * q.Wo <= 128 && (long long)q.N * q.G > device_cus() &&
+                       prepare_tiled<T, CG, 64, kTiledGradOM>(q, true, 1, CG * sizeof(T) >= 64 ? 4 : 8, &l_gom) == DCNV4_OK &&
+                       l_gom.p.tiles_per_img == 1;
+            if (one_wave)
+                return (int)DCNV4_OK;
+        }
         if constexpr (sizeof(T) == 4) {
             if (gom_direct)
                 return prepare_tiled<T, CG, 512, kTiledGradOMDirect>(q, any_size, 0, 0, &l_gom);
@@ -1917,7 +1927,8 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
         rc = gom_direct ? run_tiled<T, CG, 512, kTiledGradOMDirect>(l_gom, x, off, msk, gy, go, gm, s, 1)
                         : run_tiled<T, CG, THREADS, kTiledGradOM>(l_gom, x, off, msk, gy, go, gm, s, 1);
     } else {
-        rc = run_tiled<T, CG, THREADS, kTiledGradOM>(l_gom, x, off, msk, gy, go, gm, s, 1);
+        rc = one_wave ? run_tiled<T, CG, 64, kTiledGradOM>(l_gom, x, off, msk, gy, go, gm, s, 1)
+                      : run_tiled<T, CG, THREADS, kTiledGradOM>(l_gom, x, off, msk, gy, go, gm, s, 1);
     }
     if (rc == DCNV4_OK && use_gx16)
         return run_gx<T>(l_gx16, off, msk, gy, gx, s);

@@ -1049,6 +1049,27 @@ def test_grad_x_planes_of_one_workgroup(opts, cfg, dtype):
     close(f"{cfg.name}/{dtype}/grad_x", gx.cpu().numpy(), rgx, TOL[dtype], more)
 
 
+@pytest.mark.parametrize("cfg", [Config("gw_49", N=40, H=7, W=7, C=512, G=32, sigma=3.0), Config("gw_49_32", N=40, H=7, W=7, C=1024, G=32),
+                                 Config("gw_49_8", N=40, H=7, W=7, C=256, G=32), Config("gw_1", N=300, H=1, W=1, C=32, G=2)], ids=lambda c: c.name)
+@pytest.mark.parametrize("merged", [False, True])
+def test_backward_of_many_tiny_images_in_one_wave_workgroups(cfg, merged):
+    """grad_offset/grad_mask of images of one batch that no strip takes, by one-wave workgroups."""
+    t = make_inputs(cfg, "f16", seed=14)
+    dcn.dcnv4_set_option("fwd_strip", 2)
+    if merged:
+        d = to_gpu(t, "f16")
+        om = torch.from_numpy(merge_offset_mask(t["offset"], t["mask"], pad_value=5.0)).to("cuda")
+        gom = dcn.dcnv4_backward_merged(d["x"], om, d["grad_y"], **geo_kw(cfg))[1].cpu().numpy()
+        rgx, rgo, rgm = oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"], **geo_kw(cfg))
+        close(f"{cfg.name}/grad_offset", gom[..., :18], rgo.reshape(*gom.shape[:-1], 18), TOL["f16"])
+        close(f"{cfg.name}/grad_mask", gom[..., 18:27], rgm, TOL["f16"])
+        assert not gom[..., 27:].any()
+    else:
+        check_backward(cfg, dtype="f16", inputs=t)
+    if cfg.C // cfg.G > 8:                                # (groups of 8: the name of the grad_x pass replaces it)
+        assert f"dcnv4_tiled_kernel<_Float16, {cfg.C // cfg.G}, 64, 1>" in dcn.dcnv4_last_kernel_name(1)
+
+
 @pytest.mark.parametrize("Cg", [8, 16])
 def test_grad_x_of_a_large_tile_that_piles_up_on_one_pixel(Cg):
     """Wide padding around a small map puts tens of thousands of output pixels over a few cells.  Every tap of every
