@@ -1850,7 +1850,7 @@ int launch_bwd_tiled(const void *x, const void *off, const void *msk, const void
     constexpr int kGomWaves = CG * sizeof(T) >= 32 ? 8 : 12;
     StripLaunch l_strip;
     // More images of one or two batches than compute units (those that no strip takes): one-wave workgroups, where one of eight
-    // waves had work (64 x 7x7x1024 fp16, 64 groups: kernel 82 -> 25 us).
+    // waves had work (64 x 7x7x1024 fp16, 64 groups: kernel 82 -> 20 us).
     bool one_wave = false;
     auto rectangles = [&]() {
         if constexpr (sizeof(T) == 2) {
