@@ -39,6 +39,20 @@ def geo_kw(cfg):
     return dict(kernel=cfg.kernel, stride=cfg.stride, pad=cfg.pad, dilation=cfg.dilation, offset_scale=cfg.offset_scale)
 
 
+def forward_in(form, cfg, t, dtype):
+    """The forward of inputs t in one of its three forms, on the host."""
+    d = to_gpu(t, dtype)
+    if form == "merged":
+        om = torch.from_numpy(merge_offset_mask(t["offset"], t["mask"], pad_value=5.0)).to("cuda", TORCH_DT[dtype])
+        y = dcn.dcnv4_forward_merged(d["x"], om, **geo_kw(cfg))
+    elif form == "softmax":
+        y = dcn.dcnv4_forward_softmax(d["x"], d["offset"], d["mask"], **geo_kw(cfg))
+    else:
+        y = dcn.dcnv4_forward(d["x"], d["offset"], d["mask"], **geo_kw(cfg))
+    torch.cuda.synchronize()
+    return y.cpu().numpy()
+
+
 def check_forward(cfg, dtype, seed=0, inputs=None):
     t = inputs if inputs is not None else make_inputs(cfg, dtype, seed=seed)
     d = to_gpu(t, dtype)
@@ -826,6 +840,30 @@ def test_strip_offsets_whose_scaled_value_is_past_fp32_lie_outside(cfg, scale):
     # (grad_offset is scale times the gradient of the position, which is held to the tolerance)
     for name, g, ref, tol in zip(("grad_offset", "grad_mask"), got, refs, (abs(scale) * TOL["f32"], TOL["f32"])):
         close(f"{cfg.name}/{name}", g.cpu().numpy(), ref, tol)
+
+
+PAST_FP32 = [("whole", "separate", Config("pf_whole", N=17, H=14, W=14, C=512, G=32), {}),
+             ("one_wave", "merged", Config("pf_one_wave", N=5, H=7, W=7, C=1024, G=32), {}),
+             ("bands", "separate", Config("pf_bands", N=2, H=40, W=37, C=64, G=4), {"fwd_path": 2, "lds_kb": 40, "halo": 2}),
+             ("groups_of_8", "softmax", Config("pf_8", N=2, H=20, W=21, C=32, G=4), {"fwd_path": 2})]
+
+
+@pytest.mark.parametrize("case", PAST_FP32, ids=lambda c: c[0])
+@pytest.mark.parametrize("scale", [4.0, -2.0])                        # (products of ordinary offsets are exact)
+def test_rectangle_offsets_whose_scaled_value_is_past_fp32_lie_outside(case, scale):
+    """As in the strips: nothing, in windows that are clipped (where the clamped sample lies on the zero border) and not."""
+    _, form, cfg, opts = case
+    cfg = cfg.with_(offset_scale=scale)
+    t = make_inputs(cfg, "f32", seed=83)
+    rng = np.random.default_rng(83)
+    for v in (3.0e38, -3.4e38):
+        t["offset"][rng.random(t["offset"].shape) < 0.004] = v
+    for k, v in opts.items():
+        dcn.dcnv4_set_option(k, v)
+    y = forward_in(form, cfg, t, "f32")
+    assert dcn.dcnv4_last_kernel_name(0).startswith("dcnv4_tiled_kernel<")
+    ref = (oracle.forward_softmax if form == "softmax" else oracle.forward)(t["x"], t["offset"], t["mask"], **geo_kw(cfg))
+    close(f"{cfg.name}/{form}", y, ref, TOL["f32"])
 
 
 def test_strip_forward_over_more_rounds_than_its_table_holds():
