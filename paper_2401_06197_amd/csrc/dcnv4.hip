@@ -329,8 +329,14 @@ __global__ __launch_bounds__(kThreads) void dcnv4_fwd_kernel(const T *__restrict
 #pragma unroll
         for (int i = 0; i < KH; ++i) {
             const int k = j * KH + i;
-            const Tap t = tap_geometry((float)my_off[2 * k + 1], (float)my_off[2 * k], bh + i * p.dh, bw + j * p.dw,
-                                       chan_bytes, p);
+            const float off_y = (float)my_off[2 * k + 1], off_x = (float)my_off[2 * k];
+            Tap t = tap_geometry(off_y, off_x, bh + i * p.dh, bw + j * p.dw, chan_bytes, p);
+            // fp16 groups of 64, which come here and go through rectangles: an infinite offset has no fractional part there either
+            // (NaN, not a clamped one's; the host keeps finite products finite)
+            if constexpr (sizeof(T) == 2 && CG == 64 && KH == 3) {
+                t.lh = __builtin_amdgcn_fractf(p.scale * off_y);
+                t.lw = __builtin_amdgcn_fractf(p.scale * off_x);
+            }
             Vec<T, CPT> v00, v01, v10, v11;
             v00.load(rx, t.o00);
             v01.load(rx, t.o01);
@@ -655,6 +661,9 @@ int launch_fwd(const void *x, const void *off, const void *msk, void *y, const P
     int rc = make_geo(q, CG / CPT, &p);
     if (rc)
         return rc;
+    // (products of finite fp16 offsets stay finite; past this scale the smallest offset but zero is outside the image all the same)
+    if (sizeof(T) == 2 && CG == 64 && KS == 3)
+        p.scale = fminf(fmaxf(p.scale, -5e33f), 5e33f);
     hipLaunchKernelGGL((dcnv4_fwd_kernel<T, CG, CPT, KS, KS>), dim3(grid_of(p)), dim3(kThreads), 0, s, (const T *)x,
                        (const T *)off, (const T *)msk, (T *)y, p);
     if (KS == 3)

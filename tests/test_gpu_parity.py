@@ -842,6 +842,29 @@ def test_strip_offsets_whose_scaled_value_is_past_fp32_lie_outside(cfg, scale):
         close(f"{cfg.name}/{name}", g.cpu().numpy(), ref, tol)
 
 
+def check_forward_of_offsets_that_are_no_numbers(cfg, dtype, kernel, form="separate"):
+    """NaN where the oracle's result is NaN, and there only."""
+    t = make_inputs(cfg, dtype, seed=85)
+    rng = np.random.default_rng(85)
+    for v in (np.inf, -np.inf, np.nan):
+        t["offset"][rng.random(t["offset"].shape) < 0.002] = v
+    y = forward_in(form, cfg, t, dtype)
+    assert dcn.dcnv4_last_kernel_name(0).startswith(kernel), dcn.dcnv4_last_kernel_name(0)
+    ref = (oracle.forward_softmax if form == "softmax" else oracle.forward)(t["x"], t["offset"], t["mask"], **geo_kw(cfg))
+    bad = np.isnan(ref)
+    assert bad.any() and not bad.all()
+    assert np.array_equal(np.isnan(y), bad), f"{cfg.name}/{dtype}/{form}: NaN in other places than the oracle's"
+    close(f"{cfg.name}/{dtype}/{form}", y[~bad], ref[~bad], TOL[dtype])
+
+
+@pytest.mark.parametrize("cfg", [Config("di_64", N=17, H=14, W=14, C=512, G=8),                    # (smaller batches: slices of rectangles)
+                                 Config("di_7", N=2, H=7, W=7, C=128, G=2), Config("di_s2", N=1, H=22, W=25, C=192, G=3, stride=2),
+                                 Config("di_scale", N=17, H=14, W=14, C=512, G=8, offset_scale=1e35)], ids=lambda c: c.name)
+def test_direct_forward_of_fp16_groups_of_64_with_infinite_offsets_gives_what_the_oracle_gives(cfg):
+    dcn.dcnv4_set_option("fwd_path", 0 if cfg.N == 17 else 1)
+    check_forward_of_offsets_that_are_no_numbers(cfg, "f16", "dcnv4_fwd_kernel<")
+
+
 PAST_FP32 = [("whole", "separate", Config("pf_whole", N=17, H=14, W=14, C=512, G=32), {}),
              ("one_wave", "merged", Config("pf_one_wave", N=5, H=7, W=7, C=1024, G=32), {}),
              ("bands", "separate", Config("pf_bands", N=2, H=40, W=37, C=64, G=4), {"fwd_path": 2, "lds_kb": 40, "halo": 2}),
