@@ -865,6 +865,16 @@ def test_direct_forward_of_fp16_groups_of_64_with_infinite_offsets_gives_what_th
     check_forward_of_offsets_that_are_no_numbers(cfg, "f16", "dcnv4_fwd_kernel<")
 
 
+@pytest.mark.parametrize("form,cfg,opts", [
+    ("separate", Config("ri_bands", N=2, H=40, W=37, C=64, G=4), {"fwd_path": 2, "lds_kb": 40, "halo": 2}),       # sides that are not clipped
+    ("merged", Config("ri_8", N=2, H=33, W=21, C=32, G=4), {"fwd_path": 2, "lds_kb": 24, "halo": 1})], ids=lambda v: getattr(v, "name", ""))
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_rectangle_forward_of_infinite_offsets_gives_what_the_oracle_gives(form, cfg, opts, dtype):
+    for k, v in opts.items():
+        dcn.dcnv4_set_option(k, v)
+    check_forward_of_offsets_that_are_no_numbers(cfg, dtype, "dcnv4_tiled_kernel<", form)
+
+
 PAST_FP32 = [("whole", "separate", Config("pf_whole", N=17, H=14, W=14, C=512, G=32), {}),
              ("one_wave", "merged", Config("pf_one_wave", N=5, H=7, W=7, C=1024, G=32), {}),
              ("bands", "separate", Config("pf_bands", N=2, H=40, W=37, C=64, G=4), {"fwd_path": 2, "lds_kb": 40, "halo": 2}),
