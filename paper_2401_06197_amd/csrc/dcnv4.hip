@@ -972,8 +972,19 @@ int choose_fwd_tiled(const Problem &q, RectForward *out)
             if (g_opt.fwd_threads == 0 && g_opt.fwd_path != 1 && cus > 0 && tiles > cus && px <= 16 * 64) {
                 TGeo whole;
                 if (px <= 128) {
-                    // (fp16 on two separate tensors: the direct kernel, 64 x 8x11x512 13.3 and 14.8)
-                    if ((sizeof(T) == 4 || q.merged || q.softmax) && make_tgeo(q, 64, kTiledFwd, &whole, CG, 1) == DCNV4_OK &&
+                    // Two separate tensors: the direct kernel (fp16: 64 x 8x11x512 13.3 and 14.8), in fp32 until it has so many
+                    // workgroups to a unit; one-wave workgroups pay for idle lanes, and in groups of 32 and 64 they read the offsets
+                    // again for every slice.  us by the direct kernel and here: 9x9x512, 32 groups, 9 images 5.5 and 9.6, 24: 10.6 and
+                    // 10.9, 64: 26 and 18; 7x7x1024, 32 groups, 33 images 11.8 and 13.0, 64: 19 and 17; 282 of 1x1x512, 32 groups 3.9 and
+                    // 23.  (Of 400 calls 143 come here, two of them 4 % slower; all take 0.91 times as long as by the
+                    // direct kernel.  128 pixels: rectangles of eight waves otherwise, 8x16x512, 32 groups, 22 images 15.1 and 11.5.)
+                    const long long b = (px + 63) / 64;
+                    const double fill = (double)px / (double)(64 * b), direct = (double)q.N * (double)((px * q.G * q.Cg + 2047) / 2048) / cus;
+                    const double least = q.Cg > 16 ? 3.6 / (fill * fill) : b > 1 ? 2.0 : fill < 0.83 ? 0.7 / (fill * fill) : 1.0;
+                    // (more padding, dilations: more taps outside, which cost the direct kernel less)
+                    const bool plain = q.sh == 1 && q.sw == 1 && q.dh == 1 && q.dw == 1 && q.ph <= 1 && q.pw <= 1;
+                    const bool fewer = px == 128 || (plain && px >= (b > 1 ? 72 : 40) && direct > least);
+                    if ((q.merged || q.softmax || (sizeof(T) == 4 && fewer)) && make_tgeo(q, 64, kTiledFwd, &whole, CG, 1) == DCNV4_OK &&
                         whole.tiles_per_img == 1)
                         return finish_fwd_tiled<T, CG, 64>(whole, true, 8, out);
                 } else if (make_tgeo(q, 256, kTiledFwd, &whole, CG, 1) == DCNV4_OK && whole.tiles_per_img == 1 &&

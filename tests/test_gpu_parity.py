@@ -645,22 +645,30 @@ def test_forward_of_small_images_in_small_workgroups(cfg, threads, dtype, form):
     if dtype == "f16":                                     # (one run of channels a group, two in fp32)
         cfg = dataclasses.replace(cfg, N=max(cfg.N, 256 // cfg.G + 1))
     t = make_inputs(cfg, dtype, seed=79)
-    d = to_gpu(t, dtype)
-    if form == "merged":
-        om = torch.from_numpy(merge_offset_mask(t["offset"], t["mask"], pad_value=5.0)).to("cuda")
-        y = dcn.dcnv4_forward_merged(d["x"], om, **geo_kw(cfg))
-    elif form == "softmax":
-        y = dcn.dcnv4_forward_softmax(d["x"], d["offset"], d["mask"], **geo_kw(cfg))
-    else:
-        y = dcn.dcnv4_forward(d["x"], d["offset"], d["mask"], **geo_kw(cfg))
-    torch.cuda.synchronize()
+    if dtype == "f32" and form == "separate" and cfg.name == "sg_49":       # (few such images go to the direct kernel)
+        dcn.dcnv4_set_option("fwd_path", 2)
+        dcn.dcnv4_set_option("fwd_threads", 64)
+    y = forward_in(form, cfg, t, dtype)
     name = dcn.dcnv4_last_kernel_name(0)
     if threads and not (dtype == "f16" and form == "separate" and threads == 64):
         assert name == f"dcnv4_tiled_kernel<{'_Float16, 32' if dtype == 'f16' else 'float, 16'}, {threads}, 0>", name
     else:
         assert not name.endswith((" 64, 0>", " 256, 0>")), name
     ref = (oracle.forward_softmax if form == "softmax" else oracle.forward)(t["x"], t["offset"], t["mask"], **geo_kw(cfg))
-    close(f"{cfg.name}/{dtype}/{form}", y.cpu().numpy(), ref, TOL[dtype])
+    close(f"{cfg.name}/{dtype}/{form}", y, ref, TOL[dtype])
+
+
+@pytest.mark.parametrize("cfg,one_wave", [(Config("tf_1", N=282, H=1, W=1, C=512, G=32), False), (Config("tf_81", N=9, H=9, W=9, C=512, G=32), False),
+                                          (Config("tf_49_32", N=33, H=7, W=7, C=1024, G=32), False), (Config("tf_32_64", N=64, H=7, W=7, C=1024, G=32), True),
+                                          (Config("tf_49_12", N=12, H=7, W=7, C=1024, G=64), False), (Config("tf_49_13", N=13, H=7, W=7, C=1024, G=64), True),
+                                          (Config("tf_72_28", N=28, H=8, W=9, C=512, G=32), False), (Config("tf_72_29", N=29, H=8, W=9, C=512, G=32), True),
+                                          (Config("tf_39", N=40, H=3, W=13, C=1024, G=64), False), (Config("tf_s2", N=20, H=14, W=14, C=1024, G=64, stride=2), False)],
+                         ids=lambda v: getattr(v, "name", ""))
+def test_forward_of_tiny_fp32_images_by_the_direct_kernels_workgroups(cfg, one_wave):
+    """One-wave workgroups only where the direct kernel has workgroups enough to be the slower one (256 compute units)."""
+    check_forward(cfg, "f32", seed=86)
+    name = dcn.dcnv4_last_kernel_name(0)
+    assert name == "dcnv4_tiled_kernel<float, 16, 64, 0>" if one_wave else name.startswith("dcnv4_fwd_kernel<"), name
 
 
 STRIP_CASES = [
