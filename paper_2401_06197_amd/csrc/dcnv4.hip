@@ -1036,6 +1036,17 @@ int choose_fwd_tiled(const Problem &q, RectForward *out)
     return DCNV4_ERR_UNSUPPORTED;
 }
 
+// fp16 groups of 64 on small maps, more of them than half the compute units: the direct kernel where rectangles would go through
+// them in slices (64 images, us: 14x14x512 18 and 24, 20x20x256 19 and 22; 29 random calls 0.46 to 0.91 times as long), and before
+// strips up to 45 batches a unit (13 calls by strips 0.97 to 1.35 times as long; 10 of more batches 0.89 to 1.06 times: 35 of 15x25,
+// 32 groups, 67 us by strips and 75).
+long long wide_batches(const Problem &q) { return (long long)q.N * q.G * 2 * (((long long)q.Ho * q.Wo + 63) / 64); }
+template <typename T> bool direct_for_wide_groups(const Problem &q)
+{
+    return sizeof(T) == 2 && q.Cg == 64 && (long long)q.Ho * q.Wo <= 512 && q.sh == 1 && q.sw == 1 && 2LL * q.N * q.G > device_cus() &&
+           !q.merged && !q.softmax && g_opt.fwd_path == 0 && g_opt.fwd_strip == 0 && g_opt.fwd_threads == 0;
+}
+
 template <typename T>
 int choose_fwd_tiled_cg(const Problem &q, RectForward *out)
 {
@@ -1046,11 +1057,11 @@ int choose_fwd_tiled_cg(const Problem &q, RectForward *out)
     case 32:
     case 64:
         // wider groups go through in slices of 64 bytes (same offsets and mask, own channels)
-        // (in fp16, small maps by the direct kernel where that takes them: 64 images, us: 14x14x512 20 and 23.6 in slices,
-        // 20x20x256 19.4 and 21.5, 28x28x256 34 both)
-        if (sizeof(T) == 2 && q.Cg == 64 && q.Ho * q.Wo <= 512 && q.sh == 1 && q.sw == 1 && 2LL * q.N * q.G > device_cus() && !q.merged && !q.softmax && g_opt.fwd_path == 0 && g_opt.fwd_strip == 0 &&
-            g_opt.fwd_threads == 0)
-            return DCNV4_ERR_UNSUPPORTED;
+        if constexpr (sizeof(T) == 2) {
+            // (rectangles that the strips are compared with: not launched themselves)
+            if (direct_for_wide_groups<T>(q))
+                return wide_batches(q) < 45LL * device_cus() ? DCNV4_ERR_UNSUPPORTED : prepare_fwd_tiled<T, kWidest, 512>(q, out);
+        }
         if (q.Cg <= kWidest)
             return choose_fwd_tiled<T, 32>(q, out);
         return choose_fwd_tiled<T, kWidest>(q, out);
@@ -1509,7 +1520,7 @@ int dispatch_fwd(const void *x, const void *off, const void *msk, void *y, const
             if (rs != DCNV4_ERR_UNSUPPORTED || g_opt.fwd_strip == 1)
                 return rs;
         }
-        if (rc == DCNV4_OK)
+        if (rc == DCNV4_OK && !direct_for_wide_groups<T>(q))
             return rect.run(rect.l, x, off, msk, nullptr, y, nullptr, s, 0);
         if (g_opt.fwd_path == 2)
             return rc;

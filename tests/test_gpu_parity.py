@@ -671,6 +671,22 @@ def test_forward_of_tiny_fp32_images_by_the_direct_kernels_workgroups(cfg, one_w
     assert name == "dcnv4_tiled_kernel<float, 16, 64, 0>" if one_wave else name.startswith("dcnv4_fwd_kernel<"), name
 
 
+@pytest.mark.parametrize("cfg,kernel", [(Config("fw_16", N=64, H=14, W=14, C=512, G=8), "dcnv4_fwd_kernel<"),      # 16 batches a unit
+                                        (Config("fw_52", N=35, H=15, W=25, C=2048, G=32), "dcnv4_strip_kernel<"),
+                                        (Config("fw_65", N=349, H=9, W=16, C=512, G=8), "dcnv4_fwd_kernel<"),         # (strips are slower)
+                                        (Config("fw_few", N=1, H=14, W=14, C=512, G=8), "dcnv4_tiled_kernel<")], ids=lambda v: getattr(v, "name", ""))
+def test_forward_of_fp16_groups_of_64_on_small_maps(cfg, kernel):
+    """Strips, direct kernel and rectangles by the batches of a unit; the same results as the direct kernel's."""
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    rand = lambda *shape: torch.randn(shape, generator=gen, device="cuda").half()
+    x, off, m = rand(cfg.N, cfg.H, cfg.W, cfg.C), 2 * rand(cfg.N, cfg.H, cfg.W, cfg.G, 9, 2), rand(cfg.N, cfg.H, cfg.W, cfg.G, 9)
+    y = dcn.dcnv4_forward(x, off, m)
+    assert dcn.dcnv4_last_kernel_name(0).startswith(kernel), dcn.dcnv4_last_kernel_name(0)
+    dcn.dcnv4_set_option("fwd_path", 1)
+    ref = dcn.dcnv4_forward(x, off, m).float()
+    assert ((y.float() - ref).abs() <= TOL["f16"] * (1 + ref.abs())).all()
+
+
 STRIP_CASES = [
     Config("st_rows", N=3, H=23, W=60, C=64, G=4),                    # 64 columns with the border: whole KiB rows in fp32
     Config("st_rows1", N=2, H=30, W=61, C=64, G=4),                   # one column more
