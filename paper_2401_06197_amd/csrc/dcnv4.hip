@@ -366,6 +366,7 @@ __global__ __launch_bounds__(kThreads) void dcnv4_fwd_kernel(const T *__restrict
 #include "dcnv4_gradx.inc"
 #include "dcnv4_ring.inc"
 #include "dcnv4_strip.inc"
+#include "dcnv4_linear_choice.h"
 #include "dcnv4_linear.inc"
 #include "dcnv4_linear_tile.inc"
 
@@ -2006,9 +2007,6 @@ template <typename T, int WR, int WC, int WM, int WN, int STAGES> int launch_lin
     return hipGetLastError() == hipSuccess ? DCNV4_OK : DCNV4_ERR_LAUNCH;
 }
 
-// Tiles of the linear layers: channels x pixels, waves.
-enum { kLinear128x128 = 1, kLinear64x64 = 2, kLinear256x256 = 3, kLinear128x256 = 4, kLinearInOneChunk = 5 };
-
 template <typename T> int launch_linear_shape(int shape, const void *x, const LinGeo &g, hipStream_t s)
 {
     constexpr bool f16 = sizeof(T) == 2;
@@ -2022,53 +2020,10 @@ template <typename T> int launch_linear_shape(int shape, const void *x, const Li
     return launch_linear_tile<T, 2, 2, 2, 2, 2>(x, g, s);
 }
 
-// The tile with the lowest estimated time.  A tile takes `step` us for 128 (fp16) or 64 (fp32) bytes of K and `fixed` for
-// its first loads and its results; a compute unit works through its share one after the other or, of the 128x128 and 64x64
-// tiles, several side by side, where half the difference between the fullest unit and the mean is felt; a lone tile's step
-// takes `alone` at least.  Constants from ten to twenty layers each (49 to 200704 pixels, K 64 to 1024, 64 to 2048 channels),
-// over which the estimates are within 15 % and the choice costs 4 % at most.  us, fp32: 12544 pixels, 512 -> 1024: 92 (128x128), 101, 75 (256x256), 86
-// (128x256); 512 -> 512: 48, 56, 64, 44.5; 4000 pixels, 512 -> 512: 30, 21.8 (64x64), 59, 39.  fp16, 12544 pixels, 512 -> 1024: 24,
-// 34, 21.8; 512 -> 512: 13.5, 19.2, 18.5; 1000 pixels, 1024 -> 1024: 13.9, 7.9, 27.
 int pick_linear_tile(const LinGeo &g, int dtype)
 {
-    struct Tile {
-        int shape, run, waves_out, pixels;
-        bool side_by_side;
-        float step, fixed, alone;
-    };
-    static const Tile f16_tiles[] = {{kLinear128x128, 64, 2, 128, true, .55f, 1.9f, .55f},
-                                     {kLinear64x64, 32, 2, 64, true, .17f, 1.2f, .25f},
-                                     {kLinear256x256, 64, 4, 256, false, 1.15f, 8.6f, 1.15f}};
-    static const Tile f32_tiles[] = {{kLinear128x128, 64, 2, 128, true, .72f, 3.f, .72f},
-                                     {kLinear64x64, 32, 2, 64, true, .23f, .88f, .36f},
-                                     {kLinear256x256, 64, 4, 256, false, 1.76f, 15.6f, 1.76f},
-                                     {kLinear128x256, 64, 2, 256, false, 1.2f, 5.f, 1.2f}};
-    const bool f16 = dtype == DCNV4_F16;
-    const Tile *tiles = f16 ? f16_tiles : f32_tiles;
-    const int count = f16 ? 3 : 4, cus = device_cus();
-    const float steps = (float)((g.kbytes + (f16 ? 127 : 63)) / (f16 ? 128 : 64));
-    int best = 0;
-    float best_us = 0.f, small = 0.f;
-    for (int i = 0; i < count; ++i) {
-        const Tile &t = tiles[i];
-        int runs = 0;
-        for (int k = 0; k < g.nseg; ++k)
-            runs += (g.seg[k].nout + t.run - 1) / t.run;
-        const float n = (float)((runs + t.waves_out - 1) / t.waves_out) * (float)((g.P + t.pixels - 1) / t.pixels) / (float)cus;
-        const float full = ceilf(n), share = t.side_by_side && n > 1.f ? .5f * (n + full) : full;
-        const float us = steps * (t.step * share > t.alone ? t.step * share : t.alone) + t.fixed * share;
-        if (t.shape == kLinear64x64)
-            small = n;
-        if (best == 0 || us < best_us) {
-            best = t.shape;
-            best_us = us;
-        }
-    }
-    // K in one chunk, fp16: 64x64 tiles up to two a compute unit (3136 pixels, 128 -> 256: 3.8 us, 5.1 in one chunk; 12544 pixels:
-    // 7.6 and 6.8)
-    if (f16 && g.kbytes <= kLinChunk)
-        return small <= 2.f ? kLinear64x64 : kLinearInOneChunk;
-    return best;
+    const int nout[kLinMaxSeg] = {g.seg[0].nout, g.nseg > 1 ? g.seg[1].nout : 0};
+    return linear_tile_choice(g.P, g.kbytes, nout, g.nseg, dtype == DCNV4_F16, device_cus());
 }
 
 }  // namespace
