@@ -257,6 +257,9 @@ long long dcnv4_backward_merged_algorithmic_bytes(int N, int H, int W, int G, in
  *                 LDS allows)
  *   "module_rows" 1 = dcnv4_module_forward keeps the tensors between its layers channel-last (default: the
  *                 full module keeps them plane-major, one (image, group) after the other)
+ *   "linear_tile" tile of the linear layers, output channels x pixels: 1 = 128x128, 2 = 64x64, 3 = 256x256,
+ *                 4 = 128x256 (fp32), 5 = the kernel that reads x once (fp16, K of up to 256 bytes); 0 = the one
+ *                 with the lowest estimated time.  A tile that a type or K does not have: DCNV4_ERR_UNSUPPORTED
  *   "gom_coop"    1 = the fp32 grad_offset/grad_mask pass moves its values through per-wave LDS slices
  *                 even for whole groups (default: each lane reads and writes its own pixel's values)
  *   "gx_threads"  workgroup size of the staged grad_x kernel (256, 512 or 768)

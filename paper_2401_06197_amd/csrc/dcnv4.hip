@@ -534,7 +534,7 @@ struct Options {
     int gx_own = 0;        // grad_x kernel, an (image, channel run) to one workgroup: 1 always, 2 never
     int gom_coop = 0;      // 1: the fp32 grad_offset/grad_mask pass goes through LDS slices even for whole groups
     int fwd_strip = 0;     // forward and grad_offset/grad_mask out of a rolling window of rows: 1 wherever it applies, 2 never
-    int linear_tile = 0;   // tile of the linear layers: 1 128x128, 2 64x64, 3 256x256, 4 128x256 (fp32), 5 K in one chunk (fp16, up to 256 bytes)
+    int linear_tile = 0;   // tile of the linear layers (linear_tile_choice)
     int module_rows = 0;   // 1: the module keeps its tensors channel-last between the layers (default: plane-major)
 } g_opt;
 
@@ -2197,7 +2197,10 @@ int begin_linear(LinGeo *g, const void *x, long long P, int K, int dtype)
 int launch_linear(const void *x, const LinGeo &g, int dtype, hipStream_t s)
 {
     const int shape = g_opt.linear_tile != 0 ? g_opt.linear_tile : pick_linear_tile(g, dtype);
-    if (shape != kLinearInOneChunk || dtype != DCNV4_F16 || g.kbytes > kLinChunk)
+    // (asked for by option: a tile that the type, or K, does not have)
+    if (dtype == DCNV4_F16 ? shape == kLinear128x256 || (shape == kLinearInOneChunk && g.kbytes > kLinChunk) : shape == kLinearInOneChunk)
+        return DCNV4_ERR_UNSUPPORTED;
+    if (shape != kLinearInOneChunk)
         return dtype == DCNV4_F16 ? launch_linear_shape<_Float16>(shape, x, g, s) : launch_linear_shape<float>(shape, x, g, s);
     const int tiles = (g.P + kLinPixels - 1) / kLinPixels;
     // maps of few pixels and many channels: the passes over blocks of output channels are spread over

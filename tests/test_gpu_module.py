@@ -256,13 +256,77 @@ def test_linear_fp32_small_numbers_keep_their_bits(K, ex, ew):
     assert ((y - ref).abs() <= lim).all(), ((y - ref).abs() / lim).max()
 
 
-@pytest.mark.parametrize("tile", [1, 2, 3, 4, 5])
-@pytest.mark.parametrize("dtype", ["f32", "f16"])
+TILES = [(1, "f32"), (2, "f32"), (3, "f32"), (4, "f32"), (1, "f16"), (2, "f16"), (3, "f16"), (5, "f16")]      # (5: K up to 256 bytes)
+
+
+@pytest.mark.parametrize("tile,dtype", TILES)
 def test_linear_tiles(tile, dtype):
     """Every tile at its edges: one pixel, a pixel less and more than a tile, runs of channels cut short, K of one unit,
     of less than a step, of steps and a part; and the module, whose first launch has two layers and plane-major results."""
     for P, K, Nout in [(1, 16, 32), (63, 48, 96), (65, 64, 160), (255, 144, 64), (257, 208, 288), (130, 528, 128), (513, 96, 544)]:
         dcn.dcnv4_set_option("linear_tile", tile)
-        test_linear_layer_matches_oracle(P, K, Nout, dtype)
-    for cfg in (MODULE_CASES[3], MODULE_CASES[6], Config("m_two", N=2, H=9, W=11, C=192, G=6)):
+        if tile == 5 and K > 128:
+            with pytest.raises(dcn.Dcnv4Error):                              # a tile that there is not is refused, not replaced
+                test_linear_layer_matches_oracle(P, K, Nout, dtype)
+        else:
+            test_linear_layer_matches_oracle(P, K, Nout, dtype)
+    for cfg in (MODULE_CASES[3], MODULE_CASES[6]) + (() if tile == 5 else (Config("m_two", N=2, H=9, W=11, C=192, G=6),)):
         run_module(cfg, dtype, lightweight=False)
+
+
+@pytest.mark.parametrize("tile,dtype", [(4, "f16"), (5, "f32")])
+def test_linear_tiles_that_a_type_does_not_have_are_refused(tile, dtype):
+    dcn.dcnv4_set_option("linear_tile", tile)
+    with pytest.raises(dcn.Dcnv4Error) as e:
+        test_linear_layer_matches_oracle(64, 64, 64, dtype)
+    assert e.value.status == 3
+
+
+@pytest.mark.parametrize("tile", [1, 2, 3, 4])
+def test_linear_fp32_tiles_make_blocks_of_special_operands_again(tile):
+    """Small numbers, infinities, NaNs and numbers that round to infinity in bf16, in different blocks of 32 pixels and of 32
+    channels (first, inner, last, of the first and of later tiles), among ordinary ones; bounds as above."""
+    dcn.dcnv4_set_option("linear_tile", tile)
+    P, K, nout = 521, 80, 544
+    g = torch.Generator().manual_seed(9)
+    x, w = torch.randn(P, K, generator=g), torch.randn(nout, K, generator=g)
+    w[:, 0] = torch.where(w[:, 0] < 0, -0.25, 0.25)
+    for p in (3, 100, 161, 255, 300, 520):
+        x[p] *= 2.0 ** -120
+    for o in (5, 66, 191, 288, 543):
+        w[o] *= 2.0 ** -116
+    for p, v in ((40, np.inf), (130, -np.inf), (200, np.nan), (410, np.inf), (515, float(np.finfo(np.float32).max))):
+        x[p, 0] = v
+    w[350, 7], w[127, 3] = np.nan, np.inf
+    y = dcn.dcnv4_linear(x.cuda(), w.cuda(), None).cpu()
+    ref = x.double() @ w.double().T
+    assert torch.equal(torch.isnan(y), torch.isnan(ref)) and torch.equal(torch.isinf(y), torch.isinf(ref))
+    assert torch.equal(y[torch.isinf(ref)].double(), ref[torch.isinf(ref)])
+    lim = 2.0 ** -24 * K ** 0.5 * x.double().norm(dim=1)[:, None] * w.double().norm(dim=1)[None, :] + K * 2.0 ** -149
+    fin = torch.isfinite(ref)
+    assert ((y.double() - ref).abs()[fin] <= lim[fin]).all(), ((y.double() - ref).abs() / lim)[fin].max()
+    test_linear_fp32_rows_with_one_weight(64)
+    test_linear_fp32_infinities_and_large_numbers_are_those_of_fp32()
+
+
+@pytest.mark.parametrize("tile", [1, 2, 3, 4])
+def test_module_fp32_with_small_values_between_its_layers(tile):
+    """The second layer's input is plane-major: values about 2^-124 there, made again by fp32 products.  The operator is the
+    identity (no offsets, a scalar of one on the middle tap).  Bound: both layers' sums, the first one's errors all adding up."""
+    dcn.dcnv4_set_option("linear_tile", tile)
+    N, H, W, C, G = 2, 13, 21, 320, 10
+    g = torch.Generator().manual_seed(10)
+    x = torch.randn(N, H, W, C, generator=g) * 2.0 ** -60
+    w_in, w_out = (torch.randn(C, C, generator=g) * 2.0 ** e / C ** 0.5 for e in (-64, 100))
+    w_om, b_om = torch.zeros(G * 32, C), torch.zeros(G, 32)
+    b_om[:, 18 + 4] = 1.0
+    zero = torch.zeros(C).cuda()
+    y = dcn.dcnv4_module_forward(x.cuda(), w_om.cuda(), b_om.reshape(-1).cuda(), G, w_in=w_in.cuda(), b_in=zero, w_out=w_out.cuda(), b_out=zero)
+    xd, wi, wo = x.double().reshape(-1, C), w_in.double(), w_out.double()
+    v = xd @ wi.T
+    ref = v @ wo.T
+    sums = 2.0 ** -24 * C ** 0.5
+    first = sums * xd.norm(dim=1)[:, None] * wi.norm(dim=1)[None, :] + C ** 0.5 * 2.0 ** -149
+    lim = first @ wo.abs().T + sums * v.norm(dim=1)[:, None] * wo.norm(dim=1)[None, :]
+    err = (y.double().cpu().reshape(-1, C) - ref).abs()
+    assert (err <= lim).all(), (err / lim).max()                             # (with the operands left split: up to 9 times the bound)
