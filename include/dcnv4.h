@@ -277,7 +277,9 @@ long long dcnv4_backward_merged_algorithmic_bytes(int N, int H, int W, int G, in
 int dcnv4_set_option(const char *key, int value);
 
 /* Name of the kernel that the most recent dcnv4_forward (backward = 0) or dcnv4_backward
- * (backward = 1) call launched, as it appears in a profiler's kernel trace.  Static storage;
+ * (backward = 1) call launched, as it appears in a profiler's kernel trace; two kernels with " + " between
+ * them, and "(owned)" before a grad_x kernel whose workgroups have whole planes to themselves, "(owned,
+ * uncleared)" where no other kernel has cleared grad_x for it.  Static storage;
  * NULL before the first such call. */
 const char *dcnv4_last_kernel_name(int backward);
 

@@ -538,7 +538,7 @@ struct Options {
     int module_rows = 0;   // 1: the module keeps its tensors channel-last between the layers (default: plane-major)
 } g_opt;
 
-char g_last_kernel[2][96];
+char g_last_kernel[2][128];
 
 FastDiv make_div(unsigned d)
 {
@@ -1847,8 +1847,8 @@ int run_gx(const GxLaunch &l, const void *off, const void *msk, const void *gy, 
     hipLaunchKernelGGL(kern, dim3(l.grid), dim3((unsigned)l.waves * 64), l.lds, s, (const T *)off, (const T *)msk, (const T *)gy,
                        (T *)gx, l.p);
     const size_t had = strlen(g_last_kernel[1]);             // (the grad_offset/grad_mask pass, launched just before)
-    snprintf(g_last_kernel[1] + had, sizeof(g_last_kernel[1]) - had, " + dcnv4_gradx_kernel<%s, %d>",
-             sizeof(T) == 2 ? "_Float16" : "float", l.waves);
+    snprintf(g_last_kernel[1] + had, sizeof(g_last_kernel[1]) - had, " + %sdcnv4_gradx_kernel<%s, %d>",
+             l.p.fresh ? "(owned, uncleared) " : l.p.owned ? "(owned) " : "", sizeof(T) == 2 ? "_Float16" : "float", l.waves);
     return hipGetLastError() == hipSuccess ? DCNV4_OK : DCNV4_ERR_LAUNCH;
 }
 

@@ -472,18 +472,25 @@ def test_runs_on_a_side_stream():
     close("stream/y", y.cpu().numpy(), ref, TOL["f16"])
 
 
+@pytest.mark.parametrize("opts", [{}, {"bwd_path": 2, "gx_own": 1}, {"bwd_path": 2, "gx_own": 1, "halo": 1, "lds_kb": 40}],
+                         ids=["default", "owned", "owned_bands"])
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
-def test_non_finite_upstream_gradients_propagate_like_in_the_oracle(dtype):
+def test_non_finite_upstream_gradients_propagate_like_in_the_oracle(dtype, opts):
     """A NaN or an infinity in grad_y must reach exactly the gradient entries it reaches in the definition
     (the fixed-point accumulation of grad_x sends such pixels through its fp32 path)."""
     cfg = Config("nonfinite", N=1, H=20, W=24, C=32, G=2)
+    for k, v in opts.items():
+        dcn.dcnv4_set_option(k, v)
     t = make_inputs(cfg, dtype, seed=77)
     t["grad_y"][0, 5, 7, 3] = np.nan
     t["grad_y"][0, 12, 20, 17] = np.inf
     t["grad_y"][0, 18, 2, 30] = -np.inf
     d = to_gpu(t, dtype)
-    gx, go, gm = dcn.dcnv4_backward(d["x"], d["offset"], d["mask"], d["grad_y"])
+    out = tuple(torch.full_like(d[k], 7.0) for k in ("x", "offset", "mask"))
+    gx, go, gm = dcn.dcnv4_backward(d["x"], d["offset"], d["mask"], d["grad_y"], out=out)
     torch.cuda.synchronize()
+    if opts:
+        assert " + (owned" in dcn.dcnv4_last_kernel_name(1), dcn.dcnv4_last_kernel_name(1)
     rgx, rgo, rgm = oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"])
     tol = TOL[dtype]
     got = gx.cpu().numpy().astype(np.float64)
@@ -1108,11 +1115,13 @@ def test_grad_x_tiles(cfg, dtype, opts):
 
 
 # All tiles of an (image, channel run) by one workgroup, which stores its sums: bands that overlap, taps past the halo and terms
-# too big for the fixed-point sums (both go straight to memory, before and after the stores), tiles split in columns (gx_wide120),
-# one-wave workgroups on many small maps.
-GRADX_OWNED = {"bands": ({"gx_own": 1, "halo": 1, "lds_kb": 40}, [c for c in GRADX if c.name != "gx_pad"]),
-               "own_choice": ({}, [Config("gx_planes", N=20, H=28, W=27, C=256, G=16), Config("gx_seven", N=40, H=7, W=9, C=1024, G=64),
+# too big for the fixed-point sums (both go straight to memory, before and after the stores), tiles split in columns (gx_wide120:
+# grad_x is cleared then), bands wholly above and below the image (gx_pad, gx_thin_pad), one-wave workgroups on many small maps.
+GRADX_OWNED = {"bands": ({"gx_own": 1, "halo": 1, "lds_kb": 40}, GRADX + [Config("gx_tall", N=2, H=90, W=9, C=32, G=2, sigma=4.0),
+                                                                          Config("gx_thin_pad", N=2, H=60, W=3, C=32, G=2, pad=12, sigma=4.0)]),
+               "own_choice": ({}, [Config("gx_planes", N=32, H=28, W=27, C=256, G=16), Config("gx_seven", N=40, H=7, W=9, C=1024, G=64),
                                    Config("gx_two_bands", N=16, H=50, W=60, C=256, G=16)])}
+GRADX_CLEARED = ("gx_odd", "gx_s2", "gx_d2", "gx_wide32", "gx_wide64", "gx_wide120", "gx_pad")
 
 
 @pytest.mark.parametrize("opts,cfg", [(o, c) for o, (_, cs) in GRADX_OWNED.items() for c in cs], ids=lambda v: v if isinstance(v, str) else v.name)
@@ -1126,10 +1135,11 @@ def test_grad_x_planes_of_one_workgroup(opts, cfg, dtype):
     dcn.dcnv4_set_option("bwd_path", 2)
     for k, v in GRADX_OWNED[opts][0].items():
         dcn.dcnv4_set_option(k, v)
-    out = tuple(torch.full_like(d[k], 7.0) for k in ("x", "offset", "mask"))      # (grad_x is not cleared by another pass here)
+    out = tuple(torch.full_like(d[k], 7.0) for k in ("x", "offset", "mask"))
     gx = dcn.dcnv4_backward(d["x"], d["offset"], d["mask"], d["grad_y"], out=out, **geo_kw(cfg))[0]
     torch.cuda.synchronize()
-    assert "dcnv4_gradx_kernel" in dcn.dcnv4_last_kernel_name(1)
+    how = "(owned) " if cfg.name in GRADX_CLEARED else "(owned, uncleared) "
+    assert f" + {how}dcnv4_gradx_kernel<" in dcn.dcnv4_last_kernel_name(1), dcn.dcnv4_last_kernel_name(1)
     if cfg.name == "gx_seven":
         assert dcn.dcnv4_last_kernel_name(1).endswith(", 1>")
     rgx = oracle.backward(t["x"], t["offset"], t["mask"], t["grad_y"], **geo_kw(cfg))[0]
@@ -1146,12 +1156,12 @@ def test_grad_x_planes_of_one_workgroup(opts, cfg, dtype):
 
 @pytest.mark.parametrize("cfg", [Config("gw_49", N=40, H=7, W=7, C=512, G=32, sigma=3.0), Config("gw_49_32", N=40, H=7, W=7, C=1024, G=32),
                                  Config("gw_49_8", N=40, H=7, W=7, C=256, G=32), Config("gw_1", N=300, H=1, W=1, C=32, G=2)], ids=lambda c: c.name)
-@pytest.mark.parametrize("merged", [False, True])
-def test_backward_of_many_tiny_images_in_one_wave_workgroups(cfg, merged):
+@pytest.mark.parametrize("form", ["separate", "merged", "softmax"])
+def test_backward_of_many_tiny_images_in_one_wave_workgroups(cfg, form):
     """grad_offset/grad_mask of images of one batch that no strip takes, by one-wave workgroups."""
     t = make_inputs(cfg, "f16", seed=14)
     dcn.dcnv4_set_option("fwd_strip", 2)
-    if merged:
+    if form == "merged":
         d = to_gpu(t, "f16")
         om = torch.from_numpy(merge_offset_mask(t["offset"], t["mask"], pad_value=5.0)).to("cuda")
         gom = dcn.dcnv4_backward_merged(d["x"], om, d["grad_y"], **geo_kw(cfg))[1].cpu().numpy()
@@ -1159,9 +1169,15 @@ def test_backward_of_many_tiny_images_in_one_wave_workgroups(cfg, merged):
         close(f"{cfg.name}/grad_offset", gom[..., :18], rgo.reshape(*gom.shape[:-1], 18), TOL["f16"])
         close(f"{cfg.name}/grad_mask", gom[..., 18:27], rgm, TOL["f16"])
         assert not gom[..., 27:].any()
+    elif form == "softmax":
+        d = to_gpu(t, "f16")
+        got = dcn.dcnv4_backward_softmax(d["x"], d["offset"], d["mask"], d["grad_y"], **geo_kw(cfg))
+        refs = oracle.backward_softmax(t["x"], t["offset"], t["mask"], t["grad_y"], **geo_kw(cfg))
+        for name, g, ref in zip(("grad_x", "grad_offset", "grad_mask"), got, refs):
+            close(f"{cfg.name}/softmax/{name}", g.cpu().numpy(), ref, TOL["f16"])
     else:
         check_backward(cfg, dtype="f16", inputs=t)
-    if cfg.C // cfg.G > 8:                                # (groups of 8: the name of the grad_x pass replaces it)
+    if cfg.C // cfg.G > 8 and form != "softmax":          # (groups of 8, softmax: the name of the grad_x pass replaces it)
         assert f"dcnv4_tiled_kernel<_Float16, {cfg.C // cfg.G}, 64, 1>" in dcn.dcnv4_last_kernel_name(1)
 
 
