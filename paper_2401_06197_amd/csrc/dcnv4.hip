@@ -1038,10 +1038,15 @@ int choose_fwd_tiled(const Problem &q, RectForward *out)
 }
 
 // fp16 groups of 64 on small maps, more of them than half the compute units: the direct kernel where rectangles would go through
-// them in slices (64 images, us: 14x14x512 18 and 24, 20x20x256 19 and 22; 29 random calls 0.46 to 0.91 times as long), and before
-// strips up to 45 batches a unit (13 calls by strips 0.97 to 1.35 times as long; 10 of more batches 0.89 to 1.06 times: 35 of 15x25,
-// 32 groups, 67 us by strips and 75).
-long long wide_batches(const Problem &q) { return (long long)q.N * q.G * 2 * (((long long)q.Ho * q.Wo + 63) / 64); }
+// them in slices (64 images, us: 14x14x512 18 and 24, 20x20x256 19 and 22; 29 random calls 0.46 to 0.91 times as long), and, up to
+// so many batches a unit, where strips would.  Direct kernel against strips, on inputs in no cache: 17 to 26 batches 0.83 to 1.10
+// times as long, 31 to 41 1.06 to 1.23 times (219 of 17x22, 4 groups: 71 us and 58); on the same inputs again and again 17 to 45
+// batches 0.74 to 1.03 times (most on maps below 200 pixels), 45 to 77 batches 0.94 to 1.13 times.
+bool few_wide_batches(const Problem &q)
+{
+    const long long px = (long long)q.Ho * q.Wo;
+    return (long long)q.N * q.G * 2 * ((px + 63) / 64) < (px < 200 ? 45LL : 30LL) * device_cus();
+}
 template <typename T> bool direct_for_wide_groups(const Problem &q)
 {
     return sizeof(T) == 2 && q.Cg == 64 && (long long)q.Ho * q.Wo <= 512 && q.sh == 1 && q.sw == 1 && 2LL * q.N * q.G > device_cus() &&
@@ -1061,7 +1066,7 @@ int choose_fwd_tiled_cg(const Problem &q, RectForward *out)
         if constexpr (sizeof(T) == 2) {
             // (rectangles that the strips are compared with: not launched themselves)
             if (direct_for_wide_groups<T>(q))
-                return wide_batches(q) < 45LL * device_cus() ? DCNV4_ERR_UNSUPPORTED : prepare_fwd_tiled<T, kWidest, 512>(q, out);
+                return few_wide_batches(q) ? DCNV4_ERR_UNSUPPORTED : prepare_fwd_tiled<T, kWidest, 512>(q, out);
         }
         if (q.Cg <= kWidest)
             return choose_fwd_tiled<T, 32>(q, out);
