@@ -1618,31 +1618,38 @@ double gx_time(const Problem &q, int waves, int per_cu, int slices, int cus, int
     return (double)(ceil_div(blocks, slots) * (owned ? tiles_img : 1)) * ((1800.0 * ((most + 3) / 4) + 960.0 * most) * (simd + 4.5) + flush);
 }
 
-// Tile choice: output rows per band x columns per tile whose cells fit the LDS, by an estimate of the time (in
-// clocks) of the busiest compute unit, `per_cu` workgroups of `waves` waves on each.  Returns false where no tile fits.
-bool choose_gx_tile(const Problem &q, int waves, int per_cu, int halo, int max_halo, int lds_bytes, int slices, int cus, bool owned,
-                    GxGeo *p, double *cost_out)
+struct GxTile {
+    int R, Q, pitch, tiles_q, tiles_per_img;
+    int waves, per_cu, lds;
+    double cost;
+};
+
+// Rows (columns) the largest rectangle of a split into parts of `len` outputs can have; `border`: cells kept
+// outside the image on each side.  Columns need one more cell unless every tile goes from border to border.
+long long gx_extent(int out, int len, int size, int s, int pad, int dil, int h, int border, bool columns)
 {
-    const int max_cells = (lds_bytes - kGxCell - 16) / (kGxCell + 4) - 2;
+    const long long parts = ((long long)out + len - 1) / len, span = (long long)(len - 1) * s + 2LL * dil + 2LL * h + 2;
+    if (parts > 8)                                     // (many parts: those inside are not clipped)
+        return (span < size + 2 * border ? span : size + 2 * border) + (columns ? 1 : 0);
+    long long most = 0;
+    for (long long k = 0; k < parts; ++k) {
+        const long long o0 = k * len, n = out - o0 < len ? out - o0 : len;
+        const long long want = o0 * s - pad - h, end = (o0 + n - 1) * s - pad + 2LL * dil + h + 2;
+        const long long lo = want > -border ? want : -border, hi = end < size + border ? end : size + border;
+        const long long e = (hi - lo > 0 ? hi - lo : 0) + (columns && !(want <= -border && end >= size + border) ? 1 : 0);
+        if (e > most) most = e;
+    }
+    return most;
+}
+int gx_max_cells(int lds_bytes) { return (lds_bytes - kGxCell - 16) / (kGxCell + 4) - 2; }
+
+// Tile choice: output rows per band x columns per tile whose cells fit the LDS, by an estimate of the time (in
+// clocks) of the busiest compute unit, `per_cu` workgroups of `waves` waves on each; for tiles handed out one by one and for
+// owned planes in one search (either may be null), each kept where it is better than what is there.
+void choose_gx_tiles(const Problem &q, int waves, int per_cu, int halo, int lds_bytes, int slices, int cus, GxTile *any, GxTile *own)
+{
+    const int max_cells = gx_max_cells(lds_bytes);
     auto ceil_div = [](long long a, long long b) { return (a + b - 1) / b; };
-    // Rows (columns) the largest rectangle of a split into parts of `len` outputs can have; `border`: cells kept
-    // outside the image on each side.  Columns need one more cell unless every tile goes from border to border.
-    auto extent = [&](int out, int len, int size, int s, int pad, int dil, int h, int border, bool columns) {
-        const long long parts = ceil_div(out, len), span = (long long)(len - 1) * s + 2LL * dil + 2LL * h + 2;
-        if (parts > 8)                                     // (many parts: those inside are not clipped)
-            return (span < size + 2 * border ? span : size + 2 * border) + (columns ? 1 : 0);
-        long long most = 0;
-        for (long long k = 0; k < parts; ++k) {
-            const long long o0 = k * len, n = out - o0 < len ? out - o0 : len;
-            const long long want = o0 * s - pad - h, end = (o0 + n - 1) * s - pad + 2LL * dil + h + 2;
-            const long long lo = want > -border ? want : -border, hi = end < size + border ? end : size + border;
-            const long long e = (hi - lo > 0 ? hi - lo : 0) + (columns && !(want <= -border && end >= size + border) ? 1 : 0);
-            if (e > most) most = e;
-        }
-        return most;
-    };
-    double best = 1e30;
-    bool found = false;
     // the band heights, with their rectangles' rows
     struct {
         int R;
@@ -1652,14 +1659,14 @@ bool choose_gx_tile(const Problem &q, int waves, int per_cu, int halo, int max_h
     for (int bands = 1; bands <= q.Ho && bands <= 256 && nheights < 128; bands += bands < 32 ? 1 : bands / 16) {
         const int R = (int)ceil_div(q.Ho, bands);
         if (nheights == 0 || R != heights[nheights - 1].R)
-            heights[nheights++] = {R, extent(q.Ho, R, q.H, q.sh, q.ph, q.dh, halo, 2, false)};
+            heights[nheights++] = {R, gx_extent(q.Ho, R, q.H, q.sh, q.ph, q.dh, halo, 2, false)};
     }
     int splits = 0;
     for (int kq = 1; kq <= q.Wo && splits < 12; ++kq) {
         const int Q = (int)ceil_div(q.Wo, kq);
         if (kq > 1 && Q == (int)ceil_div(q.Wo, kq - 1))
             continue;
-        const long long cols = extent(q.Wo, Q, q.W, q.sw, q.pw, q.dw, halo, 1, true);
+        const long long cols = gx_extent(q.Wo, Q, q.W, q.sw, q.pw, q.dw, halo, 1, true);
         if (cols < 1 || cols > max_cells)
             continue;
         const int tiles_q = (int)ceil_div(q.Wo, Q);
@@ -1671,49 +1678,95 @@ bool choose_gx_tile(const Problem &q, int waves, int per_cu, int halo, int max_h
                 continue;
             fits = true;
             const int bands = (int)ceil_div(q.Ho, R);
-            const long long tiles = (long long)q.N * q.G * slices * bands * tiles_q;
-            const int units = (int)ceil_div(R * ceil_div(Q, 4), 4);
-            double cost;
-            if (owned) {
-                cost = gx_time(q, waves, per_cu, slices, cus, R, Q, (long long)bands * tiles_q, rows * cols, true);
-            } else {
+            auto keep = [&](GxTile *t, double cost) {
+                if (cost < t->cost)
+                    *t = {R, Q, (int)cols, tiles_q, bands * tiles_q, waves, per_cu, lds_bytes, cost};
+            };
+            if (own != nullptr)
+                keep(own, gx_time(q, waves, per_cu, slices, cus, R, Q, (long long)bands * tiles_q, rows * cols, true));
+            if (any != nullptr) {
                 // the wave with the most units of 16 pixels: per batch of up to four of them the evaluation, per unit the
                 // adds, shared with the other waves of its SIMD; then the flush, which the workgroups of a unit share as
                 // well, and the drained pipeline at the tile's end
-                const int most = (units + waves - 1) / waves;
+                const long long tiles = (long long)q.N * q.G * slices * bands * tiles_q;
+                const int units = (int)ceil_div(R * ceil_div(Q, 4), 4), most = (units + waves - 1) / waves;
                 const long long slots = (long long)cus * per_cu;
                 const double resident = tiles < slots ? (double)ceil_div(tiles, cus) : (double)per_cu;
                 const double simd = resident * (waves < units ? waves : units) / 4.0;
                 const double batches = (simd > 1.0 ? simd : 1.0) * (2900.0 * ((most + 3) / 4) + 1200.0 * most);
-                cost = (double)ceil_div(tiles, slots) * (batches + 9.0 * resident * (double)(rows * cols) + 5000.0);
-            }
-            if (cost < best) {
-                best = cost;
-                found = true;
-                p->R = R;
-                p->Q = Q;
-                p->pitch = (int)cols;
-                p->tiles_q = tiles_q;
-                p->tiles_per_img = bands * tiles_q;
+                keep(any, (double)ceil_div(tiles, slots) * (batches + 9.0 * resident * (double)(rows * cols) + 5000.0));
             }
         }
         if (fits)
             ++splits;
     }
-    *cost_out = best;
-    if (!found)
-        return false;
-    // what is left of the LDS allows for larger displacements
+}
+
+// A tile into the geometry; what is left of the LDS allows for larger displacements.
+void set_gx_tile(const Problem &q, const GxTile &t, int halo, int max_halo, GxGeo *p)
+{
+    p->R = t.R;
+    p->Q = t.Q;
+    p->pitch = t.pitch;
+    p->tiles_q = t.tiles_q;
+    p->tiles_per_img = t.tiles_per_img;
     p->halo = halo;
     for (int h = halo; h <= max_halo; ++h) {
-        const long long rows = extent(q.Ho, p->R, q.H, q.sh, q.ph, q.dh, h, 2, false);
-        const long long cols = extent(q.Wo, p->Q, q.W, q.sw, q.pw, q.dw, h, 1, true);
-        if (rows * cols > max_cells)
+        const long long rows = gx_extent(q.Ho, t.R, q.H, q.sh, q.ph, q.dh, h, 2, false);
+        const long long cols = gx_extent(q.Wo, t.Q, q.W, q.sw, q.pw, q.dw, h, 1, true);
+        if (rows * cols > gx_max_cells(t.lds))
             break;
         p->halo = h;
         p->pitch = (int)cols;
         // (at least a row: taps that stay out of the cells book on the corners of cell 0)
         p->cells = (int)((rows > 1 ? rows : 1) * cols) + 2;
+    }
+}
+
+// Tiles, workgroup and ownership of a call; false where no tile fits.
+bool choose_gx(const Problem &q, int slices, int cus, GxGeo *p, GxTile *pick)
+{
+    const int halo = g_opt.halo ? g_opt.halo : kDefaultHaloGradX, max_halo = g_opt.halo ? halo : kMaxHaloGradX;
+    // Twelve waves per compute unit either way, in one workgroup or, where that makes small tiles, in three, whose
+    // flushes and tile switches overlap and whose waves get whole batches (14x14x512, 32 groups, batch 64, fp32: 106 us
+    // in one, 59 in three; two of six waves do not fit a unit's SIMDs together: 28x28x256 fp16 115 -> 150)
+    struct {
+        int waves, per_cu;
+    } shapes[3] = {{12, 1}, {4, 3}, {1, 12}};
+    const int nshapes = g_opt.gx_threads ? 1 : 3;
+    if (g_opt.gx_threads)
+        shapes[0].waves = g_opt.gx_threads / 64;
+    const long long planes = (long long)q.N * q.G * slices;
+    const bool may_own = g_opt.gx_own == 0 && planes >= cus;
+    GxTile any = {}, own = {};
+    any.cost = own.cost = 1e30;
+    for (int i = 0; i < nshapes; ++i) {
+        // (one wave: maps of one or two batches, many of them)
+        const bool one_wave = shapes[i].waves == 1;
+        if (one_wave && (!may_own || (long long)q.Ho * q.Wo > 128))
+            continue;
+        const int lds = (g_opt.lds_kb ? g_opt.lds_kb * 1024 : kMaxLdsBytes) / shapes[i].per_cu & ~1023;
+        choose_gx_tiles(q, shapes[i].waves, shapes[i].per_cu, halo, lds, slices, cus, one_wave ? nullptr : &any, may_own ? &own : nullptr);
+    }
+    if (any.waves == 0)
+        return false;
+    set_gx_tile(q, any, halo, max_halo, p);
+    *pick = any;
+    p->owned = 0;
+    // An (image, channel run) to one workgroup, which then stores its sums instead of adding them atomically, where that is
+    // faster in these tiles, or clearly so in others.
+    if (g_opt.gx_own == 1) {
+        p->owned = p->tiles_per_img;
+    } else if (may_own) {
+        auto now = [&](bool owned) { return gx_time(q, any.waves, any.per_cu, slices, cus, p->R, p->Q, p->tiles_per_img, p->cells, owned); };
+        const double one_by_one = now(false), owned = now(true);
+        if (own.cost < 0.85 * (owned < one_by_one ? owned : one_by_one)) {
+            set_gx_tile(q, own, halo, max_halo, p);
+            *pick = own;
+            p->owned = p->tiles_per_img;
+        } else if (owned < one_by_one) {
+            p->owned = p->tiles_per_img;
+        }
     }
     return true;
 }
@@ -1740,55 +1793,10 @@ int prepare_gx(const Problem &q, GxLaunch *out)
     if (cus <= 0)
         return DCNV4_ERR_LAUNCH;
     p.slices = q.Cg / kGxChan;
-    const int halo = g_opt.halo ? g_opt.halo : kDefaultHaloGradX, max_halo = g_opt.halo ? halo : kMaxHaloGradX;
-    // Twelve waves per compute unit either way, in one workgroup or, where that makes small tiles, in three, whose
-    // flushes and tile switches overlap and whose waves get whole batches (14x14x512, 32 groups, batch 64, fp32: 106 us
-    // in one, 59 in three; two of six waves do not fit a unit's SIMDs together: 28x28x256 fp16 115 -> 150)
-    struct {
-        int waves, per_cu;
-    } shapes[3] = {{12, 1}, {4, 3}, {1, 12}}, pick = {0, 0};
-    const int nshapes = g_opt.gx_threads ? 1 : 3;
-    if (g_opt.gx_threads)
-        shapes[0].waves = g_opt.gx_threads / 64;
-    const GxGeo common = p;
-    auto choose = [&](bool owned) {                     // (the estimate of what it took)
-        double best = 1e30;
-        for (int i = 0; i < nshapes; ++i) {
-            // (one wave: maps of one or two batches, many of them)
-            if (shapes[i].waves == 1 && (!owned || (long long)q.Ho * q.Wo > 128))
-                continue;
-            GxGeo t = common;
-            double cost = 0;
-            int lds = (g_opt.lds_kb ? g_opt.lds_kb * 1024 : kMaxLdsBytes) / shapes[i].per_cu & ~1023;
-            if (choose_gx_tile(q, shapes[i].waves, shapes[i].per_cu, halo, max_halo, lds, p.slices, cus, owned, &t, &cost) && cost < best) {
-                best = cost;
-                pick = shapes[i];
-                p = t;
-            }
-        }
-        return best;
-    };
-    choose(false);
-    if (pick.waves == 0)
+    GxTile pick;
+    if (!choose_gx(q, p.slices, cus, &p, &pick))
         return DCNV4_ERR_UNSUPPORTED;
-    // An (image, channel run) to one workgroup, which then stores its sums instead of adding them atomically, where that is
-    // faster in these tiles, or clearly so in others.
     const long long planes = (long long)q.N * q.G * p.slices;
-    if (g_opt.gx_own == 1) {
-        p.owned = p.tiles_per_img;
-    } else if (g_opt.gx_own == 0 && planes >= cus) {
-        auto now = [&](bool owned) { return gx_time(q, pick.waves, pick.per_cu, p.slices, cus, p.R, p.Q, p.tiles_per_img, p.cells, owned); };
-        const double any = now(false), own = now(true);
-        const GxGeo first = p;
-        const auto first_shape = pick;
-        if (choose(true) < 0.85 * (own < any ? own : any)) {
-            p.owned = p.tiles_per_img;
-        } else {
-            p = first;
-            pick = first_shape;
-            p.owned = own < any ? p.tiles_per_img : 0;
-        }
-    }
     // Its stores are the first ones where its bands leave no row or column of the image out; grad_x needs no clearing then
     // (103 MB of zeros: 16 us).
     const long long reach = 2LL * q.dh + p.halo + 2;
