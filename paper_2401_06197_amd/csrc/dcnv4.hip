@@ -986,8 +986,16 @@ int choose_fwd_tiled(const Problem &q, RectForward *out)
                     const bool plain = q.sh == 1 && q.sw == 1 && q.dh == 1 && q.dw == 1 && q.ph <= 1 && q.pw <= 1;
                     const bool fewer = px == 128 || (plain && px >= (b > 1 ? 72 : 40) && direct > least);
                     if ((q.merged || q.softmax || (sizeof(T) == 4 && fewer)) && make_tgeo(q, 64, kTiledFwd, &whole, CG, 1) == DCNV4_OK &&
-                        whole.tiles_per_img == 1)
-                        return finish_fwd_tiled<T, CG, 64>(whole, true, 8, out);
+                        whole.tiles_per_img == 1) {
+                        // Where fewer than seven of them fit a unit (strides, dilations): three at least, and two batches an image only
+                        // with tiles enough to overlap, since one wave fills a large rectangle slowly.  us in eight waves and here: 4x29
+                        // outputs at stride 3, 28 images of 16 groups of 16, fp32 15.5 and 29.7 (one fits); 23x5 at stride 2, 110 of 4 groups of
+                        // 32 19.9 and 22.7 (three fit, 3.4 tiles a unit); 10x3 at stride 3, 522 of 4 groups of 32, fp16 49.7 and 18.8 (five).
+                        const int rc = finish_fwd_tiled<T, CG, 64>(whole, true, 8, out);
+                        const int fit = rc == DCNV4_OK ? kMaxLdsBytes / out->l.lds : 8;
+                        if (fit >= 7 || (fit >= 3 && tiles > (b == 1 ? 1LL : fit == 3 ? 4LL : 2LL) * cus))
+                            return rc;
+                    }
                 } else if (make_tgeo(q, 256, kTiledFwd, &whole, CG, 1) == DCNV4_OK && whole.tiles_per_img == 1 &&
                            finish_fwd_tiled<T, CG, 256>(whole, true, 2, out) == DCNV4_OK && 2 * out->l.lds <= kMaxLdsBytes) {
                     // (a last round of four with one wave in it, many times over, is dearer than strips: 30 x 24x24x1024 fp32,

@@ -678,6 +678,16 @@ def test_forward_of_tiny_fp32_images_by_the_direct_kernels_workgroups(cfg, one_w
     assert name == "dcnv4_tiled_kernel<float, 16, 64, 0>" if one_wave else name.startswith("dcnv4_fwd_kernel<"), name
 
 
+@pytest.mark.parametrize("form,cfg", [("softmax", Config("tl_s3", N=28, H=12, W=89, C=256, G=16, stride=3, pad=0)),
+                                      ("merged", Config("tl_s2", N=20, H=45, W=9, C=512, G=16, stride=2))], ids=lambda v: getattr(v, "name", v))
+def test_forward_of_few_outputs_of_a_large_image_keeps_eight_waves(form, cfg):
+    t = make_inputs(cfg, "f32", seed=87)
+    y = forward_in(form, cfg, t, "f32")
+    assert dcn.dcnv4_last_kernel_name(0) == "dcnv4_tiled_kernel<float, 16, 512, 0>"
+    ref = (oracle.forward_softmax if form == "softmax" else oracle.forward)(t["x"], t["offset"], t["mask"], **geo_kw(cfg))
+    close(f"{cfg.name}/{form}", y, ref, TOL["f32"])
+
+
 @pytest.mark.parametrize("cfg,kernel", [(Config("fw_16", N=64, H=14, W=14, C=512, G=8), "dcnv4_fwd_kernel<"),      # 16 batches a unit
                                         (Config("fw_52", N=35, H=15, W=25, C=2048, G=32), "dcnv4_strip_kernel<"),
                                         (Config("fw_65", N=349, H=9, W=16, C=512, G=8), "dcnv4_fwd_kernel<"),         # (strips are slower)
