@@ -966,8 +966,10 @@ int choose_fwd_tiled(const Problem &q, RectForward *out)
             // Whole images of a few batches leave waves of eight idle, and nothing runs beside a refill.  More of them than
             // compute units go to smaller workgroups with one rectangle each: two of four waves a unit, eight of one wave
             // where an image is one or two batches.  us, 64 images: fp32 14x14x512, 16 groups 44 -> 34; 20x20x256 35 -> 30;
-            // 28x28x256 57 (strips) -> 52; fp16 28x28x256, 8 groups 38.5 (strips) -> 34.5; merged fp32 7x7x1024 61 -> 19, fp16 41
-            // -> 13.  (With fewer images: 8 of 28x28x256, 13.3 in eight waves and 15.7 like this.)
+            // 28x28x256 57 (strips) -> 52, on inputs in no cache 58.8 -> 56.9; fp16 28x28x256, 8 groups 40.5 (strips) -> 34.4; merged fp32
+            // 7x7x1024 60 -> 18, fp16 41 -> 13.  (With fewer images: 8 of 28x28x256, 13.3 in eight waves and 15.7 like this.  In place of
+            // rectangles of eight waves 0.70 to 0.96 times as long; in place of strips, 69 random calls, 0.94 times on average, 6 of
+            // them 2 to 9 % longer: 227 of 15x26, 8 groups of 32, fp16 65 -> 71.)
             const long long px = (long long)q.Ho * q.Wo, tiles = (long long)q.N * q.G * (q.Cg / CG);
             const int cus = device_cus();
             if (g_opt.fwd_threads == 0 && g_opt.fwd_path != 1 && cus > 0 && tiles > cus && px <= 16 * 64) {
