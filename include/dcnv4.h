@@ -259,7 +259,7 @@ long long dcnv4_backward_merged_algorithmic_bytes(int N, int H, int W, int G, in
  *                 full module keeps them plane-major, one (image, group) after the other)
  *   "linear_tile" tile of the linear layers, output channels x pixels: 1 = 128x128, 2 = 64x64, 3 = 256x256,
  *                 4 = 128x256 (fp32), 5 = the kernel that reads x once (fp16, K of up to 256 bytes); 0 = the one
- *                 with the lowest estimated time.  A tile that a type or K does not have: DCNV4_ERR_UNSUPPORTED
+ *                 with the lowest estimated time.  In place of a tile that a type or K does not have: 128x128
  *   "gom_coop"    1 = the fp32 grad_offset/grad_mask pass moves its values through per-wave LDS slices
  *                 even for whole groups (default: each lane reads and writes its own pixel's values)
  *   "gx_threads"  workgroup size of the staged grad_x kernel (256, 512 or 768)

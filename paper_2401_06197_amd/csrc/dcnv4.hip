@@ -2219,10 +2219,7 @@ int begin_linear(LinGeo *g, const void *x, long long P, int K, int dtype)
 
 int launch_linear(const void *x, const LinGeo &g, int dtype, hipStream_t s)
 {
-    const int shape = g_opt.linear_tile != 0 ? g_opt.linear_tile : pick_linear_tile(g, dtype);
-    // (asked for by option: a tile that the type, or K, does not have)
-    if (dtype == DCNV4_F16 ? shape == kLinear128x256 || (shape == kLinearInOneChunk && g.kbytes > kLinChunk) : shape == kLinearInOneChunk)
-        return DCNV4_ERR_UNSUPPORTED;
+    const int shape = g_opt.linear_tile != 0 ? linear_tile_asked(g_opt.linear_tile, g.kbytes, dtype == DCNV4_F16) : pick_linear_tile(g, dtype);
     if (shape != kLinearInOneChunk)
         return dtype == DCNV4_F16 ? launch_linear_shape<_Float16>(shape, x, g, s) : launch_linear_shape<float>(shape, x, g, s);
     const int tiles = (g.P + kLinPixels - 1) / kLinPixels;

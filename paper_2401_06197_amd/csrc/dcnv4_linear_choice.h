@@ -6,6 +6,13 @@
 constexpr int kLinChunk = 256;         // bytes of K that the kernel of one chunk takes at most (16 units of 16 bytes)
 enum { kLinear128x128 = 1, kLinear64x64 = 2, kLinear256x256 = 3, kLinear128x256 = 4, kLinearInOneChunk = 5 };
 
+// The tile that an option asks for; in place of one that the type, or K, does not have: 128x128.
+inline int linear_tile_asked(int shape, int kbytes, bool f16)
+{
+    const bool there = f16 ? shape != kLinear128x256 && (shape != kLinearInOneChunk || kbytes <= kLinChunk) : shape != kLinearInOneChunk;
+    return there ? shape : kLinear128x128;
+}
+
 // The tile with the lowest estimated time (us).  A compute unit works through its share of the tiles one after the other or,
 // `slots` of them, side by side, where half the difference between the fullest unit and the mean is felt, and a part (`gen`) of
 // the idle slots of the last round.  A tile takes `step` for 128 (fp16) or 64 (fp32) bytes of K, a lone one `alone` at least, and

@@ -256,30 +256,16 @@ def test_linear_fp32_small_numbers_keep_their_bits(K, ex, ew):
     assert ((y - ref).abs() <= lim).all(), ((y - ref).abs() / lim).max()
 
 
-TILES = [(1, "f32"), (2, "f32"), (3, "f32"), (4, "f32"), (1, "f16"), (2, "f16"), (3, "f16"), (5, "f16")]      # (5: K up to 256 bytes)
-
-
-@pytest.mark.parametrize("tile,dtype", TILES)
+@pytest.mark.parametrize("tile", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
 def test_linear_tiles(tile, dtype):
     """Every tile at its edges: one pixel, a pixel less and more than a tile, runs of channels cut short, K of one unit,
     of less than a step, of steps and a part; and the module, whose first launch has two layers and plane-major results."""
     for P, K, Nout in [(1, 16, 32), (63, 48, 96), (65, 64, 160), (255, 144, 64), (257, 208, 288), (130, 528, 128), (513, 96, 544)]:
         dcn.dcnv4_set_option("linear_tile", tile)
-        if tile == 5 and K > 128:
-            with pytest.raises(dcn.Dcnv4Error):                              # a tile that there is not is refused, not replaced
-                test_linear_layer_matches_oracle(P, K, Nout, dtype)
-        else:
-            test_linear_layer_matches_oracle(P, K, Nout, dtype)
-    for cfg in (MODULE_CASES[3], MODULE_CASES[6]) + (() if tile == 5 else (Config("m_two", N=2, H=9, W=11, C=192, G=6),)):
+        test_linear_layer_matches_oracle(P, K, Nout, dtype)
+    for cfg in (MODULE_CASES[3], MODULE_CASES[6], Config("m_two", N=2, H=9, W=11, C=192, G=6)):
         run_module(cfg, dtype, lightweight=False)
-
-
-@pytest.mark.parametrize("tile,dtype", [(4, "f16"), (5, "f32")])
-def test_linear_tiles_that_a_type_does_not_have_are_refused(tile, dtype):
-    dcn.dcnv4_set_option("linear_tile", tile)
-    with pytest.raises(dcn.Dcnv4Error) as e:
-        test_linear_layer_matches_oracle(64, 64, 64, dtype)
-    assert e.value.status == 3
 
 
 @pytest.mark.parametrize("tile", [1, 2, 3, 4])

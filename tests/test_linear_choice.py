@@ -20,8 +20,8 @@ PICK = r"""
 int main()
 {
     int f16, P, kbytes, nseg, nout[2];
-    while (scanf("%d %d %d %d %d %d", &f16, &P, &kbytes, &nseg, nout, nout + 1) == 6)
-        printf("%d\n", linear_tile_choice(P, kbytes, nout, nseg, f16 != 0, 256));
+    while (scanf("%d %d %d %d %d %d", &f16, &P, &kbytes, &nseg, nout, nout + 1) == 6)      // (no output channels: P is the tile asked for)
+        printf("%d\n", nout[0] ? linear_tile_choice(P, kbytes, nout, nseg, f16 != 0, 256) : linear_tile_asked(P, kbytes, f16 != 0));
     return 0;
 }
 """
@@ -46,3 +46,8 @@ def test_fp16_layers_and_pairs_of_layers(tmp_path):
     """K in one chunk: 64x64 tiles for few pixels, else the kernel that reads x once; longer K by the estimates; two layers' channels count together."""
     assert picks(tmp_path, [(True, 200704, 256, [128]), (True, 196, 256, [64]), (True, 1000, 2048, [1024]), (True, 12544, 1024, [1024]),
                             (True, 12544, 1024, [512, 512]), (False, 12544, 2048, [1024]), (False, 12544, 2048, [512, 512])]) == [5, 2, 2, 3, 3, 3, 3]
+
+
+def test_tiles_asked_for_that_a_type_or_k_does_not_have_are_128x128(tmp_path):
+    asked = [(f16, tile, kbytes, [0]) for f16, kbytes in ((False, 256), (True, 256), (True, 272)) for tile in (1, 2, 3, 4, 5)]
+    assert picks(tmp_path, asked) == [1, 2, 3, 4, 1, 1, 2, 3, 1, 5, 1, 2, 3, 1, 1]
