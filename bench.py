@@ -226,7 +226,7 @@ def run_module_leg(torch, dcn, lib, stream, cfg, leg, a, steps):
             raise dcn.Dcnv4Error(rc, leg)
     torch.cuda.synchronize()
     t = time_leg(torch, stream, launch, nsets, steps, a.warmup, a.cold_only)
-    rec = {"workload": cfg.name, "kernel": "dcnv4_linear_kernel + " + str(dcn.dcnv4_last_kernel_name(0)), "steps": steps,
+    rec = {"workload": cfg.name, "kernel": "linear layers + " + str(dcn.dcnv4_last_kernel_name(0)), "steps": steps,
            "us_per_launch": round(t["cold"] * 1e3, 3), "out_elems_per_s": P * cfg.C / (t["cold"] * 1e-3),
            "moved_bytes": moved, "GBps": moved / (t["cold"] * 1e-3) / 1e9,
            "frac_of_hbm_peak": moved / (t["cold"] * 1e-3) / 1e9 / HBM_PEAK_GBS,
