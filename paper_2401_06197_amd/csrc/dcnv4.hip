@@ -47,6 +47,13 @@ __device__ __forceinline__ int fdiv(int n, FastDiv f)
     return (int)((__umulhi((unsigned)n, f.mul) + (unsigned)n) >> f.shift);
 }
 
+typedef const __attribute__((address_space(4))) FastDiv ArgDiv;        // in the kernel's arguments
+__device__ __forceinline__ int arg_div(int n, ArgDiv &f)
+{
+    return fdiv(n, FastDiv{f.mul, f.shift});
+}
+__device__ __forceinline__ int arg_div(int n, const FastDiv &f) { return fdiv(n, f); }
+
 struct Geo {
     int H, W, Ho, Wo, G;
     int sh, sw, ph, pw, dh, dw;
