@@ -87,6 +87,8 @@ def load_library():
 
 
 def _pair(v):
+    if type(v) is int:
+        return v, v
     return (int(v), int(v)) if isinstance(v, int) else (int(v[0]), int(v[1]))
 
 
@@ -132,11 +134,12 @@ def dcnv4_backward_merged_algorithmic_bytes(N, H, W, G, Cg, Ho, Wo, dtype):
 
 def _dtype_code(t):
     import torch
-    if t.dtype == torch.float32:
+    dt = t.dtype
+    if dt is torch.float32:
         return DCNV4_F32
-    if t.dtype == torch.float16:
+    if dt is torch.float16:
         return DCNV4_F16
-    raise TypeError(f"dcnv4: unsupported tensor dtype {t.dtype}")
+    raise TypeError(f"dcnv4: unsupported tensor dtype {dt}")
 
 
 def _check(name, t, ref):
@@ -148,11 +151,23 @@ def _check(name, t, ref):
         raise ValueError(f"dcnv4: {name} must share dtype and device with x")
 
 
+def _check_all(x, named):
+    """_check of x and of each (name, tensor), whose messages are only made where one does not pass.  (A small call is bound by
+    this module: forward and backward of 1x14x14x64 took 36 us, 21 of them here.)"""
+    at, dt = x.get_device(), x.dtype
+    if at < 0 or not x.is_cuda or not x.is_contiguous():
+        _check("x", x, x)
+    for name, t in named:
+        if t.get_device() != at or t.dtype is not dt or not t.is_contiguous():
+            _check(name, t, x)
+
+
 def _stream_ptr(stream, device):
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream(device)
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # (the handle itself: a Stream object around it takes 1.9 us)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if device.index is None else device.index)
 
 
 def _call(device, entry, args):
@@ -184,17 +199,18 @@ def _conv_hw(H, W, kh, kw, sh, sw, ph, pw, dh, dw):
 
 
 def _shape_args(x, offset, mask, kernel, stride, pad, dilation):
-    (kh, kw), (sh, sw), (ph, pw), (dh, dw) = map(_pair, (kernel, stride, pad, dilation))
-    if x.dim() != 4 or offset.dim() != 6 or mask.dim() != 5:
+    (kh, kw), (sh, sw), (ph, pw), (dh, dw) = _pair(kernel), _pair(stride), _pair(pad), _pair(dilation)
+    xshape, oshape, mshape = x.shape, offset.shape, mask.shape
+    if len(xshape) != 4 or len(oshape) != 6 or len(mshape) != 5:
         raise ValueError("dcnv4: expected x [N,H,W,C], offset [N,Ho,Wo,G,K,2], mask [N,Ho,Wo,G,K]")
-    N, H, W, C = x.shape
-    G = mask.shape[3]
+    N, H, W, C = xshape
+    G = mshape[3]
     if G < 1 or C % G:
         raise ValueError("dcnv4: C must be a multiple of G")
     Ho, Wo = _conv_hw(H, W, kh, kw, sh, sw, ph, pw, dh, dw)
     K = kh * kw
-    if tuple(mask.shape) != (N, Ho, Wo, G, K) or tuple(offset.shape) != (N, Ho, Wo, G, K, 2):
-        raise ValueError(f"dcnv4: offset/mask shapes {tuple(offset.shape)}/{tuple(mask.shape)} do not match "
+    if mshape != (N, Ho, Wo, G, K) or oshape != (N, Ho, Wo, G, K, 2):
+        raise ValueError(f"dcnv4: offset/mask shapes {tuple(oshape)}/{tuple(mshape)} do not match "
                          f"N={N} Ho={Ho} Wo={Wo} G={G} K={K}")
     return (N, H, W, G, C // G, kh, kw, sh, sw, ph, pw, dh, dw), (N, Ho, Wo, C)
 
@@ -207,10 +223,9 @@ def dcnv4_forward(x, offset, mask, kernel=3, stride=1, pad=1, dilation=1, offset
     instead of launching (for launch loops that must not pay the checks every time)."""
     import torch
     geo, yshape = _shape_args(x, offset, mask, kernel, stride, pad, dilation)
-    for name, t in (("x", x), ("offset", offset), ("mask", mask)):
-        _check(name, t, x)
+    _check_all(x, (("offset", offset), ("mask", mask)))
     if out is None:
-        out = torch.empty(yshape, dtype=x.dtype, device=x.device)
+        out = x.new_empty(yshape)
     else:
         _check("out", out, x)
         if tuple(out.shape) != yshape:
@@ -238,17 +253,17 @@ def dcnv4_backward(x, offset, mask, grad_y, kernel=3, stride=1, pad=1, dilation=
     """(grad_x, grad_offset, grad_mask) of dcnv4_forward for upstream gradient grad_y."""
     import torch
     geo, yshape = _shape_args(x, offset, mask, kernel, stride, pad, dilation)
-    for name, t in (("x", x), ("offset", offset), ("mask", mask), ("grad_y", grad_y)):
-        _check(name, t, x)
-    if tuple(grad_y.shape) != yshape:
+    _check_all(x, (("offset", offset), ("mask", mask), ("grad_y", grad_y)))
+    if grad_y.shape != yshape:
         raise ValueError("dcnv4: grad_y has the wrong shape")
     if out is None:
-        out = (torch.empty_like(x), torch.empty_like(offset), torch.empty_like(mask))
-    gx, go, gm = out
-    for name, t, ref in (("grad_x", gx, x), ("grad_offset", go, offset), ("grad_mask", gm, mask)):
-        _check(name, t, x)
-        if t.shape != ref.shape:
-            raise ValueError(f"dcnv4: {name} has the wrong shape")
+        gx, go, gm = torch.empty_like(x), torch.empty_like(offset), torch.empty_like(mask)
+    else:
+        gx, go, gm = out
+        for name, t, ref in (("grad_x", gx, x), ("grad_offset", go, offset), ("grad_mask", gm, mask)):
+            _check(name, t, x)
+            if t.shape != ref.shape:
+                raise ValueError(f"dcnv4: {name} has the wrong shape")
     args = (x.data_ptr(), offset.data_ptr(), mask.data_ptr(), grad_y.data_ptr(),
             gx.data_ptr(), go.data_ptr(), gm.data_ptr(), *geo,
             float(offset_scale), _dtype_code(x), _stream_ptr(stream, x.device))
@@ -259,16 +274,17 @@ def dcnv4_backward(x, offset, mask, grad_y, kernel=3, stride=1, pad=1, dilation=
 
 
 def _merged_shape_args(x, om, kernel, stride, pad, dilation):
-    (kh, kw), (sh, sw), (ph, pw), (dh, dw) = map(_pair, (kernel, stride, pad, dilation))
-    if x.dim() != 4 or om.dim() != 5 or om.shape[4] != 32:
+    (kh, kw), (sh, sw), (ph, pw), (dh, dw) = _pair(kernel), _pair(stride), _pair(pad), _pair(dilation)
+    xshape, oshape = x.shape, om.shape
+    if len(xshape) != 4 or len(oshape) != 5 or oshape[4] != 32:
         raise ValueError("dcnv4: expected x [N,H,W,C] and offset_mask [N,Ho,Wo,G,32]")
-    N, H, W, C = x.shape
-    G = om.shape[3]
+    N, H, W, C = xshape
+    G = oshape[3]
     if G < 1 or C % G:
         raise ValueError("dcnv4: C must be a multiple of G")
     Ho, Wo = _conv_hw(H, W, kh, kw, sh, sw, ph, pw, dh, dw)
-    if tuple(om.shape) != (N, Ho, Wo, G, 32):
-        raise ValueError(f"dcnv4: offset_mask shape {tuple(om.shape)} does not match N={N} Ho={Ho} Wo={Wo} G={G}")
+    if oshape != (N, Ho, Wo, G, 32):
+        raise ValueError(f"dcnv4: offset_mask shape {tuple(oshape)} does not match N={N} Ho={Ho} Wo={Wo} G={G}")
     return (N, H, W, G, C // G, kh, kw, sh, sw, ph, pw, dh, dw), (N, Ho, Wo, C)
 
 
@@ -278,10 +294,9 @@ def dcnv4_forward_merged(x, offset_mask, kernel=3, stride=1, pad=1, dilation=1, 
     values, 5 unused entries per (pixel, group)."""
     import torch
     geo, yshape = _merged_shape_args(x, offset_mask, kernel, stride, pad, dilation)
-    for name, t in (("x", x), ("offset_mask", offset_mask)):
-        _check(name, t, x)
+    _check_all(x, (("offset_mask", offset_mask),))
     if out is None:
-        out = torch.empty(yshape, dtype=x.dtype, device=x.device)
+        out = x.new_empty(yshape)
     else:
         _check("out", out, x)
         if tuple(out.shape) != yshape:
@@ -299,17 +314,17 @@ def dcnv4_backward_merged(x, offset_mask, grad_y, kernel=3, stride=1, pad=1, dil
     """(grad_x, grad_offset_mask) of dcnv4_forward_merged; grad_offset_mask is laid out like offset_mask."""
     import torch
     geo, yshape = _merged_shape_args(x, offset_mask, kernel, stride, pad, dilation)
-    for name, t in (("x", x), ("offset_mask", offset_mask), ("grad_y", grad_y)):
-        _check(name, t, x)
-    if tuple(grad_y.shape) != yshape:
+    _check_all(x, (("offset_mask", offset_mask), ("grad_y", grad_y)))
+    if grad_y.shape != yshape:
         raise ValueError("dcnv4: grad_y has the wrong shape")
     if out is None:
-        out = (torch.empty_like(x), torch.empty_like(offset_mask))
-    gx, gom = out
-    for name, t, ref in (("grad_x", gx, x), ("grad_offset_mask", gom, offset_mask)):
-        _check(name, t, x)
-        if t.shape != ref.shape:
-            raise ValueError(f"dcnv4: {name} has the wrong shape")
+        gx, gom = torch.empty_like(x), torch.empty_like(offset_mask)
+    else:
+        gx, gom = out
+        for name, t, ref in (("grad_x", gx, x), ("grad_offset_mask", gom, offset_mask)):
+            _check(name, t, x)
+            if t.shape != ref.shape:
+                raise ValueError(f"dcnv4: {name} has the wrong shape")
     args = (x.data_ptr(), offset_mask.data_ptr(), grad_y.data_ptr(), gx.data_ptr(), gom.data_ptr(), *geo,
             float(offset_scale), _dtype_code(x), _stream_ptr(stream, x.device))
     if prepare_only:
