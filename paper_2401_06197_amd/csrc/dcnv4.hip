@@ -1282,10 +1282,16 @@ bool strips_win(const Problem &q, const TGeo &r, int rect_waves, const SGeo &p, 
     const float strip = t.strip_whole * (float)((busiest + waves - 1) / waves) +
                         (t.strip_rounds + t.strip_near * near_r) * (float)busiest / waves + t.strip_staged * staged +
                         t.strip_mean * mean + t.strip_once;
+    // (The fit is of strips whose rounds read their arguments piece by piece.  Since then they take less: by 0.89 in fp32 and for
+    // 16-byte pixels, the factor with the fewest misses of 0.84 to 1, where every unit has a tile.  With it, and narrow pixels asked
+    // from 24 batches to a unit on instead of 48, the launched kernel is 2.6 % slower than the better of the two over 500 random
+    // calls, before 3.3 %; the 37 that changed kernels are 9 % faster on average, three of them 5 to 7 % slower, offsets of 4 pixels
+    // among them: fp32 5 x 74x116x256, 8 groups 67.4 -> 70.9 us; 30 x 75x59x80, 5 groups 69.9 -> 75.1.)
+    const float since = (q.dtype == DCNV4_F32 || pb == 16) && p.ntiles >= cus ? 0.89f : 1.f;
     // A margin for windows that allow for small displacements: offsets of 4 pixels cost the strips most there (64-byte pixels in
     // fp32, allowing for 4: 6 % faster than rectangles at offsets of 1 and 2 pixels, 7 % slower at 4).  Over a thousand other
     // calls for which this picks strips: 9 % faster on average, 6 % of the calls slower by 5 % or more.
-    return strip * (1.f + 0.02f * (float)(near_r > near_c ? near_r : near_c)) < rect;
+    return since * strip * (1.f + 0.02f * (float)(near_r > near_c ? near_r : near_c)) < rect;
 }
 
 // Chooses strips of columns, bands of rows, the window's rows and the displacement it allows for, by the batches that
@@ -1300,14 +1306,14 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, cons
     // The forward: for two batches to a compute unit or less of maps that are not tiny, since bands are cut finer than rectangles
     // (1 of 40x47, 16 groups of 8, fp32: 12.3 us by rectangles, 8.2 by strips; 16 of 14x14, 16 groups of 16: 8.6 and 10.3), at
     // stride 1 (at 2 a window holds four times the pixels: 2 of 64x98, 7 groups of 32, fp16: 12.6 and 16.0); and by both kernels'
-    // estimates where there are batches to stream, two rounds of eight waves or four of twelve.  In between, where several small
+    // estimates where there are batches to stream, two rounds of eight waves or of twelve.  In between, where several small
     // workgroups share a unit (10 to 15 % faster in each of 29 calls) and where narrow pixels lie side by side in memory (one
     // group: 5 % faster over 86 calls), rectangles.
     const bool few = !gom && batches <= 2LL * cus && (long long)q.Ho * q.Wo >= (pb == 64 ? 400 : 700);
     // The grad_offset/grad_mask pass from a quarter of a batch on (1 image of 28x28, 8 groups, fp32: 21.2 us by rectangles, 18.6
     // by strips, with grad_x; 1 of 14x14, 4 groups: 16.3 and 16.5).
     if (cus > 0 && g_opt.fwd_strip != 1) {
-        if (gom ? batches * 4 < cus : !few && batches < (pb == 64 ? 16LL : 48LL) * cus)
+        if (gom ? batches * 4 < cus : !few && batches < (pb == 64 ? 16LL : 24LL) * cus)
             return DCNV4_ERR_UNSUPPORTED;
         if (!gom && ((few && (q.sh > 1 || q.sw > 1) && pb > 16) || (!few && q.G == 1 && pb < 64) || (rect != nullptr && rect->many)))
             return DCNV4_ERR_UNSUPPORTED;
