@@ -1124,6 +1124,32 @@ def test_grad_x_tiles(cfg, dtype, opts):
     close(f"{cfg.name}/{dtype}/grad_x", gom[0].cpu().numpy(), rgx, TOL[dtype])
 
 
+@pytest.mark.parametrize("own", [1, 2], ids=["stored", "added"])
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_grad_x_pairs_of_channels_of_either_sign(own, dtype):
+    """Two channels share a 64-bit sum, the even one's sign carried into the odd one's: even channels all negative, odd ones
+    tiny or of either sign, terms up to the largest that enter the sums.  Bound: 2^-22 for each of a pixel's terms (at most all
+    nine of each of the 99 outputs) and fp32's roundings of their magnitudes, in fp16 one rounding of the result for each place a
+    sum is added to memory in parts."""
+    cfg = Config("gx_pairs", N=2, H=9, W=11, C=32, G=2)
+    t = make_inputs(cfg, dtype, seed=13)
+    gy = t["grad_y"]
+    gy[..., 0::2] = -np.abs(gy[..., 0::2]) * 6
+    gy[..., 1::4] = gy[..., 1::4] / 1024
+    t["mask"][0] *= 3
+    d = to_gpu(t, dtype)
+    dcn.dcnv4_set_option("bwd_path", 2)
+    dcn.dcnv4_set_option("gx_own", own)
+    gx = dcn.dcnv4_backward(d["x"], d["offset"], d["mask"], d["grad_y"], **geo_kw(cfg))[0]
+    torch.cuda.synchronize()
+    assert "dcnv4_gradx_kernel" in dcn.dcnv4_last_kernel_name(1)
+    ref = oracle.backward(t["x"], t["offset"], t["mask"], gy, **geo_kw(cfg))[0]
+    size = oracle.backward(t["x"], t["offset"], np.abs(t["mask"]), np.abs(gy), **geo_kw(cfg))[0]
+    lim = 99 * 9 * 2.0 ** -22 + size * (2.0 ** -20 if dtype == "f32" else 2.0 ** -8)
+    err = np.abs(gx.cpu().numpy().astype(np.float64) - ref)
+    assert (err <= lim).all(), (err / lim).max()
+
+
 # All tiles of an (image, channel run) by one workgroup, which stores its sums: bands that overlap, taps past the halo and terms
 # too big for the fixed-point sums (both go straight to memory, before and after the stores), tiles split in columns (gx_wide120:
 # grad_x is cleared then), bands wholly above and below the image (gx_pad, gx_thin_pad), one-wave workgroups on many small maps.
