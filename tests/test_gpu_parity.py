@@ -1150,6 +1150,31 @@ def test_grad_x_pairs_of_channels_of_either_sign(own, dtype):
     assert (err <= lim).all(), (err / lim).max()
 
 
+def test_fp32_grad_x_beyond_the_window_asks_for_whole_runs_of_channels():
+    """Corners that go straight to memory take a pixel's 16 channels, 64 bytes, in one instruction.  A backward pass with most of
+    them (offsets of 8 pixels, windows that allow for 5) against one with hardly any (1 pixel) took 2.5 times as long, and 3.8 times
+    with even and odd channels apart."""
+    gen = torch.Generator(device="cuda").manual_seed(15)
+    rand = lambda *shape: torch.randn(shape, generator=gen, device="cuda")
+    x, gy, m = rand(1, 128, 140, 96), rand(1, 128, 140, 96), rand(1, 128, 140, 6, 9)
+    near = rand(1, 128, 140, 6, 9, 2)
+    times = []
+    for off in (near, 8 * near):
+        out = (torch.empty_like(x), torch.empty_like(off), torch.empty_like(m))
+        best = float("inf")
+        for _ in range(12):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(20):
+                dcn.dcnv4_backward(x, off, m, gy, out=out)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end))
+        times.append(best)
+    assert dcn.dcnv4_last_kernel_name(1).endswith(" + dcnv4_gradx_kernel<float, 4>"), dcn.dcnv4_last_kernel_name(1)
+    assert times[1] < 3.2 * times[0], times
+
+
 # All tiles of an (image, channel run) by one workgroup, which stores its sums: bands that overlap, taps past the halo and terms
 # too big for the fixed-point sums (both go straight to memory, before and after the stores), tiles split in columns (gx_wide120:
 # grad_x is cleared then), bands wholly above and below the image (gx_pad, gx_thin_pad), one-wave workgroups on many small maps.
