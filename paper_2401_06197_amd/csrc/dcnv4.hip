@@ -1270,28 +1270,47 @@ ForwardTimes forward_times(int dtype, int pb)
                                   : ForwardTimes{4.21f, 1.82f, 1.05f, 3.17f, 2.80f, 2.31f, 3.51f, 0.84f, 0.16f, 2.10f, 6.93f};
     return ForwardTimes{3.80f, 0.00f, 0.88f, 1.98f, 2.89f, 2.78f, 0.00f, 1.36f, 0.00f, 2.67f, 6.29f};
 }
+// The same once more where strips have become faster since, fitted to 13 thousand random calls in which both kernels launch
+// (16 batches of 64-byte pixels a unit and more, 24 of narrower ones): 64-byte pixels by the times at offsets of 4 pixels, which cost
+// strips most, others by the mean over 1, 2 and 4.  Their ratio within 6, 4 and 6 %.  `strip_near` counts columns too.
+ForwardTimes strip_times_now(int pb)
+{
+    if (pb == 64)
+        return ForwardTimes{2.93f, 3.35f, 1.11f, 4.37f, 3.09f, 3.29f, 2.53f, 1.54f, 0.49f, 1.59f, 7.33f};
+    if (pb == 32)
+        return ForwardTimes{4.17f, 4.75f, -0.29f, 6.10f, -4.30f, 2.03f, 1.98f, 2.38f, 0.31f, 5.94f, -0.83f};
+    return ForwardTimes{2.83f, 6.89f, -0.27f, 3.38f, 0.74f, 1.59f, -0.23f, 1.87f, 0.21f, 5.49f, 2.79f};
+}
 bool strips_win(const Problem &q, const TGeo &r, int rect_waves, const SGeo &p, int waves, long long busiest, int pb, long long batches, int cus)
 {
-    const ForwardTimes t = forward_times(q.dtype, pb);
     const float mean = (float)batches / (float)(cus * waves);
     const float tiles = (float)((r.nblocks + cus - 1) / cus), rounds = (float)((r.R * r.Q + 63) / 64) / rect_waves;
-    const float rect = tiles * (t.rect_rounds * rounds + t.rect_staged * (float)r.xtile_bytes * (1.f / 65536) + t.rect_tiles) +
-                       t.rect_mean * mean + t.rect_once;
     const int near_r = p.halo_r < 7 ? 7 - p.halo_r : 0, near_c = p.tiles_q > 1 && p.halo_c < 7 ? 7 - p.halo_c : 0;
     const float staged = (float)((p.ntiles + cus - 1) / cus) * (float)p.VR * (float)p.row_lds * (1.f / 65536);
-    const float strip = t.strip_whole * (float)((busiest + waves - 1) / waves) +
-                        (t.strip_rounds + t.strip_near * near_r) * (float)busiest / waves + t.strip_staged * staged +
-                        t.strip_mean * mean + t.strip_once;
-    // (The fit is of strips whose rounds read their arguments piece by piece.  Since then they take less: by 0.89 in fp32 and for
-    // 16-byte pixels, the factor with the fewest misses of 0.84 to 1, where every unit has a tile.  With it, and narrow pixels asked
-    // from 24 batches to a unit on instead of 48, the launched kernel is 2.6 % slower than the better of the two over 500 random
-    // calls, before 3.3 %; the 37 that changed kernels are 9 % faster on average, three of them 5 to 7 % slower, offsets of 4 pixels
-    // among them: fp32 5 x 74x116x256, 8 groups 67.4 -> 70.9 us; 30 x 75x59x80, 5 groups 69.9 -> 75.1.)
-    const float since = (q.dtype == DCNV4_F32 || pb == 16) && p.ntiles >= cus ? 0.89f : 1.f;
+    auto rect = [&](const ForwardTimes &t) {
+        return tiles * (t.rect_rounds * rounds + t.rect_staged * (float)r.xtile_bytes * (1.f / 65536) + t.rect_tiles) +
+               t.rect_mean * mean + t.rect_once;
+    };
+    auto strip = [&](const ForwardTimes &t, int near) {
+        return t.strip_whole * (float)((busiest + waves - 1) / waves) + (t.strip_rounds + t.strip_near * (float)near) * (float)busiest / waves +
+               t.strip_staged * staged + t.strip_mean * mean + t.strip_once;
+    };
     // A margin for windows that allow for small displacements: offsets of 4 pixels cost the strips most there (64-byte pixels in
     // fp32, allowing for 4: 6 % faster than rectangles at offsets of 1 and 2 pixels, 7 % slower at 4).  Over a thousand other
     // calls for which this picks strips: 9 % faster on average, 6 % of the calls slower by 5 % or more.
-    return since * strip * (1.f + 0.02f * (float)(near_r > near_c ? near_r : near_c)) < rect;
+    const ForwardTimes t = forward_times(q.dtype, pb);
+    if (strip(t, near_r) * (1.f + 0.02f * (float)(near_r > near_c ? near_r : near_c)) < rect(t))
+        return true;
+    // And what the strips' present times add to that, by a margin of the fit's error, so that a call is hardly ever slower than
+    // through its rectangles: of those 13 thousand calls 1331 come here, at offsets of 1, 2 and 4 pixels 0.91, 0.91 and 0.94 times as
+    // long, 77 of them more than 3 % longer at one of the three.  (A factor of 0.89 on the first estimate: 2469 calls, 0.93, 0.94 and
+    // 1.00 times as long, and 768 of them 3 to 32 % longer.)  fp32, offsets of 1, 2 and 4 pixels: 5 x 74x116x256, 8 groups, stays with
+    // rectangles (65, 66 and 67 us; strips 61, 63 and 71).
+    // Not with strides, which are not among them (fp16 1 x 155x271x360, 45 groups, stride 2: rectangles 38 us, strips 50).
+    if ((q.dtype != DCNV4_F32 && pb != 16) || q.sh > 1 || q.sw > 1)
+        return false;
+    const ForwardTimes now = strip_times_now(pb);
+    return strip(now, near_r + near_c) < (pb == 64 ? 0.95f : 0.94f) * rect(now);
 }
 
 // Chooses strips of columns, bands of rows, the window's rows and the displacement it allows for, by the batches that
@@ -1306,9 +1325,11 @@ int make_sgeo(const Problem &q, int cg_kernel, int waves, StripLaunch *out, cons
     // The forward: for two batches to a compute unit or less of maps that are not tiny, since bands are cut finer than rectangles
     // (1 of 40x47, 16 groups of 8, fp32: 12.3 us by rectangles, 8.2 by strips; 16 of 14x14, 16 groups of 16: 8.6 and 10.3), at
     // stride 1 (at 2 a window holds four times the pixels: 2 of 64x98, 7 groups of 32, fp16: 12.6 and 16.0); and by both kernels'
-    // estimates where there are batches to stream, two rounds of eight waves or of twelve.  In between, where several small
-    // workgroups share a unit (10 to 15 % faster in each of 29 calls) and where narrow pixels lie side by side in memory (one
-    // group: 5 % faster over 86 calls), rectangles.
+    // estimates where there are batches to stream, two rounds of eight waves or of twelve (narrow pixels, 24 to 48 batches a unit:
+    // 372 random calls that the first estimate takes there 0.81, 0.81 and 0.85 times as long at offsets of 1, 2 and 4 pixels, four
+    // of them more than 3 % longer, at 4).  In between, where several small workgroups share a unit and where narrow pixels lie
+    // side by side in memory (one group: 5 % faster over 86 calls), rectangles.  (Strips in place of several small workgroups, 3256
+    // random calls: below 64 batches a unit 1.02 to 1.05 times as long, above 0.96 to 0.98: the line could lie there.)
     const bool few = !gom && batches <= 2LL * cus && (long long)q.Ho * q.Wo >= (pb == 64 ? 400 : 700);
     // The grad_offset/grad_mask pass from a quarter of a batch on (1 image of 28x28, 8 groups, fp32: 21.2 us by rectangles, 18.6
     // by strips, with grad_x; 1 of 14x14, 4 groups: 16.3 and 16.5).

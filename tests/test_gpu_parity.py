@@ -638,6 +638,19 @@ def test_forward_by_the_estimates_of_both_kernels(cfg, dtype, kernel):
     assert dcn.dcnv4_last_kernel_name(0).startswith(kernel)
 
 
+@pytest.mark.parametrize("cfg,dtype,kernel", [
+    (Config("fp_74", N=5, H=74, W=116, C=256, G=8, sigma=4.0), "f32", "dcnv4_tiled_kernel<"),     # us, offsets of 4 pixels: 67 and 71
+    (Config("fp_49", N=15, H=49, W=80, C=96, G=3, sigma=4.0), "f32", "dcnv4_tiled_kernel<"),      # 40 and 46
+    (Config("fp_43", N=1, H=179, W=145, C=344, G=43), "f16", "dcnv4_tiled_kernel<"),              # 48 and 56
+    (Config("fp_s2", N=1, H=155, W=271, C=360, G=45, stride=2), "f16", "dcnv4_tiled_kernel<"),    # 38 and 50
+    (Config("fp_60", N=7, H=60, W=87, C=192, G=12, sigma=4.0), "f32", "dcnv4_strip_kernel<"),     # rectangles take 1.05 times as long
+    (Config("fp_24", N=1, H=101, W=64, C=632, G=79), "f16", "dcnv4_strip_kernel<"),               # 31 batches a unit: 1.20 times
+], ids=lambda v: getattr(v, "name", ""))
+def test_forward_strips_where_no_size_of_offsets_makes_them_slower(cfg, dtype, kernel):
+    check_forward(cfg, dtype, seed=88)
+    assert dcn.dcnv4_last_kernel_name(0).startswith(kernel), dcn.dcnv4_last_kernel_name(0)
+
+
 # Whole images of 64-byte pixels, more of them than compute units, in small workgroups: one wave for one or two batches, four
 # waves to as large as two rectangles fit the LDS (31x31), with strides and samples far outside.
 SMALL_GROUPS = [(Config("sg_49", N=9, H=7, W=7, C=1024, G=32), 64), (Config("sg_128", N=5, H=8, W=16, C=1024, G=32, sigma=4.0), 64),
