@@ -166,8 +166,11 @@ def _stream_ptr(stream, device):
     import torch
     if stream is not None:
         return stream.cuda_stream
-    # (the handle itself: a Stream object around it takes 1.9 us)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if device.index is None else device.index)
+    # (the handle itself, where torch gives it: the function is not part of its interface.  A Stream object around it takes 1.9 us)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return raw(torch.cuda.current_device() if device.index is None else device.index)
 
 
 def _call(device, entry, args):

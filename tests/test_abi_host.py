@@ -186,3 +186,17 @@ def test_missing_library_is_an_error_not_a_fallback(monkeypatch):
     monkeypatch.setattr(dcn, "LIB_PATH", "/nonexistent/libdcnv4.so")
     with pytest.raises(ImportError):
         dcn.load_library()
+
+
+def test_current_stream_without_torchs_private_function(monkeypatch):
+    """The handle comes from a function that torch may drop: then from the stream object."""
+    import torch
+
+    class Stream:
+        cuda_stream = 4711
+
+    asked = []
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device: asked.append(device) or Stream)
+    assert dcn._stream_ptr(None, torch.device("cuda:1")) == 4711 and asked == [torch.device("cuda:1")]
+    assert dcn._stream_ptr(Stream, torch.device("cuda:0")) == 4711
