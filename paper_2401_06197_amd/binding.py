@@ -162,6 +162,13 @@ def _check_all(x, named):
             _check(name, t, x)
 
 
+def _uninitialised(x, shape):
+    """A plain tensor of x's type on its device, whatever subclass x is of.  (new_empty keeps the subclass; it takes 1.2 us where
+    torch.empty takes 1.6.)"""
+    import torch
+    return x.new_empty(shape) if type(x) is torch.Tensor else torch.empty(shape, dtype=x.dtype, device=x.device)
+
+
 def _stream_ptr(stream, device):
     import torch
     if stream is not None:
@@ -224,11 +231,10 @@ def dcnv4_forward(x, offset, mask, kernel=3, stride=1, pad=1, dilation=1, offset
 
     With prepare_only the checked argument tuple for load_library().dcnv4_forward is returned
     instead of launching (for launch loops that must not pay the checks every time)."""
-    import torch
     geo, yshape = _shape_args(x, offset, mask, kernel, stride, pad, dilation)
     _check_all(x, (("offset", offset), ("mask", mask)))
     if out is None:
-        out = x.new_empty(yshape)
+        out = _uninitialised(x, yshape)
     else:
         _check("out", out, x)
         if tuple(out.shape) != yshape:
@@ -295,11 +301,10 @@ def dcnv4_forward_merged(x, offset_mask, kernel=3, stride=1, pad=1, dilation=1, 
                          prepare_only=False):
     """dcnv4_forward with the offsets and mask values in one tensor [N,Ho,Wo,G,32]: 18 offsets, 9 mask
     values, 5 unused entries per (pixel, group)."""
-    import torch
     geo, yshape = _merged_shape_args(x, offset_mask, kernel, stride, pad, dilation)
     _check_all(x, (("offset_mask", offset_mask),))
     if out is None:
-        out = x.new_empty(yshape)
+        out = _uninitialised(x, yshape)
     else:
         _check("out", out, x)
         if tuple(out.shape) != yshape:

@@ -472,6 +472,19 @@ def test_runs_on_a_side_stream():
     close("stream/y", y.cpu().numpy(), ref, TOL["f16"])
 
 
+@pytest.mark.parametrize("merged", [False, True], ids=["separate", "merged"])
+def test_forward_of_a_tensor_subclass_gives_a_plain_tensor(merged):
+    class Tagged(torch.Tensor):
+        pass
+
+    cfg = Config("sub", N=1, H=6, W=5, C=32, G=2)
+    d = to_gpu(make_inputs(cfg, "f32", seed=16), "f32")
+    om = torch.cat([d["offset"].flatten(4), d["mask"], torch.zeros(1, 6, 5, 2, 5, device="cuda")], 4)
+    for x in (d["x"].as_subclass(Tagged), torch.nn.Parameter(d["x"]), d["x"]):
+        y = dcn.dcnv4_forward_merged(x, om) if merged else dcn.dcnv4_forward(x, d["offset"], d["mask"])
+        assert type(y) is torch.Tensor and not y.requires_grad
+
+
 @pytest.mark.parametrize("opts", [{}, {"bwd_path": 2, "gx_own": 1}, {"bwd_path": 2, "gx_own": 1, "halo": 1, "lds_kb": 40}],
                          ids=["default", "owned", "owned_bands"])
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
