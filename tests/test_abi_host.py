@@ -200,3 +200,13 @@ def test_current_stream_without_torchs_private_function(monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_stream", lambda device: asked.append(device) or Stream)
     assert dcn._stream_ptr(None, torch.device("cuda:1")) == 4711 and asked == [torch.device("cuda:1")]
     assert dcn._stream_ptr(Stream, torch.device("cuda:0")) == 4711
+
+
+@pytest.mark.parametrize("entry,shapes", [
+    ("dcnv4_forward", [(1, 6, 5, 32), (1, 6, 5, 2, 9, 2), (1, 6, 5, 2, 9)]), ("dcnv4_forward_merged", [(1, 6, 5, 32), (1, 6, 5, 2, 32)]),
+    ("dcnv4_backward", [(1, 6, 5, 32), (1, 6, 5, 2, 9, 2), (1, 6, 5, 2, 9), (1, 6, 5, 32)]),
+    ("dcnv4_backward_merged", [(1, 6, 5, 32), (1, 6, 5, 2, 32), (1, 6, 5, 32)])])
+def test_host_tensors_are_refused(entry, shapes):
+    import torch
+    with pytest.raises(ValueError, match="x must be a GPU tensor"):
+        getattr(dcn, entry)(*(torch.zeros(s) for s in shapes))
