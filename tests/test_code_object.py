@@ -45,7 +45,7 @@ def test_arguments_of_the_rectangle_forward_stay_within_512_bytes(kernels):
 
 def test_scratch_memory(kernels):
     """Registers kept in scratch memory, bytes a lane: none but those named here."""
-    allowed = {"tiled_kernelIfLi16ELi512ELi3E": 8, "tiled_kernelIfLi8ELi512ELi1E": 56, "tiled_kernelIDF16_Li32ELi768ELi2E": 24}
+    allowed = {"tiled_kernelIfLi16ELi512ELi3E": 8, "tiled_kernelIfLi8ELi512ELi1E": 48}
     for name, k in kernels.items():
         limit = next((v for part, v in allowed.items() if part in name), 0)
         assert k["private_segment_fixed_size"] <= limit, (name, k["private_segment_fixed_size"])
