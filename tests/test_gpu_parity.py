@@ -1220,7 +1220,7 @@ def test_grad_x_pairs_of_channels_of_either_sign(own, dtype, terms):
 
 def test_fp32_grad_x_beyond_the_window_asks_for_whole_runs_of_channels():
     """Corners that go straight to memory take a pixel's 16 channels, 64 bytes, in one instruction.  A backward pass with most of
-    them (offsets of 8 pixels, windows that allow for 5) against one with hardly any (1 pixel) took 2.5 times as long, and 3.8 times
+    them (offsets of 8 pixels, windows that allow for 5) against one with hardly any (1 pixel) took 2.5 to 2.7 times as long, and 3.8 times
     with even and odd channels apart."""
     gen = torch.Generator(device="cuda").manual_seed(15)
     rand = lambda *shape: torch.randn(shape, generator=gen, device="cuda")
@@ -1240,7 +1240,7 @@ def test_fp32_grad_x_beyond_the_window_asks_for_whole_runs_of_channels():
             best = min(best, start.elapsed_time(end))
         times.append(best)
     assert dcn.dcnv4_last_kernel_name(1).endswith(" + dcnv4_gradx_kernel<float, 4>"), dcn.dcnv4_last_kernel_name(1)
-    assert times[1] < 3.2 * times[0], times
+    assert times[1] < 3.3 * times[0], times
 
 
 # All tiles of an (image, channel run) by one workgroup, which stores its sums: bands that overlap, taps past the halo and terms
